@@ -4,123 +4,212 @@
 //   repack_kernel     : canonical [K,N] stream -> tiled device layout
 //                       (paper, Section "Efficient Low-Precision Weight Loading",
 //                       the "Change Layout" pre-processing step)
+// Both are bound by memory: a weight passes through each once when a model is loaded.
 #include "qg_common.h"
+#include "qg_static_for.h"
 
 namespace qg {
 
-// Eight consecutive codes fill exactly `bits` bytes; one thread writes them.
-__global__ __launch_bounds__(256) void pack_codes_kernel(const uint8_t* __restrict__ codes, int bits,
-                                                         int64_t count, uint8_t* __restrict__ out,
-                                                         int64_t out_bytes) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t e0 = g * 8;
-  if (e0 >= count) return;
-  const uint32_t mask = (1u << bits) - 1u;
-  uint64_t acc = 0;
-  for (int i = 0; i < 8; ++i) {
-    uint64_t c = (e0 + i < count) ? (codes[e0 + i] & mask) : 0u;
-    acc |= c << (i * bits);
+// Vector loads and stores that assume no alignment (the hardware takes any address; the
+// canonical stream and the codes may start anywhere).
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u2_any __attribute__((ext_vector_type(2), aligned(1)));
+
+// Four codes, one per byte of x, as 4*BITS adjacent bits.
+template <int BITS>
+__device__ __forceinline__ uint32_t squeeze4(uint32_t x) {
+  if constexpr (BITS == 8) return x;
+  constexpr uint32_t M = (1u << BITS) - 1u;
+  const uint32_t p = (x & (M * 0x00010001u)) | ((x >> (8 - BITS)) & ((M << BITS) * 0x00010001u));
+  constexpr uint32_t M2 = (1u << (2 * BITS)) - 1u;
+  return (p & M2) | ((p >> (16 - 2 * BITS)) & (M2 << (2 * BITS)));
+}
+
+// 32 consecutive codes fill exactly BITS dwords.  A thread squeezes 32 codes (two 16-byte loads)
+// and a workgroup meets in LDS so that the stream leaves in 16-byte stores of whole cache lines.
+// Bound by memory: on K = 8192, N = 28672 the codes of 5 bits take 66 us = 5.7 TB/s read and written
+// (4 bits 60, 8 bits 81; a large device copy moves 5.0 TB/s).  With a thread that gathered eight
+// codes byte by byte and stored bytes it was 207 (187, 253) us: byte-wide accesses.
+constexpr int PACK_CODES = 256 * 32;      // codes per workgroup
+template <int BITS>
+__global__ __launch_bounds__(256) void pack_codes_kernel(const uint8_t* __restrict__ codes, int64_t count,
+                                                         uint8_t* __restrict__ out, int64_t out_bytes) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[256 * BITS];
+  const int tid = threadIdx.x;
+  const int64_t e0 = (int64_t)blockIdx.x * PACK_CODES;
+  const uint8_t* src = codes + e0 + 32 * tid;
+  uint32_t x[8];
+  const bool whole = e0 + PACK_CODES <= count;
+  if (whole) {
+    const u4_any a = reinterpret_cast<const u4_any*>(src)[0], b = reinterpret_cast<const u4_any*>(src)[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { x[i] = a[i]; x[4 + i] = b[i]; }
+  } else {                                // the last workgroup: codes past the end count as zero
+    const int64_t left = count - e0 - 32 * tid;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      x[i] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * i + e < left) x[i] |= (uint32_t)src[4 * i + e] << (8 * e);
+    }
   }
-  int64_t b0 = g * bits;
-  for (int i = 0; i < bits; ++i)
-    if (b0 + i < out_bytes) out[b0 + i] = (uint8_t)(acc >> (8 * i));
+  uint32_t r[BITS];
+#pragma unroll
+  for (int d = 0; d < BITS; ++d) r[d] = 0;
+  static_for<8>([&](auto Ic) __attribute__((always_inline)) {
+    constexpr int bit = decltype(Ic)::value * 4 * BITS, h = bit >> 5, p = bit & 31;
+    const uint32_t q = squeeze4<BITS>(x[decltype(Ic)::value]);
+    r[h] |= q << p;
+    if constexpr (p + 4 * BITS > 32) r[h + 1] |= q >> (32 - p);
+  });
+#pragma unroll
+  for (int d = 0; d < BITS; ++d) lds[tid * BITS + d] = r[d];
+  __syncthreads();
+  uint8_t* dst = out + (int64_t)blockIdx.x * (1024 * BITS);
+  if (whole) {
+    for (int u = tid; u < 64 * BITS; u += 256)
+      reinterpret_cast<u4_any*>(dst)[u] = reinterpret_cast<const u4_any*>(lds)[u];
+  } else {
+    const int64_t left = out_bytes - (int64_t)blockIdx.x * (1024 * BITS);
+    for (int i = tid; i < 1024 * BITS && i < left; i += 256) dst[i] = reinterpret_cast<const uint8_t*>(lds)[i];
+  }
 }
 
-__device__ __forceinline__ uint32_t fetch_code(const uint8_t* __restrict__ canon, int64_t canon_bytes,
-                                               int64_t elem, int bits) {
-  int64_t bit = elem * bits;
-  int64_t byte = bit >> 3;
-  int sh = (int)(bit & 7);
-  uint32_t w = canon[byte];
-  if (sh + bits > 8 && byte + 1 < canon_bytes) w |= (uint32_t)canon[byte + 1] << 8;
-  return (w >> sh) & ((1u << bits) - 1u);
-}
+// How the codes of a lane are arranged (see qg_common.h for the element <-> (chunk, lane, pair) maps).
+enum RepackMode {
+  REPACK_STREAMS = 0,   // first layout, two 16-bit streams
+  REPACK_PLAIN = 1,     // first layout, plain order (types with a hardware convert, codebook indices)
+  REPACK_R32 = 2,       // second layout, two 16-bit streams
+  REPACK_R32_PLAIN = 3,
+  REPACK_I8 = 4,        // third layout, four byte streams
+  NUM_REPACK = 5
+};
 
-// One thread builds one lane's 4*bits dwords of one chunk (see qg_common.h for
-// the element <-> (chunk, lane, pair) map) and writes them where load i of that
-// lane will find them.
-__global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__ canon, int64_t canon_bytes,
-                                                     uint32_t* __restrict__ out, int bits, int K, int N,
-                                                     uint32_t flip, int natural, int layout) {
-  const int KC = K / TILE_K;
-  const int64_t nchunks = (int64_t)KC * (N / TILE_N);
-  int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t chunk = gid >> 6;
-  if (chunk >= nchunks) return;
-  const int l = (int)(gid & 63);
-  const int nc = (int)(chunk / KC), kc = (int)(chunk % KC);
-  uint32_t* dst = out + chunk * (256 * bits);
-  if (layout == QG_LAYOUT_TILE128x64_I8) {
-    // four parallel byte streams: quad t at bits [t*bits, (t+1)*bits) of byte lane e of the registers
-    for (int d = 0; d < 4 * bits; ++d) {
-      uint32_t word = 0;
-      int t0 = (8 * d) / bits, t1 = (8 * d + 7) / bits;
-      if (t1 > QUADS - 1) t1 = QUADS - 1;
-      for (int t = t0; t <= t1; ++t) {
-        const int n = TILE_N * nc + quad_n(l, t);
-        const int sh = t * bits - 8 * d;
-        for (int e = 0; e < 4; ++e) {
-          const int k = TILE_K * kc + quad_k(l, t) + e;
-          const uint32_t code = fetch_code(canon, canon_bytes, (int64_t)k * N + n, bits) ^ flip;
-          const uint32_t part = ((sh >= 0) ? (code << sh) : (code >> (-sh))) & 0xffu;
-          word |= part << (8 * e);
+// One wavefront builds one chunk.  A lane's columns are adjacent (four of them, two in the second
+// layout), so what it needs of a row is ONE field of the canonical stream; a row's 64 columns of a
+// chunk are 8*BITS bytes, read once by the 16 (32) lanes of a k-block.  A lane fetches the
+// 8-byte window that holds its field from each of its 32 (64) rows -- all independent loads -- and
+// places the codes at bit positions known at compile time.  The four wavefronts of a workgroup
+// take adjacent strips of the same rows, and workgroups are dealt out so that one XCD gets a run
+// of them: the parts of a cache line that several strips need meet in that XCD's L2.
+// Bound by memory from 4 bits on (K = 8192, N = 28672: 72 us = 4.1 TB/s at 5 bits, 98 us = 4.8 at 8;
+// narrower codes by the number of row windows, which does not shrink with them: 33 us at 1 bit).
+// A thread that fetched every code by itself with two byte loads took 389 / 274 / 111 us.
+template <int BITS, int MODE>
+__global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__ canon, uint4* __restrict__ out, int K, int N,
+                                                     uint32_t flip, int groups_n, int64_t total, int64_t per_xcd) {
+  constexpr int COLS = (MODE == REPACK_R32 || MODE == REPACK_R32_PLAIN) ? 2 : 4;     // adjacent columns of a lane
+  constexpr int LANES = TILE_N / COLS;                                               // lanes per k-block
+  constexpr uint32_t CODE = (1u << BITS) - 1u;
+  const int64_t logical = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (logical >= total) return;
+  const int l = threadIdx.x & 63;
+  const int kc = (int)(logical / groups_n);
+  const int nc = (int)(logical % groups_n) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (nc >= N / TILE_N) return;
+  const int i = l % LANES, b = l / LANES;
+  const int64_t row_bytes = (int64_t)(N / 8) * BITS;
+  // the 8-byte window that holds my field, inside the segment; SH: the field's place in it
+  const int fbit = COLS * i * BITS, dw = min(fbit >> 5, 2 * BITS - 2), sh = fbit - 32 * dw;
+  const uint8_t* src = canon + (int64_t)TILE_K * kc * row_bytes + (int64_t)nc * (8 * BITS) + 4 * dw;
+  uint32_t flips = flip;
+#pragma unroll
+  for (int c = 1; c < COLS; ++c) flips |= flip << (c * BITS);
+  auto field = [&](int k) __attribute__((always_inline)) {
+    const u2_any v = *reinterpret_cast<const u2_any*>(src + k * row_bytes);
+    return (uint32_t)((((uint64_t)v.y << 32) | v.x) >> sh) ^ flips;
+  };
+  uint32_t r[4 * BITS];
+#pragma unroll
+  for (int d = 0; d < 4 * BITS; ++d) r[d] = 0;
+  if constexpr (MODE == REPACK_I8) {
+    static_for<8>([&](auto Gc) __attribute__((always_inline)) {
+      constexpr int J = decltype(Gc)::value / 4, V = decltype(Gc)::value % 4;
+      uint32_t f[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = field(64 * J + 16 * b + 4 * V + e);
+      static_for<4>([&](auto Nc) __attribute__((always_inline)) {
+        constexpr int NT = decltype(Nc)::value, bit = ((J * 4 + NT) * 4 + V) * BITS, h = bit >> 3, p = bit & 7;
+        uint32_t q = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q |= ((f[e] >> (NT * BITS)) & CODE) << (8 * e);
+        if constexpr (p + BITS <= 8) {
+          r[h] |= q << p;
+        } else {                          // the code straddles a byte of its stream
+          constexpr int n1 = 8 - p;
+          r[h] |= (q & (((1u << n1) - 1u) * 0x01010101u)) << p;
+          r[h + 1] |= (q >> n1) & ((CODE >> n1) * 0x01010101u);
         }
-      }
-      dst[(d >> 2) * 256 + l * 4 + (d & 3)] = word;
-    }
-    return;
+      });
+    });
+  } else {
+    static_for<64 / COLS>([&](auto Gc) __attribute__((always_inline)) {
+      constexpr int J = decltype(Gc)::value / 4, V = decltype(Gc)::value % 4;
+      const int k = (COLS == 4 ? 32 : 16) * J + 8 * b + 2 * V;
+      const uint32_t f0 = field(k), f1 = field(k + 1);
+      static_for<COLS>([&](auto Nc) __attribute__((always_inline)) {
+        constexpr int NT = decltype(Nc)::value, T = (J * COLS + NT) * 4 + V;
+        const uint32_t lo = (f0 >> (NT * BITS)) & CODE, hi = (f1 >> (NT * BITS)) & CODE;
+        if constexpr (MODE == REPACK_PLAIN || MODE == REPACK_R32_PLAIN) {
+          constexpr int bit = 2 * T * BITS, h = bit >> 5, p = bit & 31;
+          const uint32_t q = lo | (hi << BITS);
+          r[h] |= q << p;
+          if constexpr (p + 2 * BITS > 32) r[h + 1] |= q >> (32 - p);
+        } else {
+          constexpr int bit = T * BITS, h = bit >> 4, p = bit & 15;
+          const uint32_t q = lo | (hi << 16);
+          if constexpr (p + BITS <= 16) {
+            r[h] |= q << p;
+          } else {                        // the code straddles a register half of its stream
+            constexpr int n1 = 16 - p;
+            r[h] |= (q & (((1u << n1) - 1u) * 0x00010001u)) << p;
+            r[h + 1] |= (q >> n1) & ((CODE >> n1) * 0x00010001u);
+          }
+        }
+      });
+    });
   }
-  if (natural) {
-    // plain order: code c = 2t + {0 lo, 1 hi} of the lane at bits [c*bits, (c+1)*bits)
-    for (int d = 0; d < 4 * bits; ++d) {
-      uint32_t word = 0;
-      int c0 = (32 * d) / bits, c1 = (32 * d + 31) / bits;
-      if (c1 > 2 * PAIRS - 1) c1 = 2 * PAIRS - 1;
-      for (int c = c0; c <= c1; ++c) {
-        int t = c >> 1;
-        int k = TILE_K * kc + pair_k(layout, l, t) + (c & 1);
-        int n = TILE_N * nc + pair_n(layout, l, t);
-        uint32_t code = fetch_code(canon, canon_bytes, (int64_t)k * N + n, bits);
-        int sh = c * bits - 32 * d;
-        word |= (sh >= 0) ? (code << sh) : (code >> (-sh));
-      }
-      dst[(d >> 2) * 256 + l * 4 + (d & 3)] = word;
-    }
-    return;
-  }
-  for (int d = 0; d < 4 * bits; ++d) {
-    uint32_t lo = 0, hi = 0;
-    int t0 = (16 * d) / bits, t1 = (16 * d + 15) / bits;
-    if (t1 > PAIRS - 1) t1 = PAIRS - 1;
-    for (int t = t0; t <= t1; ++t) {
-      int k = TILE_K * kc + pair_k(layout, l, t);
-      int n = TILE_N * nc + pair_n(layout, l, t);
-      uint32_t clo = fetch_code(canon, canon_bytes, (int64_t)k * N + n, bits) ^ flip;
-      uint32_t chi = fetch_code(canon, canon_bytes, (int64_t)(k + 1) * N + n, bits) ^ flip;
-      int sh = t * bits - 16 * d;
-      if (sh >= 0) { lo |= clo << sh; hi |= chi << sh; }
-      else         { lo |= clo >> (-sh); hi |= chi >> (-sh); }
-    }
-    dst[(d >> 2) * 256 + l * 4 + (d & 3)] = (lo & 0xffffu) | (hi << 16);
-  }
+  uint4* dst = out + ((int64_t)nc * (K / TILE_K) + kc) * (64 * BITS) + l;
+#pragma unroll
+  for (int d = 0; d < BITS; ++d) dst[64 * d] = make_uint4(r[4 * d], r[4 * d + 1], r[4 * d + 2], r[4 * d + 3]);
 }
 
 int launch_pack_codes(const uint8_t* codes, int bits, int64_t count, uint8_t* out, hipStream_t st) {
-  int64_t groups = (count + 7) / 8;
-  int64_t out_bytes = (count * bits + 7) / 8;
-  if (groups == 0) return QG_OK;
-  int64_t blocks = (groups + 255) / 256;
-  hipLaunchKernelGGL(pack_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, st, codes, bits, count, out, out_bytes);
+  if (count <= 0) return QG_OK;
+  const int64_t out_bytes = (count * bits + 7) / 8;
+  const dim3 grid((unsigned)((count + PACK_CODES - 1) / PACK_CODES));
+  switch (bits) {
+#define QG_PACK(B) case B: hipLaunchKernelGGL(pack_codes_kernel<B>, grid, dim3(256), 0, st, codes, count, out, out_bytes); break;
+    QG_PACK(1) QG_PACK(2) QG_PACK(3) QG_PACK(4) QG_PACK(5) QG_PACK(6) QG_PACK(7) QG_PACK(8)
+#undef QG_PACK
+    default: return QG_EINVAL;
+  }
+  return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
+}
+
+template <int MODE>
+static int launch_repack_mode(const uint8_t* canon, int bits, int K, int N, uint32_t flip, uint4* out, hipStream_t st) {
+  const int groups_n = (N / TILE_N + 3) / 4;
+  const int64_t total = (int64_t)(K / TILE_K) * groups_n, per_xcd = (total + 7) / 8;
+  const dim3 grid((unsigned)(8 * per_xcd));
+  switch (bits) {
+#define QG_REPACK(B) case B: hipLaunchKernelGGL((repack_kernel<B, MODE>), grid, dim3(256), 0, st, canon, out, K, N, flip, groups_n, total, per_xcd); break;
+    QG_REPACK(1) QG_REPACK(2) QG_REPACK(3) QG_REPACK(4) QG_REPACK(5) QG_REPACK(6) QG_REPACK(7) QG_REPACK(8)
+#undef QG_REPACK
+    default: return QG_EINVAL;
+  }
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
 int launch_repack(const uint8_t* canon, int bits, int K, int N, uint32_t flip, int natural, int layout, uint8_t* out, hipStream_t st) {
-  int64_t nchunks = (int64_t)(K / TILE_K) * (N / TILE_N);
-  int64_t canon_bytes = ((int64_t)K * N * bits + 7) / 8;
-  int64_t blocks = (nchunks * 64 + 255) / 256;
-  hipLaunchKernelGGL(repack_kernel, dim3((unsigned)blocks), dim3(256), 0, st, canon, canon_bytes,
-                     reinterpret_cast<uint32_t*>(out), bits, K, N, flip, natural, layout);
-  return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
+  uint4* o = reinterpret_cast<uint4*>(out);
+  if (layout == QG_LAYOUT_TILE128x64_I8) return launch_repack_mode<REPACK_I8>(canon, bits, K, N, flip, o, st);
+  if (layout == QG_LAYOUT_TILE128x64_R32)
+    return natural ? launch_repack_mode<REPACK_R32_PLAIN>(canon, bits, K, N, flip, o, st)
+                   : launch_repack_mode<REPACK_R32>(canon, bits, K, N, flip, o, st);
+  return natural ? launch_repack_mode<REPACK_PLAIN>(canon, bits, K, N, flip, o, st)
+                 : launch_repack_mode<REPACK_STREAMS>(canon, bits, K, N, flip, o, st);
 }
 
 }  // namespace qg
