@@ -26,10 +26,11 @@ FLAGS = ["--offload-arch=gfx950", "-std=c++20", "-O3", "-fPIC", "-fvisibility=hi
 
 
 def _jobs():
-    jobs = [("qg_pack.hip", None), ("qg_probe.hip", None), ("qg_api.hip", None)]
+    jobs = [("qg_pack.hip", None), ("qg_probe.hip", None), ("qg_api.hip", None), ("qg_a8_rowsum.hip", None)]
     for src in ("qg_dequant.hip", "qg_decode_gemm.hip", "qg_large.hip", "qg_large32.hip", "qg_gemv.hip"):
         jobs += [(src, wt) for wt in range(NUM_WT)]
-    jobs += [("qg_a8_gemm.hip", -bits) for bits in range(1, 9)]      # int8 activations: once per code width
+    for src in ("qg_a8_gemm.hip", "qg_a8_large.hip"):      # int8 activations: once per code width
+        jobs += [(src, -bits) for bits in range(1, 9)]
     jobs.append(("qg_large.hip", NUM_WT))      # the tiled kernel on weights already de-quantised (pass-through decoder)
     for src in ("qg_dequant.hip", "qg_decode_gemm.hip", "qg_large.hip"):      # codebook indices of 1..8 bits (kernel-side types 15..22)
         jobs += [(src, NUM_WT + 1 + b) for b in range(8)]
