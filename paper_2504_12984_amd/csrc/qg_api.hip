@@ -26,6 +26,7 @@ int launch_repack(const uint8_t*, int, int, int, uint32_t, int, int, uint8_t*, h
 QG_FOR_ALL_WT(QG_DECL)
 #undef QG_DECL
 int large_launch_wt14(const GemmParams&, int, int, hipStream_t);
+int launch_reduce_tiles(const GemmParams&, int, int, hipStream_t);
 // codebook indices of 1..8 bits: kernel-side weight types WT_LUT0 .. WT_LUT0 + 7
 #define QG_FOR_ALL_LUT(X) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22)
 #define QG_DECL(i)                                                            \
@@ -383,17 +384,28 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // 256 and 128 rows by rounds of workgroups) and split-K.  Host arithmetic only.
 //
 // Split-K serves the lower row tiles when they would leave CUs idle.  Candidates: 64- or
-// 128-row tiles, K cut into 1, 2, 4 or 8 slabs of an even number of chunks (the kernel
-// works in pairs of chunks), at most one workgroup per CU when split.  Cost in
-// microseconds, fitted to measurements at K = 1024 .. 8192, N = 2048 .. 14336:
-// chunks per workgroup x time per chunk (1.33 at up to 4 bits, + 0.33 per bit above,
-// x 1.13 for 128 rows) + for the exchange of partial sums 5 + 0.4 per MB with 64-row
-// tiles, 11 + 0.6 per MB with 128-row tiles.
+// 128-row tiles, K cut into 1 to 8 slabs of an even number of chunks (the kernel
+// works in pairs of chunks), at most one workgroup per CU when split.  tiled_cost estimates the
+// time in microseconds, fitted to 1300 measurements at K = 1024 .. 28672, N = 2048 .. 28672, M = 24 .. 1000 at
+// 4 bits and 700 at 3, 6 and 8: what it picks takes 0.4 % longer than the best candidate on average, 13 % at most.
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
 // hardware convert) + 1.2 per slab (the last arriver of a tile reads the slabs back one
 // pair after the other).
+static double tiled_cost(int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
+  const int over = t.bits > 4 ? t.bits - 4 : 0;
+  const bool hw_convert = (t.bits == 4 || t.bits == 6 || t.bits == 8);      // e2m1, e3m2, e4m3
+  const double unpack = t.kind == QG_FLOAT ? (hw_convert ? 1.0 + 0.04 * over : 1.5) : 1.0 + 0.085 * over;
+  // a chunk alone on a CU, and with a second workgroup there
+  const double alone = unpack * (bm == 64 ? 0.95 : 1.30), pair = unpack * (bm == 64 ? 1.65 : 2.6);
+  const int64_t n = ((M + bm - 1) / bm) * ((N + 255) / 256) * sk, full = n / 512, rest = n % 512;
+  const double loop = cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
+  const double read = 0.19e-6 * (double)K * (double)N * t.bits / 8.0;       // the weights from memory
+  const double mb = (double)sk * (double)M * (double)N * 4.0e-6;            // partial sums
+  return 4.0 + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? 4.0 + 0.385 * mb : 3.0 + 0.335 * mb);
+}
+
 static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out, int* splitk_out, int* cps_out,
                        double* cost_out = nullptr) {
   const int bits = t.bits;
@@ -417,18 +429,14 @@ static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out,
       }
       if (cost_out) *cost_out = best;
     } else if (splitk <= 0) {
-      const double tc = 1.33 + 0.33 * (bits > 4 ? bits - 4 : 0);
       double best = 1e30;
       for (int cand_bm = 64; cand_bm <= 128; cand_bm *= 2)
-        for (int sk = 1; sk <= 8; sk *= 2) {
+        for (int sk = 1; sk <= 8; ++sk) {
           const int64_t tiles_m = (M + cand_bm - 1) / cand_bm;
           int cps = (KC + sk - 1) / sk;
           if (sk > 1 && (cps & 1)) ++cps;
-          if (sk > 1 && (cps < 4 || tiles_m * tiles_n * sk > 256)) continue;
-          const double rounds = (double)((tiles_m * tiles_n * sk + 255) / 256);
-          const double mb = (double)sk * (double)(tiles_m * cand_bm) * (double)(tiles_n * 256) * 4.0 / 1e6;
-          const double cost = rounds * cps * tc * (cand_bm == 64 ? 1.0 : 1.13) +
-                              (sk > 1 ? (cand_bm == 64 ? 5.0 + 0.4 * mb : 11.0 + 0.6 * mb) : 0.0);
+          if (sk > 1 && (cps < 4 || (KC + cps - 1) / cps != sk || tiles_m * tiles_n * sk > 256)) continue;
+          const double cost = tiled_cost(cand_bm, sk, cps, M, N, K, t);
           if (cost < best) { best = cost; bm = cand_bm; splitk = sk; }
         }
       if (cost_out) *cost_out = best;
@@ -675,7 +683,8 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
       rc = acquire_ws(ws_mode, (size_t)q.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), (size_t)tiles * 4, st, q);
       if (rc != QG_OK) return rc;
     }
-    return large_launch_wt14(q, route, bm, st);
+    rc = large_launch_wt14(q, route, bm, st);
+    return rc == QG_OK && q.splitk > LARGE_MEET ? launch_reduce_tiles(q, route, bm, st) : rc;
   }
 
   if (path == 1 || path == 3) {
@@ -701,7 +710,8 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
     rc = acquire_ws(ws_mode, (size_t)p.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), (size_t)tiles * 4, st, p);   // a ticket per 64-column strip
     if (rc != QG_OK) return rc;
   }
-  return wt_is_lut(wt) ? kLargeLut[wt - WT_LUT0](p, route, bm, st) : kLarge[wt](p, route, bm, st);
+  rc = wt_is_lut(wt) ? kLargeLut[wt - WT_LUT0](p, route, bm, st) : kLarge[wt](p, route, bm, st);
+  return rc == QG_OK && p.splitk > LARGE_MEET ? launch_reduce_tiles(p, route, bm, st) : rc;
 }
 
 int qgemm(const void* A, const void* packed_W, const void* scales, const uint8_t* zeros, qg_wtype t, int layout,

@@ -182,6 +182,20 @@ inline bool set_group_index(P& p) {
   return true;
 }
 
+// The tiled kernel: columns per tile, row tiles per L2 panel, and the order of the tiles (panels of
+// GROUP_M row tiles, column by column inside a panel).
+constexpr int LARGE_BN = 256;
+constexpr int LARGE_GROUP_M = 4;
+constexpr int LARGE_MEET = 3;      // up to so many K-slabs meet inside the tiled kernel, more in reduce_tiles_kernel
+template <int GROUP_M>
+__device__ __forceinline__ void tile_position(int tile, int tiles_m, int tiles_n, int* tm, int* tn) {
+  const int panel = GROUP_M * tiles_n;
+  const int first_m = (tile / panel) * GROUP_M;
+  const int gsize = min(tiles_m - first_m, GROUP_M);
+  *tm = first_m + (tile % panel) % gsize;
+  *tn = (tile % panel) / gsize;
+}
+
 // The 16x16 tiled kernel's own choice of 64-row tiles: when 128-row tiles would occupy at
 // most half of the 256 CUs (column tiles are 256 wide).
 inline bool large_prefers_64_rows(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 255) / 256) <= 128; }

@@ -14,8 +14,6 @@
 // Workgroup ids are remapped so that the workgroups resident on one XCD (ids
 // congruent mod 8) form 4 x 8 panels of tiles that share A and W in that XCD's L2.
 // Compiled once per weight type (QG_WT).
-// QG_DBG_NOBARRIER / NOAFRAG / NOSTAGE / NOWLOAD (never defined by the build) each cut one stage out for
-// timing experiments -- results are wrong with them.
 #include "qg_decode.h"
 #include "qg_static_for.h"
 
@@ -47,15 +45,25 @@ __device__ __forceinline__ void mfma16_acc(f4_t& acc, const u4_t& w, const u4_t&
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
 }
 
+// A finished accumulator in vector registers, copied where it is used (left to itself the register
+// allocator copies all of them ahead of the epilogue and spills what does not fit)
+__device__ __forceinline__ f4_t acc_read(const f4_t& acc) {
+  f4_t v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float x;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[r]));
+    v[r] = x;
+  }
+  return v;
+}
+
 template <int ROUTE>
 __device__ __forceinline__ uint32_t pack_out(float lo, float hi) {
   f2_t f = {lo, hi};
   if constexpr (ROUTE == ROUTE_F16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, h2_t));
   else return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, b2_t));
 }
-
-constexpr int LARGE_BN = 256;
-constexpr int LARGE_GROUP_M = 4;   // m-tiles per L2 panel
 
 // LDS: A slab of one chunk = 4 k-step slices, each [BM rows][4 pieces of 16 B];
 // piece p of row r is stored at slot p ^ lds_swizzle(r).  A fragment read takes
@@ -70,8 +78,15 @@ struct LargeLds {
   static constexpr int BUF = 4 * SLICE;
 };
 
+// The lower tiles leave the registers for two workgroups on a CU, which hide each other's waits
+// (64 rows, K = 8192, u4: two tiles per CU take 1.4 us per chunk, one alone 1.06); not so weights of
+// 16 bits, whose two stages alone are 128 registers, and 128-row tiles with 8-bit codes in groups of 32.
+constexpr int large_per_cu(int wt, int gpc, int bm, bool mx) {
+  return (bm > 128 || wt == WT_DENSE16 || (bm == 128 && gpc == 4 && wt_bits(wt) == 8 && !mx)) ? 1 : 2;
+}
+
 template <int WT, int ROUTE, int GPC, int BM, bool MX = false>
-__global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, int tiles_n, int per_xcd, int tn0) {
+__global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kernel(GemmParams p, int tiles_m, int tiles_n, int per_xcd, int tn0) {
   // GPC = groups per 128-row chunk: 1 (group size 128 or more), 2 (64) or 4 (32)
   // MX: power-of-two block scales (8-bit exponents, one per 32 rows: GPC = 4) on e2m1 / e4m3 codes
   constexpr bool TWO_GROUPS = (GPC == 2), FOUR_GROUPS = (GPC == 4);
@@ -91,11 +106,9 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
   const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (logical >= tiles * p.splitk) return;
   const int slab = logical / tiles, tile = logical % tiles;
-  const int panel = LARGE_GROUP_M * tiles_n;
-  const int first_m = (tile / panel) * LARGE_GROUP_M;
-  const int gsize = min(tiles_m - first_m, LARGE_GROUP_M);
-  const int tm = first_m + (tile % panel) % gsize;
-  const int tn = tn0 + (tile % panel) / gsize;          // tn0: first column tile of this launch
+  int tm, tn;
+  tile_position<LARGE_GROUP_M>(tile, tiles_m, tiles_n, &tm, &tn);
+  tn += tn0;                                             // first column tile of this launch
 
   const int tid = threadIdx.x, l = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -131,12 +144,10 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
                                                  min(kstep, 4 * KC - 1) * 64, 0);
   };
   // Staging registers: SETS sets of PIECES pieces; a piece is loaded SETS k-steps before it is
-  // stored to LDS (2: half a chunk ahead; 4: a whole chunk ahead -- measured on the prefill
-  // shapes: no difference, the loads are not late; 2 is the build's value).
-#ifndef QG_STAGE_SETS
-#define QG_STAGE_SETS 2
-#endif
-  constexpr int SETS = QG_STAGE_SETS;
+  // stored to LDS.  Loads return in order, so this is also how far ahead the weights can be in flight:
+  // a k-step of a 64-row tile is only 0.3 us, and with 4 sets instead of 2 a chunk takes 1.06 us
+  // instead of 1.22 (K = N = 8192, M = 64, u4); 2 are enough for the higher tiles.
+  constexpr int SETS = (BM == 64 && WT != WT_DENSE16) ? 4 : 2;
   static_assert(SETS == 2 || SETS == 4, "staging distance");
   u4_t stage[SETS][PIECES];
   auto a_issue = [&](int set, int kstep) __attribute__((always_inline)) {
@@ -229,19 +240,19 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
   if constexpr (D::IS_LUT) my_level = D::fetch(p.T, tid);       // codebook indices: this thread's level of the table
   WStage wA, wB;
   w_issue(wA, kbeg);
-  const int ks0 = 4 * kbeg;
+  const int ks0 = 4 * kbeg, ks1 = ks0 + 4;                     // my first two chunks
   if constexpr (SETS == 2) {
     a_issue(0, ks0); a_issue(1, ks0 + 1);
     a_commit(0, 0, 0); a_issue(0, ks0 + 2);
     a_commit(1, 0, 1); a_issue(1, ks0 + 3);
-    a_commit(0, 0, 2); a_issue(0, ks0 + 4);     // slice 0 of the second chunk
-    a_commit(1, 0, 3); a_issue(1, ks0 + 5);     // slice 1 of the second chunk
+    a_commit(0, 0, 2); a_issue(0, ks1);         // slice 0 of the second chunk
+    a_commit(1, 0, 3); a_issue(1, ks1 + 1);     // slice 1 of the second chunk
   } else {
     a_issue(0, ks0); a_issue(1, ks0 + 1); a_issue(2, ks0 + 2); a_issue(3, ks0 + 3);
-    a_commit(0, 0, 0); a_issue(0, ks0 + 4);     // the four slices of the second chunk
-    a_commit(1, 0, 1); a_issue(1, ks0 + 5);
-    a_commit(2, 0, 2); a_issue(2, ks0 + 6);
-    a_commit(3, 0, 3); a_issue(3, ks0 + 7);
+    a_commit(0, 0, 0); a_issue(0, ks1);         // the four slices of the second chunk
+    a_commit(1, 0, 1); a_issue(1, ks1 + 1);
+    a_commit(2, 0, 2); a_issue(2, ks1 + 2);
+    a_commit(3, 0, 3); a_issue(3, ks1 + 3);
   }
 
   // my A fragment of row-tile mt, k-step slice j: piece b of row mt*16 + i16
@@ -325,11 +336,7 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
     // A fragments: flat index f = J*MTS + MT over the chunk, read two tiles ahead
     const uint8_t* abase = lds + CUR * L::BUF + a_rd;
     auto a_read = [&](int f) __attribute__((always_inline)) {
-#ifdef QG_DBG_NOAFRAG
-      return (u4_t){0x3c003c00u + (uint32_t)f, 0x3c003c00u, 0x3c003c00u, (uint32_t)(uintptr_t)abase};
-#else
       return *reinterpret_cast<const u4_t*>(abase + (f / MTS) * L::SLICE + (f % MTS) * (16 * 64));
-#endif
     };
     u4_t ar[3];
     ar[0] = a_read(0);
@@ -374,24 +381,18 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
         __builtin_amdgcn_sched_barrier(0);
         // ---- the one extra item of this tile --------------------------------------------
         if constexpr (MT % 4 == 0) {
-#ifndef QG_DBG_NOSTAGE
           constexpr int I = MT / 4;
           *reinterpret_cast<u4_t*>(lds + NXT * L::BUF + J * L::SLICE + a_dst0 + 4096 * I) = stage[J % SETS][I];
-#endif
         } else if constexpr (MT % 4 == 2) {
-#ifndef QG_DBG_NOSTAGE
           constexpr int I = MT / 4;
           stage[J % SETS][I] = a_load(I, 4 * (kc + 1) + J + SETS);     // SETS k-steps from now
-#endif
         } else {
           constexpr int IDX = MT / 2;                  // 0 .. FREE_PER_STEP-1
           constexpr int FS = J * FREE_PER_STEP + IDX;
-#ifndef QG_DBG_NOWLOAD
           static_for<WPS>([&](auto Xc) __attribute__((always_inline)) {
             constexpr int I = FS * WPS + decltype(Xc)::value;
             if constexpr (I < WPIECES) w_piece(wn, kc + 1, std::integral_constant<int, I>{});
           });
-#endif
           static_for<CPS>([&](auto Xc) __attribute__((always_inline)) {
             constexpr int X = decltype(Xc)::value;
             if constexpr (!FOUR_GROUPS && J == 2 && IDX >= FREE_PER_STEP - CSLOTS)
@@ -418,9 +419,7 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) wf[JN & 1][nt] = (u4_t){nf[nt][0], nf[nt][1], nf[nt][2], nf[nt][3]};
     });
-#ifndef QG_DBG_NOBARRIER
     __syncthreads();
-#endif
   };
 
   // Chunks go in pairs (buffers, weight stages and constants alternate); an odd chunk
@@ -437,97 +436,117 @@ __global__ __launch_bounds__(256) void large_kernel(GemmParams p, int tiles_m, i
   // does not see the asm MFMAs, so it inserts no wait states of its own)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
+  if (!active) return;
+  const int ncol = TILE_N * nc + 16 * b;       // a lane holds 16 consecutive columns of row mt*16 + i16
+  auto store_row = [&](int m, const f4_t (&v)[4]) __attribute__((always_inline)) {
+    uint32_t o[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {              // column offset 4r + nt
+      o[2 * r + 0] = pack_out<ROUTE>(v[0][r], v[1][r]);
+      o[2 * r + 1] = pack_out<ROUTE>(v[2][r], v[3][r]);
+    }
+    u4_t* dst = reinterpret_cast<u4_t*>(p.C + (int64_t)m * p.N + ncol);
+    dst[0] = (u4_t){o[0], o[1], o[2], o[3]};
+    dst[1] = (u4_t){o[4], o[5], o[6], o[7]};
+  };
+
   // ---- split-K: partial tiles meet in the workspace ------------------------------------
+  // Lane layout of a partial tile: fragment (mt, nt) of thread tid at 16 * ((mt*4+nt)*256 + tid);
+  // rows past M stay out.  Only the lower tiles use this (the host never splits 256-row tiles).
   // Partial sums cross workgroups (and XCDs, whose L2s are not coherent with each other)
   // through 16-byte buffer stores and loads that carry the sc1 cache-policy bit, which is
   // what a device-scope relaxed atomic store / load compiles to on this target: the store
-  // writes through, the load bypasses the local caches.  Every wavefront handles its own
-  // 64-column strip of the tile by itself (no workgroup barrier after the main loop): its
-  // stores complete, lane 0 draws a ticket of that strip, and the wavefront that draws the
-  // last of the splitk tickets sums all slabs in slab order -- the result does not depend
-  // on arrival order.  The read-back is the expensive part (measured: one CU sustains only
-  // about 60 GB/s of such loads, and the four strips of a tile are in practice finished by
-  // the same, slowest workgroup), which is what the host's cost model charges per MB.
-  // Only the lower tiles use this (the host never splits 256-row tiles).
+  // writes through, the load bypasses the local caches.
+  // From four slabs on, reduce_tiles_kernel (qg_reduce.hip), enqueued behind this one, adds the slabs:
+  // a load of this kind takes 1.9 us and one workgroup per tile would do all the reading
+  // (M = 64, K = N = 8192 in 8 slabs: 20.4 us against 29.8).  With two or three the second launch costs more than
+  // it saves (M = 300, three: 55.6 against 51.9), and the slabs meet here.  Every wavefront handles
+  // its own 64-column strip of the tile by itself and first draws a ticket (low half of the strip's counter).
+  // All but the last to draw store their partial strip, wait for it, count it as done (high
+  // half) and leave.  The last one keeps its own sums in registers, waits until the others are done --
+  // they have left their main loops and wait for nothing, so that wait ends -- and adds the
+  // slabs in slab order, its own at its place: the result does not depend on arrival order.
   if constexpr (BM <= 128) {
     if (p.splitk > 1) {
-      if (!active) return;
       constexpr int SC1 = 16;                                   // cache policy: device coherence
-      constexpr int TILE_BYTES = BM * LARGE_BN * 4;
+      constexpr int AWAY = 0x40000000;                          // beyond the resource: loads give zeros, stores nothing
       auto ws_rsrc = [&](int sp) __attribute__((always_inline)) {
-        return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (BM * LARGE_BN), 0, TILE_BYTES, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (BM * LARGE_BN), 0, BM * LARGE_BN * 4, 0x00020000);
       };
-      // lane layout of a partial tile: fragment (mt, nt) of thread tid at 16 * ((mt*4+nt)*256 + tid)
-      // (QG_DBG_NOEXSTORE / QG_DBG_NOEXLOAD: diagnostic builds without the exchange / without the
-      // read-back, wrong results, timing only; never defined by the build)
-#ifndef QG_DBG_NOEXSTORE
-      {
-        const __amdgpu_buffer_rsrc_t mine = ws_rsrc(slab);
-#pragma unroll
-        for (int mt = 0; mt < MTS; ++mt)
-          if (m0 + mt * 16 + i16 < p.M) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[mt][nt]), mine, 16 * tid, (mt * 4 + nt) * 4096, SC1);
-          }
-      }
-#endif
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // my partial strip is out before my ticket is drawn
+      auto ws_off = [&](int mt) __attribute__((always_inline)) { return m0 + mt * 16 + i16 < p.M ? 16 * tid : AWAY; };
+      const bool here = p.splitk <= LARGE_MEET;
       unsigned* ticket = p.tickets + 4 * tile + w;
       unsigned drawn = 0;
-      if (l == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      drawn = __builtin_amdgcn_readfirstlane(drawn);
-      if (drawn != (unsigned)(p.splitk - 1)) return;
-#pragma unroll
-      for (int mt = 0; mt < MTS; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = (f4_t){0.f, 0.f, 0.f, 0.f};
-#if !defined(QG_DBG_NOEXLOAD) && !defined(QG_DBG_NOEXSTORE)
-      // two slabs' loads are in flight together (the second of an odd count is a repeat
-      // of the last slab whose values are dropped)
-      for (int sp = 0; sp < p.splitk; sp += 2) {
-        const bool two = sp + 1 < p.splitk;
-        const __amdgpu_buffer_rsrc_t r0 = ws_rsrc(sp), r1 = ws_rsrc(two ? sp + 1 : sp);
-        u4_t v0[MTS][4], v1[MTS][4];
-#pragma unroll
-        for (int mt = 0; mt < MTS; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            v0[mt][nt] = v1[mt][nt] = (u4_t){0u, 0u, 0u, 0u};
-            if (m0 + mt * 16 + i16 < p.M) {                       // rows past M were not written
-              v0[mt][nt] = __builtin_amdgcn_raw_buffer_load_b128(r0, 16 * tid, (mt * 4 + nt) * 4096, SC1);
-              v1[mt][nt] = __builtin_amdgcn_raw_buffer_load_b128(r1, 16 * tid, (mt * 4 + nt) * 4096, SC1);
-            }
-          }
-#pragma unroll
-        for (int mt = 0; mt < MTS; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            acc[mt][nt] += __builtin_bit_cast(f4_t, v0[mt][nt]);
-            if (two) acc[mt][nt] += __builtin_bit_cast(f4_t, v1[mt][nt]);
-          }
+      if (here) {
+        if (l == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drawn = __builtin_amdgcn_readfirstlane(drawn) & 0xffffu;
       }
-#endif
+      if (!here || drawn != (unsigned)(p.splitk - 1)) {
+        const __amdgpu_buffer_rsrc_t mine = ws_rsrc(slab);
+#pragma unroll
+        for (int mt = 0; mt < MTS; ++mt) {
+          const int off = ws_off(mt);
+#pragma unroll
+          for (int nt = 0; nt < 4; ++nt)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc_read(acc[mt][nt])), mine, off, (mt * 4 + nt) * 4096, SC1);
+        }
+        if (!here) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // my partial strip is out before it counts as done
+        if (l == 0) __hip_atomic_fetch_add(ticket, 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+      }
+      while ((__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) != (unsigned)(p.splitk - 1))
+        __builtin_amdgcn_s_sleep(1);
+      asm volatile("" ::: "memory");                              // no slab is read ahead of the count
       if (l == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+      // the other slabs in slab order (S of them), the loads of R row tiles in flight
+      static_assert(LARGE_MEET == 3, "one or two other slabs");
+      auto meet = [&](auto Sc, auto Rc) __attribute__((always_inline)) {
+        constexpr int S = decltype(Sc)::value, R = decltype(Rc)::value;
+        const __amdgpu_buffer_rsrc_t rsrc[2] = {ws_rsrc(slab == 0 ? 1 : 0), ws_rsrc(slab == 2 ? 1 : p.splitk - 1)};
+#pragma unroll
+        for (int h = 0; h < MTS; h += R) {
+          u4_t x[S][R][4];
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            const int off = ws_off(h + i);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+              for (int y = 0; y < S; ++y)
+                x[y][i][nt] = __builtin_amdgcn_raw_buffer_load_b128(rsrc[y], off, ((h + i) * 4 + nt) * 4096, SC1);
+          }
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            f4_t sum[4];
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+              const f4_t first = __builtin_bit_cast(f4_t, x[0][i][nt]), own = acc_read(acc[h + i][nt]);
+              if constexpr (S == 1) {
+                sum[nt] = first + own;
+              } else {
+                const f4_t second = __builtin_bit_cast(f4_t, x[1][i][nt]);
+                sum[nt] = slab == 2 ? (first + second) + own : (first + own) + second;
+              }
+            }
+            const int m = m0 + (h + i) * 16 + i16;
+            if (m < p.M) store_row(m, sum);
+          }
+        }
+      };
+      if (p.splitk == 2) meet(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+      else meet(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+      return;
     }
   }
 
-  // ---- epilogue: a lane holds 16 consecutive columns of row mt*16 + i16 ---------------
-  if (!active) return;
-  const int ncol = TILE_N * nc + 16 * b;
+  // ---- epilogue -------------------------------------------------------------------------
 #pragma unroll
   for (int mt = 0; mt < MTS; ++mt) {
     const int m = m0 + mt * 16 + i16;
     if (m < p.M) {
-      uint32_t o[8];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {          // column offset 4r + nt
-        o[2 * r + 0] = pack_out<ROUTE>(acc[mt][0][r], acc[mt][1][r]);
-        o[2 * r + 1] = pack_out<ROUTE>(acc[mt][2][r], acc[mt][3][r]);
-      }
-      u4_t* dst = reinterpret_cast<u4_t*>(p.C + (int64_t)m * p.N + ncol);
-      dst[0] = (u4_t){o[0], o[1], o[2], o[3]};
-      dst[1] = (u4_t){o[4], o[5], o[6], o[7]};
+      const f4_t v[4] = {acc_read(acc[mt][0]), acc_read(acc[mt][1]), acc_read(acc[mt][2]), acc_read(acc[mt][3])};
+      store_row(m, v);
     }
   }
 }
