@@ -273,6 +273,12 @@ static int check_common(qg_wtype t, int layout, int act, int scale_dtype, int64_
 // tiles of 16 rows a wavefront of the streaming kernel carries for M rows (M <= 64)
 static int row_tiles(int64_t M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
 
+// Whether an arrangement (its tens are its row tiles) serves M rows: it has the row tiles they need, and not
+// twice as many or more.
+static bool covers_rows(int variant, int64_t M) {
+  return variant / 10 == row_tiles(M) || (variant / 10 == 3 && M > 32 && M <= 48);
+}
+
 // Streaming kernel (M <= 64): wavefront arrangement and split-K by shape.  Host arithmetic only.
 // (mx: block-scaled weights -- group 32, but only four scale bytes per block and lane, so every
 // arrangement has the registers for them)
@@ -280,7 +286,10 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
                            bool mx = false) {
   const int KC = K / TILE_K, NCH = N / TILE_N;
   const int mt = row_tiles(M);
-  int variant = 10 * mt + 1;                  // 4 wavefronts on one strip
+  // 33 .. 48 rows carry three row tiles: a quarter less of A to load and of matrix instructions than four
+  // (K = N = 8192, M = 40, u4: 17.8 us against 19.8; K = 4096, N = 28672: 25.4 against 28.2)
+  const int tens = (M > 32 && M <= 48) ? 30 : 10 * mt;
+  int variant = tens + 1;                     // 4 wavefronts on one strip
   // One row tile, short K (at most 32 chunks): as many wavefronts per strip as leaves each
   // two chunks -- 16 (every load of the strip in flight at once) up to 4-bit codes, whose
   // ring fits the 128 registers 16 wavefronts leave each; 8 from 16 chunks on; else 4.
@@ -304,7 +313,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // their A rows in the vector cache (measured 2-4 % shorter at K = 8192, N = 28672;
   // with 2 or 4 row tiles: 2 strips x 2 wavefronts along K, 10-15 % shorter)
   // (with several row tiles also for short K: K = 4096, N = 28672, M = 24: 20.8 us against 22.4)
-  if ((KC > 32 || mt > 1) && NCH % 2 == 0 && NCH / 2 >= 192) variant = (mt == 1) ? 14 : (mt == 2) ? 26 : 46;
+  if ((KC > 32 || mt > 1) && NCH % 2 == 0 && NCH / 2 >= 192) variant = (mt == 1) ? 14 : tens + 6;
   // up to 6 bits per code a wavefront needs few enough registers for 16 of them per
   // workgroup (2 strips x 8 along K): twice the wavefronts in flight, 1-6 % shorter
   if (KC > 32 && variant == 14 && wt_bits(wt) <= 6 && group != 64) variant = 15;
@@ -320,7 +329,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // wavefronts at 3 bits; 8-bit codes: two strips x 4 wavefronts, 23.5 against 27.3)
   if (variant == 11 && KC > 32 && NCH > 128 && NCH < 256) variant = wt_bits(wt) <= 6 ? 10 : (NCH % 2 == 0 ? 14 : 11);
   if (knob(3) > 0) variant = knob(3);
-  if (group == 32 && !mx) variant = 10 * mt + 1;   // four groups per chunk: the 4-wavefront arrangements only
+  if (group == 32 && !mx) variant = tens + 1;   // four groups per chunk: the 4-wavefront arrangements only
   const int waves = kDecodeWaves[wt_is_lut(wt) ? 0 : wt](variant);      // the same map for every type
   // Split K over workgroups only when the column strips alone cannot fill the
   // 256 CUs, and never below 4 chunks per wavefront (2 with 16 wavefronts per strip, or with a
@@ -330,9 +339,9 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   if (splitk <= 0) {
     splitk = 1;
     const int min_chunks = (waves >= 16 || (KC <= 32 && NCH <= 128)) ? 2 : 4;      // per wavefront
-    // (several row tiles on 192 or more strips: no split -- K = 4096, N = 14336, M = 24 takes
-    // 12.1 us unsplit against 14.7 in two)
-    while (NCH * splitk < 256 && !(mt > 1 && NCH >= 192) && KC / (splitk * 2) >= min_chunks * waves) splitk *= 2;
+    // (several row tiles: 192 workgroups are enough -- K = 4096, N = 14336, M = 24 takes 12.1 us
+    // unsplit against 14.7 in two; N = 6144, M = 40: 11.9 in two, 17.2 in four)
+    while (NCH * splitk < 256 && !(mt > 1 && NCH * splitk >= 192) && KC / (splitk * 2) >= min_chunks * waves) splitk *= 2;
     // long K and still at most half of the CUs busy: K in four, down to one chunk per wavefront
     // (K = 14336, N = 4096: 11.0 us against 16.2 with K in two; deeper splits lose to the exchange)
     while (KC > 32 && splitk < 4 && NCH * splitk <= 128 && KC / (splitk * 2) >= waves) splitk *= 2;
@@ -370,7 +379,7 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
   int variant;
   plan_streaming(p.M, p.N, p.K, p.group, wt, &variant, &p.splitk, &p.chunks_per_split, p.scale_e8m0 != 0);
   const int mt = row_tiles(p.M);
-  if (variant / 10 != mt) { g_last_error = "wavefront arrangement does not cover M rows"; return QG_EINVAL; }
+  if (!covers_rows(variant, p.M)) { g_last_error = "wavefront arrangement does not cover M rows"; return QG_EINVAL; }
   if (p.splitk > 1) {
     const int NCH = p.N / TILE_N;
     size_t pbytes = (size_t)p.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float);
@@ -481,7 +490,7 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
     double tiled = 1e30;
     int bm, sk, cps;
     plan_tiled(M, N, K, t, &bm, &sk, &cps, &tiled);
-    const double streaming = 10.0 + (2.2 + 0.09 * (bits > 4 ? bits - 4 : 0)) * ((double)K / 1024.0) * ((double)N / 8192.0);
+    const double streaming = (M <= 48 ? 0.92 : 1.0) * (10.0 + (2.2 + 0.09 * (bits > 4 ? bits - 4 : 0)) * ((double)K / 1024.0) * ((double)N / 8192.0));
     if (tiled < 0.9 * streaming) return 2;          // both fits are good to about 10 %
   }
   return 1;
@@ -691,7 +700,7 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
     // a forced arrangement must have the row tiles every block of rows needs, or rows would stay unwritten
     if (knob(3) > 0 && (group != 32 || p.scale_e8m0))
       for (int64_t r0 = 0; r0 < M; r0 += 64)
-        if (knob(3) / 10 != row_tiles(M - r0 < 64 ? M - r0 : 64)) { g_last_error = "forced wavefront arrangement does not cover the rows of M"; return QG_EINVAL; }
+        if (!covers_rows(knob(3), M - r0 < 64 ? M - r0 : 64)) { g_last_error = "forced wavefront arrangement does not cover the rows of M"; return QG_EINVAL; }
     for (int64_t r0 = 0; r0 < M; r0 += 64) {
       GemmParams q = p;
       q.A = p.A + r0 * K;
@@ -921,7 +930,7 @@ int qg_plan(qg_wtype t, int layout, int act, int scale_dtype, int64_t group, int
     plan_streaming((int)(M < 64 ? M : 64), (int)N, (int)K, (int)group, wt, &plan[1], &plan[3], &plan[4], scale_dtype == QG_E8M0);
     if (knob(3) > 0 && (group != 32 || scale_dtype == QG_E8M0))
       for (int64_t r0 = 0; r0 < M; r0 += 64)
-        if (knob(3) / 10 != row_tiles(M - r0 < 64 ? M - r0 : 64)) return QG_EINVAL;
+        if (!covers_rows(knob(3), M - r0 < 64 ? M - r0 : 64)) return QG_EINVAL;
   } else {
     if (plan[0] < 1 || plan[0] > 5) return QG_EINVAL;
     if (plan[0] == 5) {

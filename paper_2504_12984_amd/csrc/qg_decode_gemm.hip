@@ -1,4 +1,4 @@
-// Decode-sized matmul, M <= 64 (one, two or four tiles of 16 rows): the weights are streamed from HBM exactly once
+// Decode-sized matmul, M <= 64 (one to four tiles of 16 rows): the weights are streamed from HBM exactly once
 // and the kernel is built to keep that stream saturated.
 //
 // One workgroup of NW wavefronts owns one 64-column strip of W and one slab of
@@ -373,7 +373,7 @@ static int launch_cfg(const GemmParams& p, hipStream_t st) {
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
-// variant = 10 * (row tiles: 1, 2, 4) + (0: 8 wavefronts per strip, 1: 4 wavefronts, 2: 16 wavefronts)
+// variant = 10 * (row tiles: 1, 2, 3, 4) + (0: 8 wavefronts per strip, 1: 4 wavefronts, 2: 16 wavefronts)
 template <int ROUTE, int GPC>
 static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
   if constexpr (GPC == 4 && (QG_WT == 9 || QG_WT == 13)) {
@@ -387,6 +387,8 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
         case 16: return launch_cfg<ROUTE, 4, 16, 2, 1, 4, true>(p, st);
         case 21: return launch_cfg<ROUTE, 4, 4, 2, 2, 1, true>(p, st);
         case 26: return launch_cfg<ROUTE, 4, 4, 2, 2, 2, true>(p, st);
+        case 31: return launch_cfg<ROUTE, 4, 4, 2, 3, 1, true>(p, st);
+        case 36: return launch_cfg<ROUTE, 4, 4, 2, 3, 2, true>(p, st);
         case 46: return launch_cfg<ROUTE, 4, 4, 2, 4, 2, true>(p, st);
         case 41: return launch_cfg<ROUTE, 4, 4, 2, 4, 1, true>(p, st);
         default: return QG_EINVAL;
@@ -398,6 +400,7 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     switch (variant) {
       case 11: return launch_cfg<ROUTE, 4, 4, 2, 1>(p, st);
       case 21: return launch_cfg<ROUTE, 4, 4, 2, 2>(p, st);
+      case 31: return launch_cfg<ROUTE, 4, 4, 2, 3>(p, st);
       case 41: return launch_cfg<ROUTE, 4, 4, 2, 4>(p, st);
       default: return QG_EINVAL;
     }
@@ -411,6 +414,8 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     case 16: return launch_cfg<ROUTE, GPC, 16, 2, 1, 4>(p, st);    // 4 strips x 4
     case 21: return launch_cfg<ROUTE, GPC, 4, 2, 2>(p, st);
     case 26: return launch_cfg<ROUTE, GPC, 4, 2, 2, 2>(p, st);     // 2 row tiles, 2 strips x 2
+    case 31: return launch_cfg<ROUTE, GPC, 4, 2, 3>(p, st);
+    case 36: return launch_cfg<ROUTE, GPC, 4, 2, 3, 2>(p, st);     // 3 row tiles, 2 strips x 2
     case 46: return launch_cfg<ROUTE, GPC, 4, 2, 4, 2>(p, st);     // 4 row tiles, 2 strips x 2
     case 41: return launch_cfg<ROUTE, GPC, 4, 2, 4>(p, st);
     default: return QG_EINVAL;
@@ -421,11 +426,10 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
 // number of wavefronts along K per strip of a variant (the host sizes split-K with it)
 int QG_CAT(decode_waves_wt, QG_WT)(int variant) {
   switch (variant) {
-    case 10: return 8;
+    case 10: case 15: return 8;
     case 12: return 16;
     case 14: case 16: return 4;
-    case 26: case 46: return 2;
-    case 15: return 8;
+    case 26: case 36: case 46: return 2;
     default: return 4;
   }
 }
