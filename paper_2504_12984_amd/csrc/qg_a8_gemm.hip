@@ -8,16 +8,16 @@
 // Same streaming design as the 16-bit-activation kernel for small M (the weights are read from
 // HBM once, each wavefront keeps a ring of two 128x64 chunks in registers, K is reduced inside
 // the matrix instruction, then across wavefronts in LDS, then -- if K is also split over
-// workgroups -- through fp32 partial tiles and an arrival counter), on the third device layout:
+// workgroups -- through a tree of pairwise fp32 exchanges), on the third device layout:
 // a lane's 16*BITS bytes are FOUR parallel byte streams (byte lane e of every register), quad t
 // occupies bits [t*BITS, (t+1)*BITS) of each, so one shift + one mask turn a register into
 // four int8 operands of v_mfma_i32_16x16x64_i8 at once (two more operations when the codes
 // straddle a byte).  Codes stay unsigned (intk is stored offset-binary); the zero-point term is
 // taken out afterwards through the row sums of A, which one extra matrix instruction with an
 // all-ones operand delivers:  sum a (q - z) = sum a q - z sum a.
-// Rows beyond 64 are served in blocks of 64 by the host (a first slice: no LDS-staged tile
-// kernel for prefill-sized M yet).  Compiled once per code width (QG_BITS).
+// Rows beyond 64 go to the tiled kernel (qg_a8_large.hip), or in blocks of 64 through this one.  Compiled once per code width (QG_BITS).
 #include "qg_common.h"
+#include "qg_exchange.h"
 #include "qg_static_for.h"
 
 #ifndef QG_BITS
@@ -208,7 +208,6 @@ __global__ __launch_bounds__(NW * 64) void a8_kernel(A8Params p) {
 
   // ---- reduce over the NW wavefronts through LDS, one 16-row tile at a time -----------------
   __shared__ float red[NW * 16 * 64];                      // [NW][16 column offsets][64 lanes]
-  int* s_last = reinterpret_cast<int*>(red);               // reused once the sums are in registers
   constexpr int PER = 16 / NW;                             // column offsets per thread
   const int idx0 = PER * w;
   float sum[MT][PER];
@@ -236,7 +235,30 @@ __global__ __launch_bounds__(NW * 64) void a8_kernel(A8Params p) {
     }
   }
 
-  if (p.splitk > 1) {
+  if constexpr (MT <= 2) {
+    if (p.splitk > 1) {
+      constexpr int PAIR = PER >= 2 ? 2 : 1, NP = PER / PAIR;
+      bool live[MT][NP];                                     // whose result is mine to store
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) live[mt][q] = mt * 16 + i16 < p.M;
+      if (!tree_exchange<MT, PER>(sum, live, p.slots, nc, NCH, split, p.splitk, idx0, l)) return;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          if (live[mt][q]) {
+            const float as = p.a_scale ? p.a_scale[mt * 16 + i16] : 1.0f;
+            uint16_t* dst = p.C + (int64_t)(mt * 16 + i16) * p.N + n16 + idx0;
+            if constexpr (PAIR == 1) dst[q] = (uint16_t)(pack_out_a8(sum[mt][q] * as, 0.f, p.out_bf16) & 0xffffu);
+            else *reinterpret_cast<uint32_t*>(dst + 2 * q) = pack_out_a8(sum[mt][2 * q] * as, sum[mt][2 * q + 1] * as, p.out_bf16);
+          }
+      return;
+    }
+  }
+  if constexpr (MT > 2) if (p.splitk > 1) {
+    int* last = reinterpret_cast<int*>(red);               // its sums are in registers by now
     // Partial tiles cross workgroups through device-scope relaxed atomics (write-through
     // stores, cache-bypassing loads) and one arrival counter per strip; the last arriver
     // sums the slabs in slab order, so the result does not depend on arrival order.
@@ -251,9 +273,9 @@ __global__ __launch_bounds__(NW * 64) void a8_kernel(A8Params p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a workgroup barrier alone does not wait for global stores
     __syncthreads();
     if (tid == 0)
-      *s_last = (__hip_atomic_fetch_add(&p.tickets[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(p.splitk - 1));
+      *last = (__hip_atomic_fetch_add(&p.tickets[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(p.splitk - 1));
     __syncthreads();
-    if (!*s_last) return;
+    if (!*last) return;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

@@ -97,14 +97,16 @@ static int hip_fail(hipError_t e, const char* what) {
 // this one capacity; only forced split factors (the experiment knobs) can exceed it.
 constexpr size_t WS_PARTIAL_BYTES = size_t(32) << 20;
 constexpr size_t WS_TICKETS = 16384;
-constexpr size_t WS_BYTES = WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned);
+// Behind them, as large as the partial sums: the slots in which the streaming kernel's slabs meet (zero between calls,
+// so they cannot share memory with sums that stay behind).
+constexpr size_t WS_BYTES = WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned) + WS_PARTIAL_BYTES;
 
 // qgemm: one workspace per device and stream.  Kernels of one stream run in order, so they
 // can share a workspace; kernels of different streams may overlap, so each stream gets its
 // own.  It is allocated once, on the first call of that (device, stream) that splits K, at
 // the fixed capacity, and never freed or moved, so a HIP graph captured later keeps valid
 // pointers.  (A forced split beyond the capacity gets a larger block; the old one is kept
-// allocated for the same reason.)  The counters are zeroed by a memset enqueued on the
+// allocated for the same reason.)  The counters and slots are zeroed by a memset enqueued on the
 // stream ahead of the first kernel; nothing synchronises.
 struct Workspace {
   int dev = -1;
@@ -117,7 +119,7 @@ static std::mutex g_ws_mutex;
 static Workspace g_ws[32];
 static int g_ws_used = 0;
 
-static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t st, float** partial, unsigned** tickets) {
+static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t st, float** partial, unsigned** tickets, void** slots = nullptr) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
@@ -135,15 +137,17 @@ static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t 
     const size_t pb = partial_bytes < WS_PARTIAL_BYTES ? WS_PARTIAL_BYTES : ((partial_bytes + 255) & ~size_t(255));
     const size_t tc = ticket_count < WS_TICKETS ? WS_TICKETS : ticket_count;
     unsigned char* block = nullptr;
-    e = hipMalloc(&block, pb + tc * sizeof(unsigned));
+    const size_t cleared = ((tc * sizeof(unsigned) + 255) & ~size_t(255)) + pb;
+    e = hipMalloc(&block, pb + cleared);
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(workspace)");
-    // counters start at zero; every kernel that uses them leaves them at zero
-    e = hipMemsetAsync(block + pb, 0, tc * sizeof(unsigned), st);
+    // counters and slots start at zero; every kernel that uses them leaves them at zero
+    e = hipMemsetAsync(block + pb, 0, cleared, st);
     if (e != hipSuccess) { (void)hipFree(block); return hip_fail(e, "hipMemsetAsync(tickets)"); }
     w.base = block; w.partial_bytes = pb; w.ticket_count = tc;      // an earlier, smaller block stays allocated
   }
   *partial = reinterpret_cast<float*>(w.base);
   *tickets = reinterpret_cast<unsigned*>(w.base + w.partial_bytes);
+  if (slots) *slots = w.base + w.partial_bytes + ((w.ticket_count * sizeof(unsigned) + 255) & ~size_t(255));
   return QG_OK;
 }
 
@@ -164,8 +168,8 @@ static bool can_have_workspace(size_t partial_bytes, size_t ticket_count, hipStr
 // qgemm_noalloc: the same workspace as one fixed array in device memory, part of the code
 // object (zero when it is loaded), one copy per GPU.  Its address on a device is looked up
 // once, with that device current, and kept; host code never uses the array's name otherwise.
-// Partial sums need no clearing (a call reads back only slots it has written itself) and
-// every arrival counter is returned to zero by the last arriver of the kernel that used it.
+// Partial sums need no clearing (a call reads back only what it has written itself);
+// every arrival counter and exchange slot is returned to zero by the kernel that used it.
 static __device__ __align__(256) unsigned char scratch[WS_BYTES];
 static std::mutex g_scratch_mutex;
 static unsigned char* g_scratch_ptr[64] = {};
@@ -187,7 +191,7 @@ static int static_scratch_base(unsigned char** base) {
   return QG_OK;
 }
 
-static int get_static_scratch(size_t partial_bytes, size_t ticket_count, float** partial, unsigned** tickets) {
+static int get_static_scratch(size_t partial_bytes, size_t ticket_count, float** partial, unsigned** tickets, void** slots) {
   if (partial_bytes > WS_PARTIAL_BYTES || ticket_count > WS_TICKETS) {
     g_last_error = "qgemm_noalloc: this call needs " + std::to_string(partial_bytes) + " bytes of split-K partial sums and " +
                    std::to_string(ticket_count) + " arrival counters; the fixed scratch holds " +
@@ -199,13 +203,14 @@ static int get_static_scratch(size_t partial_bytes, size_t ticket_count, float**
   if (rc != QG_OK) return rc;
   *partial = reinterpret_cast<float*>(base);
   *tickets = reinterpret_cast<unsigned*>(base + WS_PARTIAL_BYTES);
+  *slots = base + WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned);
   return QG_OK;
 }
 
 enum WsMode { WS_PER_STREAM = 0, WS_STATIC = 1 };
 static int acquire_ws(int mode, size_t partial_bytes, size_t ticket_count, hipStream_t st, GemmParams& p) {
-  return mode == WS_STATIC ? get_static_scratch(partial_bytes, ticket_count, &p.ws, &p.tickets)
-                           : get_workspace(partial_bytes, ticket_count, st, &p.ws, &p.tickets);
+  return mode == WS_STATIC ? get_static_scratch(partial_bytes, ticket_count, &p.ws, &p.tickets, &p.slots)
+                           : get_workspace(partial_bytes, ticket_count, st, &p.ws, &p.tickets, &p.slots);
 }
 
 // ---- buffer of the de-quantise-first path (forced path 4) -------------------------------------
@@ -620,7 +625,7 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
   p.Z = zeros;
   p.T = static_cast<const uint16_t*>(codebook);
   p.C = static_cast<uint16_t*>(C);
-  p.ws = nullptr; p.tickets = nullptr;
+  p.ws = nullptr; p.tickets = nullptr; p.slots = nullptr;
   p.M = (int)M; p.N = (int)N; p.K = (int)K; p.group = (int)group;
   p.zbias = (t.kind == QG_INT) ? (1 << (t.bits - 1)) : 0;
   p.scale_bf16 = (scale_dtype == QG_BF16);
@@ -866,7 +871,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
   p.S = static_cast<const uint16_t*>(scales);
   p.Z = zeros;
   p.C = static_cast<uint16_t*>(C);
-  p.ws = nullptr; p.tickets = nullptr;
+  p.ws = nullptr; p.tickets = nullptr; p.slots = nullptr;
   p.N = (int)N; p.K = (int)K; p.group = (int)group;
   p.zbias = (t.kind == QG_INT) ? (1 << (t.bits - 1)) : 0;
   p.scale_bf16 = (scale_dtype == QG_BF16);
@@ -890,7 +895,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
     if (q.splitk > 1) {
       const int NCH = q.N / TILE_N;
       float* ws = nullptr; unsigned* tk = nullptr;
-      int rc = get_workspace((size_t)q.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float), (size_t)NCH, st, &ws, &tk);
+      int rc = get_workspace((size_t)q.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float), (size_t)NCH, st, &ws, &tk, &q.slots);
       if (rc != QG_OK) return rc;
       q.ws = ws; q.tickets = tk;
     }

@@ -142,6 +142,7 @@ struct GemmParams {
   uint16_t* C;
   float* ws;            // split-K partial sums
   unsigned* tickets;    // one arrival counter per output tile, zero between calls
+  void* slots;          // split-K of the streaming kernel: exchange slots, zero between calls
   int M, N, K, group;
   int zbias, scale_bf16;
   int scale_e8m0;       // scales are 8-bit exponents (streaming kernel only; e2m1 / e4m3, group 32)
@@ -163,6 +164,7 @@ struct A8Params {
   uint16_t* C;
   float* ws;
   unsigned* tickets;
+  void* slots;            // as in GemmParams
   int M, N, K, group;
   int zbias, scale_bf16, out_bf16;
   const uint2* rowsum;    // tiled kernel: row sums of A per scale group, [K/group][M], three bf16 terms each; or null

@@ -15,14 +15,11 @@
 // pipeline, Section "Key Ideas", with no layout conversion and no trip through
 // LDS).  The K reduction runs inside the MFMA (across the four 8-wide k-blocks
 // of lanes), then across the wavefronts through LDS, then -- when K is also
-// split over workgroups -- through fp32 partial tiles summed in split order by
-// the last workgroup to arrive (the k-dimension parallelisation the paper names
+// split over workgroups -- through a binary tree of pairwise fp32 exchanges (the k-dimension parallelisation the paper names
 // in Section "End-to-End Performance").
 // Compiled once per weight type (QG_WT).
-// QG_DBG_NODECODE / NOMFMA / NOSZ / NOREDUCE (never defined by the build) each cut one
-// stage out for timing experiments -- results are wrong with them; QG_SZ_BCAST and
-// QG_W_FIRST are two measured-and-rejected orderings of the scale and weight loads.
 #include "qg_decode.h"
+#include "qg_exchange.h"
 #include "qg_static_for.h"
 
 #ifndef QG_WT
@@ -105,24 +102,16 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     Stage& s = st[S];
     __builtin_amdgcn_sched_barrier(0);         // stay below the last use of the entry being refilled,
                                                // so that the refill reuses the same registers
-#ifndef QG_W_FIRST
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) s.a[mt][j] = *reinterpret_cast<const u4_t*>(arow[mt] + c * TILE_K + 32 * j);
-#endif
     const uint4* src = wstrip + (int64_t)c * (64 * BITS);
 #pragma unroll
     for (int i = 0; i < BITS; ++i) {
       uint4 q = stream_load(src + i * 64);
       s.r[4 * i + 0] = q.x; s.r[4 * i + 1] = q.y; s.r[4 * i + 2] = q.z; s.r[4 * i + 3] = q.w;
     }
-#ifdef QG_DBG_NOSZ
-#pragma unroll
-    for (int g = 0; g < GPC; ++g) { s.s[g] = make_uint2(0x3c003c00u, 0x3c003c00u); s.z[g] = 0x04040404u; }
-    __builtin_amdgcn_sched_barrier(0);
-    return;
-#endif
     const int g0 = (GPC > 1) ? GPC * c : ((c >> p.gshift) & p.gmask);
     if constexpr (D::IS_LUT) {   // codebook indices: scales only
 #pragma unroll
@@ -137,23 +126,11 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
       __builtin_amdgcn_sched_barrier(0);
       return;
     }
-#ifdef QG_SZ_BCAST
-    if (b == 0) {
-#endif
 #pragma unroll
     for (int g = 0; g < GPC; ++g) {
       s.s[g] = *reinterpret_cast<const uint2*>(p.S + (int64_t)(g0 + g) * p.N + n0);
       s.z[g] = *reinterpret_cast<const uint32_t*>(zbase + (int64_t)(g0 + g) * p.N + n0);
     }
-#ifdef QG_SZ_BCAST
-    }
-#endif
-#ifdef QG_W_FIRST
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s.a[mt][j] = *reinterpret_cast<const u4_t*>(arow[mt] + c * TILE_K + 32 * j);
-#endif
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -186,16 +163,6 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
       return;
     }
     typename D::Consts gc[GPC];
-#ifdef QG_SZ_BCAST
-    {
-      const int ba = 4 * i16;
-#pragma unroll
-      for (int g = 0; g < GPC; ++g) {
-        s.s[g].x = __builtin_amdgcn_ds_bpermute(ba, s.s[g].x); s.s[g].y = __builtin_amdgcn_ds_bpermute(ba, s.s[g].y);
-        s.z[g] = __builtin_amdgcn_ds_bpermute(ba, s.z[g]);
-      }
-    }
-#endif
 #pragma unroll
     for (int g = 0; g < GPC; ++g) D::make_consts(gc[g], s.s[g], D::IS_LUT ? 0u : (s.z[g] & zmask), p.zbias, p.scale_bf16);
     static_for<4>([&](auto Jc) __attribute__((always_inline)) {
@@ -203,19 +170,10 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
       static_for<4>([&](auto NTc) __attribute__((always_inline)) {
         constexpr int NT = decltype(NTc)::value;
         uint32_t o[4];
-#ifdef QG_DBG_NODECODE
-        o[0] = s.r[(J * 4 + NT) % RAW]; o[1] = s.r[(J * 4 + NT + 1) % RAW]; o[2] = s.r[(J * 4 + NT + 2) % RAW]; o[3] = s.r[(J * 4 + NT + 3) % RAW] ^ s.s[0].x ^ s.z[0];
-#else
         D::template frag<J, NT>(s.r, gc[J * GPC / 4], u, o);          // k-step J lies in group J*GPC/4 of the chunk
-#endif
         const u4_t wf = {o[0], o[1], o[2], o[3]};      // unpacked once, used by every row tile
-#ifdef QG_DBG_NOMFMA
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt][NT][0] += __builtin_bit_cast(float, wf.x ^ wf.y ^ wf.z ^ wf.w ^ s.a[mt][J].x ^ s.a[mt][J].w);
-#else
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt][NT] = mfma16<ROUTE>(wf, s.a[mt][J], acc[mt][NT]);
-#endif
       });
     });
   };
@@ -264,17 +222,9 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
   // ---- reduce over the NW wavefronts through LDS, one 16-row tile at a time -----------------
   if constexpr (D::IS_LUT) __syncthreads();                // every wavefront is done with the table
   float* red = reinterpret_cast<float*>(lds_raw);          // [NW][16 column offsets][64 lanes]
-  int* s_last = reinterpret_cast<int*>(red);               // reused once the sums are in registers
   constexpr int PER = 16 / NK;                             // column offsets per thread
   const int idx0 = PER * wk;
   float sum[MT][PER];
-#ifdef QG_DBG_NOREDUCE
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int e = 0; e < PER; ++e) sum[mt][e] = acc[mt][e & 3][(e >> 2) & 3];
-  if (false)
-#endif
   // lanes whose row is past M carry nothing: they stay out of the LDS traffic, of the
   // split-K exchange and of the final store
 #pragma unroll
@@ -301,8 +251,32 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     }
   }
 
-  if (p.splitk > 1) {
-    // Partial tiles cross workgroups (and XCDs, whose L2s are not coherent with
+  // ---- split-K ------------------------------------------------------------------------------------
+  if constexpr (MT <= 2) {
+    if (p.splitk > 1) {
+      constexpr int PAIR = PER >= 2 ? 2 : 1, NP = PER / PAIR;
+      bool live[MT][NP];                                     // whose result is mine to store
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) live[mt][q] = mt * 16 + i16 < p.M;
+      if (!tree_exchange<MT, PER>(sum, live, p.slots, nc, NCH, split, p.splitk, idx0, l)) return;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          if (live[mt][q]) {
+            uint16_t* dst = p.C + (int64_t)(mt * 16 + i16) * p.N + TILE_N * nc + 16 * b + idx0;
+            if constexpr (PAIR == 1) dst[q] = (uint16_t)(pack_out<ROUTE>(sum[mt][q], 0.f) & 0xffffu);
+            else *reinterpret_cast<uint32_t*>(dst + 2 * q) = pack_out<ROUTE>(sum[mt][2 * q], sum[mt][2 * q + 1]);
+          }
+      return;
+    }
+  }
+  if constexpr (MT > 2) if (p.splitk > 1) {
+    int* last = reinterpret_cast<int*>(red);             // its sums are in registers by now
+    // Three and four row tiles: too many sums for exchanges of 8 bytes (M = 64, K = N = 4096 in four slabs:
+    // 13.1 us this way, 14.4 as a tree).  Partial tiles cross workgroups (and XCDs, whose L2s are not coherent with
     // each other) through device-scope relaxed atomics: such stores write
     // through and such loads bypass the local caches, so no cache-wide
     // write-back or invalidate is needed.  Order: my stores complete, barrier,
@@ -320,9 +294,9 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a workgroup barrier alone does not wait for global stores
     __syncthreads();
     if (tid == 0)
-      *s_last = (__hip_atomic_fetch_add(&p.tickets[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(p.splitk - 1));
+      *last = (__hip_atomic_fetch_add(&p.tickets[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(p.splitk - 1));
     __syncthreads();
-    if (!*s_last) return;
+    if (!*last) return;
     // all loads of a split are issued before the first add (independent accumulators)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
