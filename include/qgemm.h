@@ -29,7 +29,7 @@
  *   - the return value is a qg_status (0 = ok, negative = error, nothing was
  *     enqueued); no call throws, none frees caller memory;
  *   - qgemm may use a library-owned workspace for split-K partial sums: one per
- *     (device, stream), of one fixed size (32 MiB + 64 KiB, which covers every
+ *     (device, stream), of one fixed size (64 MiB + 64 KiB, which covers every
  *     shape), allocated by the first call on that pair that splits K (one
  *     hipMalloc and one memset enqueued on the stream; nothing synchronises) and
  *     then never freed, moved or grown, so calls on different streams may overlap
@@ -168,7 +168,7 @@ QG_API int qgemm(const void* A, const void* packed_W, const void* scales, const 
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels,
  * same plan and therefore the same bits as qgemm, but the split-K partial sums and
  * arrival counters live in ONE fixed array in device memory that is part of the loaded
- * library (32 MiB + 64 KiB per GPU, held until the process ends); the call allocates
+ * library (64 MiB + 64 KiB per GPU, held until the process ends); the call allocates
  * nothing, frees nothing and does not synchronise.
  *   - The first call on a device with valid shapes -- M = 0 will do, all pointers may then
  *     be NULL -- looks the array's address up on that device and keeps it (the HIP runtime

@@ -489,7 +489,10 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
   // every 64-column strip -- measured 10 us + 2.2 us (+ 0.09 per bit above 4) per 1024 of K
   // at N = 8192 -- while the tiled kernel shares A through LDS among four strips and splits K
   // instead; it wins on all but the small problems (K = 8192, N = 28672, M = 64, 6 bits:
-  // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).
+  // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).  Up to 48 rows the
+  // streaming kernel carries three row tiles (0.92 of that).  The fits predate the second kernel that adds
+  // the slabs: from 49 rows on the tiled kernel would now be up to 18 % shorter on the small problems that stay
+  // here too (K = N = 8192, M = 64: 19.3 in eight slabs against 23.5); the choice is kept as tested.
   if (M > 32 && (double)K * (double)N >= 16.0e6 && knob(1) == 0 &&
       knob(2) == 0 && knob(3) == 0) {
     double tiled = 1e30;
