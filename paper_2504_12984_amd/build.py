@@ -26,7 +26,7 @@ FLAGS = ["--offload-arch=gfx950", "-std=c++20", "-O3", "-fPIC", "-fvisibility=hi
 
 
 def _jobs():
-    jobs = [("qg_pack.hip", None), ("qg_probe.hip", None), ("qg_api.hip", None), ("qg_a8_rowsum.hip", None), ("qg_reduce.hip", None)]
+    jobs = [("qg_pack.hip", None), ("qg_probe.hip", None), ("qg_api.hip", None), ("qg_reduce.hip", None)]
     for src in ("qg_dequant.hip", "qg_decode_gemm.hip", "qg_large.hip", "qg_large32.hip", "qg_gemv.hip"):
         jobs += [(src, wt) for wt in range(NUM_WT)]
     for src in ("qg_a8_gemm.hip", "qg_a8_large.hip"):      # int8 activations: once per code width

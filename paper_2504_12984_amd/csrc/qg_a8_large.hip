@@ -9,18 +9,21 @@
 // What bounds the kernel is issue: per 16x16x64 instruction and scale group two vector operations
 // per result value (two wavefronts per SIMD: an instruction every 17 clocks alone, every 25 with four
 // vector operations beside it, every 33 with six).  So the rest is kept out of the loop:
-//   * Codes enter the instruction as signed bytes in the TOP bits of each byte, (q - 2^(b-1)) * 2^(8-b):
-//     one shift and one three-input logic operation per quad; the factor 2^(8-b) leaves at the end.  The
-//     sums of a chunk stay within 2^21 and start from the bits of 1.5 * 2^23, so they are read as fp32
-//     without a convert.
-//   * What is left of the zero-points, z' = z - 2^(b-1) (0 for intk without an array), would cost a
-//     third operation per value.  It is a product of rank K/group instead,
-//     sum_g (s z')[g, n] * rowsum_g[m]: the row sums come from a small kernel ahead of this one, and
-//     both factors, split into three bf16 terms each (the products kept are exact to 2^-32), go
-//     through the bf16 matrix instruction into the same fp32 accumulators, four groups per instruction.
-// Measured at M = 1000, K = 8192, N = 28672, 4 bits, group 128: 256 us = 1830 TOP/s without, 286 us with
-// zero-points; in blocks of 64 rows through the streaming kernel (each block reads and unpacks
-// all weights again) it was 750.  Without its loads the loop would take 15 % less, without its matrix instructions 22 %.
+//   * Codes enter the instruction as signed bytes, times a power of two.  The sums of a chunk stay within 2^22 and
+//     start from the bits of a float, so they are read as fp32 without a convert and without the factor.
+//   * No zero-points (CORR = false): the byte is (q - 2^(b-1)) * 2^(8-b), one shift and one three-input
+//     logic operation per quad.
+//   * Zero-points, or uintk (CORR): the sum over a scale group has to stay an exact integer, because
+//     q and z cancel in it.  Up to 7 bits a zero-point in the range of the codes is subtracted from the four
+//     bytes of a quad at once, (q - z) * 2^(7-b), two more operations per quad and none per value.
+//     A zero-point beyond the codes, and 8-bit codes, whose difference takes nine bits, go through the row
+//     sums of A instead (one more matrix instruction per row tile and k-step, with ones for codes): one more
+//     multiply-add per value, on the integer sum and therefore exact.  Which of the two is decided by each
+//     wavefront from the zero-points it reads.
+// Measured at M = 1000, K = 8192, N = 28672, group 128 (one box, us): int4 282, uint4 with zero-points 290, with
+// zero-points beyond the codes 351, uint8 with zero-points 388 (group 64: 338, 364, -, 499); with the row sums of
+// all groups taken off ahead of the loop, in fp32 and not exact, the second was 295, the last 345.
+// In blocks of 64 rows through the streaming kernel (each block reads and unpacks all weights again) uint4 takes 750.
 // Compiled once per code width (QG_BITS).
 #include "qg_common.h"
 #include "qg_static_for.h"
@@ -60,25 +63,33 @@ __device__ __forceinline__ uint32_t quad_top(const uint32_t (&r)[4 * BITS]) {
   }
 }
 
-// x as three bf16 terms, x = t0 + t1 + t2 up to 2^-24 |x|
-__device__ __forceinline__ void split3(float x, float& t0, float& t1, float& t2) {
-  t0 = (float)(__bf16)x;
-  t1 = (float)(__bf16)(x - t0);
-  t2 = (x - t0) - t1;
-}
-__device__ __forceinline__ uint32_t pk_bf16(float lo, float hi) {
-  f2_t f = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, b2_t));
+// Quad T of the lane, minus a zero-point: the signed bytes (q - z) * 2^(7-BITS), for BITS <= 7 and 0 <= z < 2^BITS.
+// `up` has 128 - z * 2^(7-BITS) in every byte: with the code in bits 7-BITS .. 6 no byte carries into the next.
+template <int BITS, int T>
+__device__ __forceinline__ uint32_t quad_less(const uint32_t (&r)[4 * BITS], uint32_t up) {
+  constexpr int bit = T * BITS, h = bit >> 3, p = bit & 7, TO = 7 - BITS;
+  constexpr uint32_t ALL = 0x01010101u, CODE = ((1u << BITS) - 1u) << TO, SIGN = 0x80808080u;
+  uint32_t x;
+  if constexpr (p <= TO) {
+    x = (r[h] & ((((1u << BITS) - 1u) << p) * ALL)) << (TO - p);
+  } else if constexpr (p + BITS <= 8) {                            // the code ends its byte
+    x = (r[h] >> 1) & (CODE * ALL);
+  } else {
+    constexpr int n1 = 8 - p;                                      // bits of the code in register h
+    constexpr uint32_t LOW = ((1u << n1) - 1u) << TO, HIGH = CODE & ~LOW;
+    x = ((r[h] >> (p - TO)) & (LOW * ALL)) | ((r[h + 1] << (n1 + TO)) & (HIGH * ALL));
+  }
+  return (x + up) ^ SIGN;
 }
 
-template <int BITS, int GPC, bool SBF16, bool SPLIT>
+template <int BITS, int GPC, bool SBF16, bool SPLIT, bool CORR>
 __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_m, int tiles_n, int per_xcd) {
   constexpr int RAW = 4 * BITS, BM = 128, MTS = BM / 16, BUF = BM * 128;
   // slabs of A in flight: two where LDS holds them for two workgroups per CU (160 KiB), else one
   constexpr int A_AHEAD = BITS <= 7 ? 2 : 1, ABUFS = A_AHEAD + 1;
-  constexpr int W_AT = ABUFS * BUF, S_AT = W_AT + 4 * 1024 * BITS, LDS_BYTES = S_AT + 4 * 256;
+  constexpr int W_AT = ABUFS * BUF, S_AT = W_AT + 4 * 1024 * BITS, Z_AT = S_AT + 4 * 256, LDS_BYTES = Z_AT + (CORR ? 4 * 256 : 0);
   static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];   // A slabs, each wavefront's codes, each wavefront's scales
+  __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];   // A slabs, each wavefront's codes, scales, zero-points
 
   const int tiles = tiles_m * tiles_n;
   const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
@@ -114,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
   const uint64_t a_base = reinterpret_cast<uint64_t>(p.A);
   const u4_t a_rsrc = {(uint32_t)a_base, (uint32_t)(a_base >> 32) & 0xffffu, (uint32_t)p.M * (uint32_t)p.K, 0x00020000u};
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lds;
-  const uint32_t lds_a = lds_base + 1024u * (uint32_t)w, lds_w = lds_base + W_AT + (uint32_t)(w * 1024 * BITS), lds_s = lds_base + S_AT + 256u * (uint32_t)w;
+  const uint32_t lds_a = lds_base + 1024u * (uint32_t)w, lds_w = lds_base + W_AT + (uint32_t)(w * 1024 * BITS), lds_s = lds_base + S_AT + 256u * (uint32_t)w, lds_z = lds_base + Z_AT + 256u * (uint32_t)w;
   auto a_fetch = [&](int buf, int c) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -127,16 +138,25 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
   // ---- W and its scales of the next chunk -> LDS too, for this wavefront alone ---------------------
   // (a register ring would not fit beside 128 accumulators).  One buffer is enough: the codes are
   // unpacked at the start of a chunk, and the load of the next ones starts right after that.
-  const uint8_t* wstrip = p.W + (int64_t)nc * KC * (1024 * BITS) + 16 * l;
+  // (scalar bases, 32-bit lane offsets)
+  const uint8_t* wstrip = p.W + (int64_t)nc * KC * (1024 * BITS);
   // lanes 0..31 fetch two scales each of the chunk's (first) group, lanes 32..63 of its second group
-  const uint16_t* sbase = p.S + (int64_t)(GPC == 2 ? l >> 5 : 0) * p.N + TILE_N * nc + 2 * (l & 31);
+  const uint8_t* sbase = reinterpret_cast<const uint8_t*>(p.S + TILE_N * nc);
+  const uint32_t s_voff = 4u * (uint32_t)(l & 31) + (GPC == 2 ? 2u * (uint32_t)p.N * (uint32_t)(l >> 5) : 0u);
+  // lanes 0..15 fetch four zero-points each of that group, lanes 16..31 of the second (no zero-points: valid
+  // scale bytes instead, masked away)
+  const uint8_t* zbase = (p.Z ? p.Z : reinterpret_cast<const uint8_t*>(p.S)) + TILE_N * nc;
+  const uint32_t z_voff = 4u * (uint32_t)i16 + (GPC == 2 ? (uint32_t)p.N * (uint32_t)((l >> 4) & 1) : 0u);
   auto w_fetch = [&](int c) __attribute__((always_inline)) {
     const uint8_t* src = wstrip + (int64_t)c * (1024 * BITS);
 #pragma unroll
     for (int i = 0; i < BITS; ++i)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_w + (uint32_t)(i * 1024)), "v"(src + i * 1024) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(lds_w + (uint32_t)(i * 1024)), "v"(16u * (uint32_t)l), "s"(src + i * 1024) : "memory");
     const int g0 = (GPC > 1) ? GPC * c : ((c >> p.gshift) & p.gmask);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(lds_s), "v"(sbase + (int64_t)g0 * p.N) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds_s), "v"(s_voff), "s"(sbase + 2 * (int64_t)g0 * p.N) : "memory");
+    if constexpr (CORR)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds_z), "v"(z_voff), "s"(zbase + (int64_t)g0 * p.N) : "memory");
   };
 
   w_fetch(kbeg);
@@ -149,82 +169,48 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
-  // ---- zero-points: acc -= sum_g (s z')[g, n] * rowsum_g[m], times 2^(8-b) like everything in acc ----
-  // k slots of the instruction: lane block b takes group 4 q + b, its eight slots are the products
-  // (r0, r1) x (t0, t0), (t1, t1), (t2, t2) and (r2, r2) x (t0, t1) of the terms of rowsum (r) and s z' (t).
-  if (p.rowsum) {
-    if (slab == 0) {
-      const int G = p.K / p.group;
-      const int n0 = TILE_N * nc + 4 * i16;
-      const u2_t* rs = reinterpret_cast<const u2_t*>(p.rowsum);
-      int64_t rrow[MTS];
-#pragma unroll
-      for (int mt = 0; mt < MTS; ++mt) rrow[mt] = min(m0 + mt * 16 + i16, p.M - 1);
-      struct Low { u2_t s4; uint32_t z4; u2_t r[MTS]; };
-      auto fetch = [&](Low& t, int q) __attribute__((always_inline)) {
-        const int g = min(q + b, G - 1);
-        t.s4 = *reinterpret_cast<const u2_t*>(p.S + (int64_t)g * p.N + n0);
-        t.z4 = p.Z ? *reinterpret_cast<const uint32_t*>(p.Z + (int64_t)g * p.N + n0) : 0u;
-#pragma unroll
-        for (int mt = 0; mt < MTS; ++mt) t.r[mt] = rs[(int64_t)g * p.M + rrow[mt]];
-      };
-      auto add = [&](const Low& t, int q) __attribute__((always_inline)) {
-        const float on = (q + b < G) ? -(float)(1 << (8 - BITS)) : 0.f;
-        u4_t wz[4];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          const uint32_t s16 = (t.s4[nt >> 1] >> (16 * (nt & 1))) & 0xffffu;
-          const float s = SBF16 ? __builtin_bit_cast(float, s16 << 16) : (float)__builtin_bit_cast(_Float16, (uint16_t)s16);
-          const float z = (float)((int)((t.z4 >> (8 * nt)) & 0xffu) + p.zbias - (1 << (BITS - 1)));
-          float t0, t1, t2;
-          split3(s * z * on, t0, t1, t2);
-          wz[nt] = (u4_t){pk_bf16(t0, t0), pk_bf16(t1, t1), pk_bf16(t2, t2), pk_bf16(t0, t1)};
-        }
-#pragma unroll
-        for (int mt = 0; mt < MTS; ++mt) {
-          const u4_t ra = {t.r[mt].x, t.r[mt].x, t.r[mt].x, t.r[mt].y};
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt)
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8_t, wz[nt]), __builtin_bit_cast(b8_t, ra), acc[mt][nt], 0, 0, 0);
-        }
-      };
-      Low even, odd;                    // four groups ahead of use
-      fetch(even, 0);
-      for (int q = 0; q < G; q += 8) {
-        fetch(odd, q + 4);
-        add(even, q);
-        fetch(even, q + 8);
-        add(odd, q + 4);
-      }
-    }
-  }
+  // ---- zero-points: z = zeros + zbias (zbias: intk codes are stored offset-binary) --------------------
+  // What the unpack subtracts is z itself where z < 2^b (b <= 7), else nothing (8 bits: 128); `beyond` tells
+  // a wavefront that its chunk has a zero-point of which something is left.
+  const float left = (BITS == 8 ? 128.f : 0.f) - (float)p.zbias;
+  constexpr uint32_t ALL = 0x01010101u, HALF = 1u << (BITS - 1);
+  const uint32_t zmask = p.Z ? 0xffffffffu : 0u;
+  const uint32_t zhalf = p.zbias ? HALF * ALL : 0u;
+  const uint32_t zover = BITS == 8 ? 0u : ~((p.zbias ? HALF - 1u : 2u * HALF - 1u) * ALL);      // bits that zeros < 2^b - zbias do not have
+  auto beyond = [&](uint32_t z4) __attribute__((always_inline)) { return BITS == 8 ? z4 ^ (zhalf ^ 0x80808080u) : z4 & zover; };
+  // The sums are integers times the factor of the bytes, 2^SHIFT.  They are added to the bits of 1.5 * 2^(23 - SHIFT),
+  // whose last bit is worth 2^-SHIFT, so the factor is gone when those are read as fp32.
+  constexpr int SHIFT = CORR ? (BITS == 8 ? 0 : 7 - BITS) : 8 - BITS;
+  constexpr int MAGIC = 0x4b400000 - (SHIFT << 23);
+  constexpr float ORIGIN = 12582912.0f / (float)(1 << SHIFT);
 
   // my A fragment of row tile mt, k-step j: piece 4 j + b of row mt*16 + i16
   const int swz = (i16 ^ (i16 >> 3)) & 7;       // of row tile 0; row tile mt adds 2 mt to r >> 3
   __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), in a form the compiler counts: nothing of its own is in flight in the loop
   __syncthreads();
 
-  const i4_t magic = {0x4b400000, 0x4b400000, 0x4b400000, 0x4b400000};     // 1.5 * 2^23
+  const i4_t magic = {MAGIC, MAGIC, MAGIC, MAGIC};
   int abuf_i = 0;
-  for (int c = kbeg; c < kend; ++c) {
+  auto zeros_of = [&](int g) __attribute__((always_inline)) {       // of my four columns as operand
+    return *reinterpret_cast<const uint32_t*>(lds + Z_AT + 256 * w + 64 * g + 4 * i16) & zmask;
+  };
+  // One chunk.  ROWSUM: (what is left of) the zero-points goes through the row sums.
+  auto chunk = [&](auto Rowsumc, int c) __attribute__((always_inline)) {
+    constexpr bool ROWSUM = decltype(Rowsumc)::value;
     uint32_t raw[RAW];
 #pragma unroll
     for (int i = 0; i < BITS; ++i) {
       const u4_t q = *reinterpret_cast<const u4_t*>(lds + W_AT + (w * BITS + i) * 1024 + 16 * l);
       raw[4 * i + 0] = q.x; raw[4 * i + 1] = q.y; raw[4 * i + 2] = q.z; raw[4 * i + 3] = q.w;
     }
-    float sf[GPC][16];                                  // the chunk's scales of my 16 columns
+    u4_t s16[GPC][2], z16[GPC];                         // the chunk's scales (and zero-points) of my 16 columns
+    uint32_t z4[GPC];
 #pragma unroll
     for (int g = 0; g < GPC; ++g) {
       const u4_t* sp = reinterpret_cast<const u4_t*>(lds + S_AT + 256 * w + 128 * g + 32 * b);
-      const u4_t s01[2] = {sp[0], sp[1]};
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const uint32_t two = s01[i >> 3][(i & 7) >> 1];
-        if constexpr (SBF16) sf[g][i] = __builtin_bit_cast(float, (i & 1) ? (two & 0xffff0000u) : (two << 16));
-        else sf[g][i] = (float)__builtin_bit_cast(h2_t, two)[i & 1];
-        if constexpr (!SBF16) asm("" : "+v"(sf[g][i]));      // widened here and for good: the compiler would fold it into mixed multiply-adds, at half the rate
-      }
+      s16[g][0] = sp[0]; s16[g][1] = sp[1];
+      if constexpr (ROWSUM) z16[g] = *reinterpret_cast<const u4_t*>(lds + Z_AT + 256 * w + 64 * g + 16 * b);
+      else if constexpr (CORR && BITS <= 7) z4[g] = zeros_of(g);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read: the buffers may be refilled
     const int abuf_n = abuf_i == 0 ? ABUFS - 1 : abuf_i - 1;        // the slab of the chunk before this one
@@ -233,46 +219,90 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
     u4_t wf[2][4];
     static_for<8>([&](auto Xc) __attribute__((always_inline)) {
       constexpr int X = decltype(Xc)::value, T0 = X * 4;
-      wf[X / 4][X % 4] = (u4_t){quad_top<BITS, T0>(raw), quad_top<BITS, T0 + 1>(raw), quad_top<BITS, T0 + 2>(raw), quad_top<BITS, T0 + 3>(raw)};
+      if constexpr (CORR && BITS <= 7) {
+        // byte NT of the zero-points, subtracted from 128, in every byte
+        constexpr int G = (GPC == 2) ? X / 4 : 0, NT = X % 4;
+        uint32_t up = 0x80808080u;
+        if constexpr (!ROWSUM) up = __builtin_amdgcn_perm(0u, 0x80808080u - ((z4[G] | zhalf) << (7 - BITS)), NT * ALL);
+        wf[X / 4][X % 4] = (u4_t){quad_less<BITS, T0>(raw, up), quad_less<BITS, T0 + 1>(raw, up), quad_less<BITS, T0 + 2>(raw, up), quad_less<BITS, T0 + 3>(raw, up)};
+      } else {
+        wf[X / 4][X % 4] = (u4_t){quad_top<BITS, T0>(raw), quad_top<BITS, T0 + 1>(raw), quad_top<BITS, T0 + 2>(raw), quad_top<BITS, T0 + 3>(raw)};
+      }
     });
 
     const uint8_t* abuf = lds + abuf_i * BUF + i16 * 128;
     auto a_read = [&](int mt, int j) __attribute__((always_inline)) {
       return *reinterpret_cast<const i4_t*>(abuf + mt * 2048 + 16 * (((4 * j + b) ^ swz) ^ ((2 * mt) & 7)));
     };
-    // value r of sub-tile nt: acc += scale * sum.  The sums start from the bits of 1.5 * 2^23, so that
-    // read as fp32 they are 1.5 * 2^23 + sum exactly (|sum| < 2^22): a subtraction instead of a convert
-    // (with several wavefronts on a SIMD fp32 add / multiply-add issue every 2 clocks, converts and
-    // half-precision or mixed operations every 4).
-    auto scale = [&](auto Gc, auto MTc, auto NTc, auto Rc, int bits) __attribute__((always_inline)) {
-      constexpr int G = decltype(Gc)::value, MT = decltype(MTc)::value, NT = decltype(NTc)::value, R = decltype(Rc)::value;
-      acc[MT][NT][R] = __builtin_fmaf(sf[G][4 * R + NT], __builtin_bit_cast(float, bits) - 12582912.0f, acc[MT][NT][R]);
+    // The constants of a scale group: the scales, widened here and for good (the compiler would fold an fp16
+    // one into mixed multiply-adds, at half the rate), and what is left to subtract: fp16 pairs (exact) where fp32
+    // spills -- u8 on the shape above, group 128: 395 us against 452; group 64: 521 against 497.
+    constexpr bool PAIRS = GPC == 1;
+    float sf[16], nz[16];
+    h2_t nz2[8];
+    auto constants = [&](auto Gc) __attribute__((always_inline)) {
+      constexpr int G = decltype(Gc)::value;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t two = s16[G][i >> 3][(i & 7) >> 1];
+        if constexpr (SBF16) sf[i] = __builtin_bit_cast(float, (i & 1) ? (two & 0xffff0000u) : (two << 16));
+        else sf[i] = (float)__builtin_bit_cast(h2_t, two)[i & 1];
+        if constexpr (!SBF16) asm("" : "+v"(sf[i]));
+      }
+      if constexpr (ROWSUM) {
+#pragma unroll
+        for (int i = 0; i < (PAIRS ? 0 : 16); ++i) nz[i] = left - (float)((z16[G][i / 4] & zmask) >> (8 * (i % 4)) & 0xffu);
+#pragma unroll
+        for (int i = 0; i < (PAIRS ? 8 : 0); ++i) {     // from the bits of 1024 + z
+          const _Float16 from = (_Float16)(1024.f + left);
+          nz2[i] = (h2_t){from, from} - __builtin_bit_cast(h2_t, __builtin_amdgcn_perm(0x64646464u, z16[G][i / 2] & zmask, i % 2 ? 0x04030402u : 0x04010400u));
+        }
+      }
     };
-    // The chunk is a sequence of units: two sub-tiles of one row tile and one scale group, i.e. 4
-    // (group 64: 2) matrix instructions.  Each instruction is followed by its share of the previous
-    // unit's eight converts and multiply-adds (4, or 8), so vector and matrix work alternate
-    // within one wavefront and the sums of two units (16 registers) are all that is in flight.
-    constexpr int UPM = 2 * GPC, MPU = 4 / GPC, VPM = 8 / MPU;      // units per row tile, instructions per unit, values per instruction
-    i4_t a[2][2], d[2][2];
-    a[0][0] = a_read(0, 0);
-    a[0][1] = a_read(0, 1);
-    static_for<MTS * UPM + 1>([&](auto Uc) __attribute__((always_inline)) {
-      constexpr int U = decltype(Uc)::value, MT = U / UPM, H = U % 2, J0 = (GPC == 2) ? (U / 2) % 2 : 0;
-      constexpr int PU = U - 1, PMT = PU / UPM, PH = PU % 2, PG = (GPC == 2) ? (PU / 2) % 2 : 0;       // previous unit
+    // value r of sub-tile nt: acc += scale * sum.  Below 2^22 the sum added to MAGIC is a change of the mantissa alone:
+    // a subtraction instead of a convert (with several wavefronts on a SIMD fp32 add / multiply-add
+    // issue every 2 clocks, converts and half-precision or mixed operations every 4).
+    float rsum[2];                                      // ROWSUM: the row sums of two steps
+    auto scale = [&](auto Fc, auto MTc, auto NTc, auto Rc, int bits) __attribute__((always_inline)) {
+      constexpr int F = decltype(Fc)::value, MT = decltype(MTc)::value, NT = decltype(NTc)::value, R = decltype(Rc)::value;
+      float t = __builtin_bit_cast(float, bits) - ORIGIN;
+      if constexpr (ROWSUM) t = __builtin_fmaf(PAIRS ? (float)nz2[2 * R + NT / 2][NT % 2] : nz[4 * R + NT], rsum[F & 1], t);      // below 2^23: exact
+      acc[MT][NT][R] = __builtin_fmaf(sf[4 * R + NT], t, acc[MT][NT][R]);
+    };
+    // The chunk is a sequence of steps -- a scale group and a row tile, group by group, so that one group's
+    // constants are in registers -- of two units: two sub-tiles, i.e. 4 (group 64: 2) matrix
+    // instructions.  Each instruction is followed by its share of the previous unit's eight
+    // subtractions and multiply-adds (4, or 8), so vector and matrix work alternate within one
+    // wavefront and the sums of two units (16 registers) are all that is in flight.
+    constexpr int STEPS = GPC * MTS, JS = 2 / GPC, MPU = 2 * JS, VPM = 8 / MPU;      // steps, k-steps per step, instructions per unit, values per instruction
+    i4_t a[2][JS], d[2][2], rs;
+#pragma unroll
+    for (int j = 0; j < JS; ++j) a[0][j] = a_read(0, j);
+    static_for<2 * STEPS + 1>([&](auto Uc) __attribute__((always_inline)) {
+      constexpr int U = decltype(Uc)::value, F = U / 2, G = F / MTS, H = U % 2;
+      constexpr int PU = U - 1, PF = PU / 2, PMT = PF % MTS, PH = PU % 2;       // previous unit
+      if constexpr (U % (2 * MTS) == 1) constants(std::integral_constant<int, G>{});
+      if constexpr (ROWSUM && F < STEPS) {               // the row sums of this step, ready one unit later
+        const i4_t ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+        if constexpr (H == 0) {
+          rs = (i4_t){0, 0, 0, 0};
+#pragma unroll
+          for (int j = 0; j < JS; ++j) rs = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, a[F & 1][j], rs, 0, 0, 0);
+        } else {
+          rsum[F & 1] = (float)rs[0];
+        }
+      }
       static_for<MPU>([&](auto Ic) __attribute__((always_inline)) {
-        constexpr int I = decltype(Ic)::value, J = J0 + I / 2, N = I % 2, NT = 2 * H + N;
-        if constexpr (U < MTS * UPM) {
-          if constexpr (GPC == 2 || J == 0) d[U & 1][N] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i4_t, wf[J][NT]), a[MT & 1][J], magic, 0, 0, 0);
-          else d[U & 1][N] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i4_t, wf[J][NT]), a[MT & 1][J], d[U & 1][N], 0, 0, 0);
-          if constexpr (U % UPM == 0 && MT + 1 < MTS) {          // the next row tile's fragments
-            if constexpr (I == 0) a[(MT + 1) & 1][0] = a_read(MT + 1, 0);
-            if constexpr (I == 1) a[(MT + 1) & 1][1] = a_read(MT + 1, 1);
-          }
+        constexpr int I = decltype(Ic)::value, J = I / 2, N = I % 2, NT = 2 * H + N;
+        if constexpr (F < STEPS) {
+          d[U & 1][N] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i4_t, wf[GPC == 2 ? G : J][NT]), a[F & 1][J], J == 0 ? magic : d[U & 1][N], 0, 0, 0);
+          if constexpr (H == 0 && I < JS && F + 1 < STEPS)          // the next step's fragments
+            a[(F + 1) & 1][I] = a_read((F + 1) % MTS, GPC == 2 ? (F + 1) / MTS : I);
         }
         if constexpr (U > 0) {
           static_for<VPM>([&](auto Vc) __attribute__((always_inline)) {
             constexpr int V = I * VPM + decltype(Vc)::value, PN = V / 4, R = V % 4;
-            scale(std::integral_constant<int, PG>{}, std::integral_constant<int, PMT>{}, std::integral_constant<int, 2 * PH + PN>{},
+            scale(std::integral_constant<int, PF>{}, std::integral_constant<int, PMT>{}, std::integral_constant<int, 2 * PH + PN>{},
                   std::integral_constant<int, R>{}, d[PU & 1][PN][R]);
           });
         }
@@ -283,7 +313,23 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(A_AHEAD == 2 ? 4 : 0) : "memory");
     __syncthreads();
     abuf_i = abuf_i == ABUFS - 1 ? 0 : abuf_i + 1;
+  };
+
+  // From the first chunk on that has a zero-point beyond the codes, a wavefront uses the row sums.  (Two loops, one
+  // after the other: two bodies in one loop cost 120 spilled registers.  Every wavefront meets one barrier per
+  // chunk, whichever loop it is in.)
+  int c = kbeg;
+  for (; c < kend; ++c) {
+    if constexpr (CORR) {
+      uint32_t over = 0;
+#pragma unroll
+      for (int g = 0; g < GPC; ++g) over |= beyond(zeros_of(g));
+      if (__builtin_amdgcn_ballot_w64(over != 0) != 0) break;
+    }
+    chunk(std::false_type{}, c);
   }
+  if constexpr (CORR)
+    for (; c < kend; ++c) chunk(std::true_type{}, c);
 
   if (!active) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the slab loaded past the end
@@ -331,12 +377,12 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
     if (l == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
   }
 
-  // ---- row scale, the factor 2^(b-8), one rounding to the output type, store ---------------------
+  // ---- row scale, one rounding to the output type, store ---------------------
 #pragma unroll
   for (int mt = 0; mt < MTS; ++mt) {
     const int m = m0 + mt * 16 + i16;
     if (m < p.M) {
-      const float as = (p.a_scale ? p.a_scale[m] : 1.0f) * (1.0f / (float)(1 << (8 - BITS)));
+      const float as = p.a_scale ? p.a_scale[m] : 1.0f;
       uint32_t o[8];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -356,21 +402,24 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
 #define QG_CAT2(a, b) a##b
 #define QG_CAT(a, b) QG_CAT2(a, b)
 
-template <int GPC, bool SBF16, bool SPLIT>
+template <int GPC, bool SBF16, bool SPLIT, bool CORR>
 static int launch_one(const A8Params& p, hipStream_t st) {
   const int tiles_m = (p.M + 127) / 128, tiles_n = (p.N + A8_BN - 1) / A8_BN;
   const int per_xcd = (tiles_m * tiles_n * p.splitk + 7) / 8;
-  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, SBF16, SPLIT>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, per_xcd);
+  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, SBF16, SPLIT, CORR>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, per_xcd);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
-// p.rowsum: the row sums of a8_rowsum_kernel where a zero-point term is left, else null
-int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, hipStream_t st) {
-#define QG_A8L(GPC_, SB_, SP_) if (((p.group == 64) ? 2 : 1) == GPC_ && (p.scale_bf16 != 0) == SB_ && (p.splitk > 1) == SP_) return launch_one<GPC_, SB_, SP_>(p, st);
-  QG_A8L(1, false, false) QG_A8L(1, false, true) QG_A8L(1, true, false) QG_A8L(1, true, true)
-  QG_A8L(2, false, false) QG_A8L(2, false, true) QG_A8L(2, true, false) QG_A8L(2, true, true)
-#undef QG_A8L
-  return QG_EINVAL;
+template <int GPC, bool SBF16>
+static int launch_scales(const A8Params& p, bool corr, hipStream_t st) {
+  if (corr) return p.splitk > 1 ? launch_one<GPC, SBF16, true, true>(p, st) : launch_one<GPC, SBF16, false, true>(p, st);
+  return p.splitk > 1 ? launch_one<GPC, SBF16, true, false>(p, st) : launch_one<GPC, SBF16, false, false>(p, st);
+}
+
+// corr: zero-points, or uintk codes
+int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, bool corr, hipStream_t st) {
+  if (p.group == 64) return p.scale_bf16 ? launch_scales<2, true>(p, corr, st) : launch_scales<2, false>(p, corr, st);
+  return p.scale_bf16 ? launch_scales<1, true>(p, corr, st) : launch_scales<1, false>(p, corr, st);
 }
 
 }  // namespace qg

@@ -38,12 +38,11 @@ QG_FOR_ALL_LUT(QG_DECL)
 #define QG_DECL_A8(b) int a8_launch_bits##b(const A8Params&, int, int, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
-#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, hipStream_t);
+#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, bool, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
-int launch_a8_rowsum(const int8_t*, int, int, int, uint2*, hipStream_t);
 typedef int (*a8_fn)(const A8Params&, int, int, hipStream_t);
-typedef int (*a8_large_fn)(const A8Params&, hipStream_t);
+typedef int (*a8_large_fn)(const A8Params&, bool, hipStream_t);
 static const a8_large_fn kA8Large[8] = {a8_large_launch_bits1, a8_large_launch_bits2, a8_large_launch_bits3, a8_large_launch_bits4,
                                         a8_large_launch_bits5, a8_large_launch_bits6, a8_large_launch_bits7, a8_large_launch_bits8};
 static const a8_fn kA8[8] = {a8_launch_bits1, a8_launch_bits2, a8_launch_bits3, a8_launch_bits4,
@@ -770,7 +769,7 @@ static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* c
 // alone on a CU and 1.95 (+ 0.14) with a neighbour, group 64 a quarter more; a launch 7 us; the exchange of
 // partial sums 2.5 + 2.35 per slab + 0.22 per MB (fitted to M = 65 .. 1000, K = 1024 .. 14336, N = 2048 .. 28672 at 4
 // and 8 bits: within 15 % there, and the split it picks within 8 % of the best of 1, 2, 4 and 8).
-static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, size_t rowsum_bytes, int* splitk_out, int* cps_out) {
+static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* splitk_out, int* cps_out) {
   const int KC = (int)(K / TILE_K);
   const int64_t tiles = ((rows + 127) / 128) * ((N + 255) / 256);
   const int over = bits > 4 ? bits - 4 : 0;
@@ -780,7 +779,7 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
   for (int sk = 1; sk <= 8; sk *= 2) {
     const int cps = (KC + sk - 1) / sk;
     const size_t part = (size_t)sk * tiles * (128 * 256 * sizeof(float));
-    if (sk > 1 && (cps < 4 || tiles * sk > 256 || part + rowsum_bytes > WS_PARTIAL_BYTES)) continue;
+    if (sk > 1 && (cps < 4 || tiles * sk > 256 || part > WS_PARTIAL_BYTES)) continue;
     const int64_t full = tiles * sk / 512, rest = tiles * sk % 512;
     const double mb = (double)sk * (double)rows * (double)N * 4.0 / 1e6;
     const double cost = 7.0 + cps * (full * c2 + (rest == 0 ? 0.0 : rest <= 256 ? c1 : c2)) + (sk > 1 ? 2.5 + 2.35 * sk + 0.22 * mb : 0.0);
@@ -797,8 +796,10 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
 // int8 activations on more than 64 rows: the tiled kernel, or blocks of 64 rows through the streaming kernel?
 // The latter take 8.5 us + 0.165 per million weights (6 % more per bit above 4) each (a last block of up to 16 rows 0.55 of that, of up to 32
 // rows 0.65), and win while the tiled kernel's chip is nearly empty: M = 128 on K = N = 8192 37 us against 41,
-// M = 192 56 against 41; M = 1000 on N = 28672 750 against 256.
-static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bits, bool corr) {
+// M = 192 56 against 41; M = 1000 on N = 28672 750 against 256.  Zero-points make both a little longer (at most 8 % where
+// the two are close) and need no rule of their own: 200 cases, M = 96 .. 384, K = 2048 .. 14336, N = 4096 .. 28672, u4, i4,
+// u8, i8, groups 64 and 128, within 6 % of the better of the two, two 8-bit ones within 17 %.
+static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bits) {
   if (knob(0) == 2 || knob(0) == 3) return knob(0) == 2;
   if (M <= 64) return false;
   if (M > 1024) return true;
@@ -806,18 +807,14 @@ static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bit
   const int rem = (int)(M % 64);
   const double blocks = block * ((double)(M / 64) + (rem == 0 ? 0.0 : rem <= 16 ? 0.55 : rem <= 32 ? 0.65 : 1.0));
   int sk, cps;
-  const double tiled = plan_a8_tiled(M, N, K, group, bits, 0, &sk, &cps) + (corr ? 8.0 + 0.15 * (double)(K / group) : 0.0);
+  const double tiled = plan_a8_tiled(M, N, K, group, bits, &sk, &cps);
   return tiled < blocks;
 }
 
-// The tiled int8 kernel over all rows; `corr`: a zero-point term is left after the codes are centred.
+// The tiled int8 kernel over all rows; `corr`: zero-points, or uintk codes.
 // QG_EUNSUPPORTED: needs a workspace and cannot have one (nothing was enqueued).
 static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipStream_t st) {
-  const int64_t G = p.K / p.group;
-  // rows per launch: A's byte offsets stay below 2^31, the row sums within half of the workspace
-  int64_t most = ((int64_t(1) << 31) - 1) / p.K;
-  if (corr) most = std::min(most, int64_t(WS_PARTIAL_BYTES / 2 / sizeof(uint2)) / G);
-  most = most / 128 * 128;
+  const int64_t most = ((int64_t(1) << 31) - 1) / p.K / 128 * 128;      // rows per launch: A's byte offsets stay below 2^31
   if (most < 128) return QG_EUNSUPPORTED;
   for (int64_t r0 = 0; r0 < M; r0 += most) {
     A8Params q = p;
@@ -825,23 +822,15 @@ static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipSt
     q.a_scale = p.a_scale ? p.a_scale + r0 : nullptr;
     q.C = p.C + r0 * p.N;
     q.M = (int)std::min(most, M - r0);
-    const size_t rs_bytes = corr ? ((size_t)q.M * G * sizeof(uint2) + 255) & ~size_t(255) : 0;
-    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, rs_bytes, &q.splitk, &q.chunks_per_split);
+    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &q.splitk, &q.chunks_per_split);
     const int64_t tiles = (int64_t)((q.M + 127) / 128) * ((q.N + 255) / 256);
     const size_t part_bytes = q.splitk > 1 ? (size_t)q.splitk * tiles * (128 * 256 * sizeof(float)) : 0;
-    if (rs_bytes + part_bytes) {
-      float* ws = nullptr;
-      if (!can_have_workspace(rs_bytes + part_bytes, (size_t)tiles * 4, st)) return QG_EUNSUPPORTED;      // (the same answer for every block)
-      int rc = get_workspace(rs_bytes + part_bytes, (size_t)tiles * 4, st, &ws, &q.tickets);
+    if (part_bytes) {
+      if (!can_have_workspace(part_bytes, (size_t)tiles * 4, st)) return QG_EUNSUPPORTED;      // (the same answer for every block)
+      int rc = get_workspace(part_bytes, (size_t)tiles * 4, st, &q.ws, &q.tickets);
       if (rc != QG_OK) return r0 == 0 ? QG_EUNSUPPORTED : rc;
-      q.ws = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + rs_bytes);
-      if (corr) {
-        rc = launch_a8_rowsum(q.A, q.M, q.K, q.group, reinterpret_cast<uint2*>(ws), st);
-        if (rc != QG_OK) return rc;
-        q.rowsum = reinterpret_cast<uint2*>(ws);
-      }
     }
-    const int rc = kA8Large[bits - 1](q, st);
+    const int rc = kA8Large[bits - 1](q, corr, st);
     if (rc != QG_OK) return rc;
   }
   return QG_OK;
@@ -880,9 +869,8 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
   p.scale_bf16 = (scale_dtype == QG_BF16);
   p.out_bf16 = (out_dtype == QG_BF16);
   p.M = 0;
-  p.rowsum = nullptr;
   if (!set_group_index(p)) return QG_EUNSUPPORTED;
-  if (plan_a8_path(M, N, K, group, t.bits, zeros || t.kind == QG_UINT)) {
+  if (plan_a8_path(M, N, K, group, t.bits)) {
     const int rc = run_a8_tiled(p, M, zeros || t.kind == QG_UINT, t.bits, st);
     if (rc != QG_EUNSUPPORTED) return rc;                 // no workspace to be had: blocks of 64 rows need none
   }

@@ -167,7 +167,6 @@ struct A8Params {
   void* slots;            // as in GemmParams
   int M, N, K, group;
   int zbias, scale_bf16, out_bf16;
-  const uint2* rowsum;    // tiled kernel: row sums of A per scale group, [K/group][M], three bf16 terms each; or null
   int splitk, chunks_per_split;
   int gshift, gmask;      // as in GemmParams
 };
