@@ -1,0 +1,65 @@
+"""Host code of the library without a GPU: what a call allocates, clears and launches, through a stand-in
+for the HIP runtime (host_runtime_stub.cpp) in a process of its own."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LIB = os.environ.get("QGEMM_LIB") or os.path.join(ROOT, "paper_2504_12984_amd", "libqgemm.so")
+
+PRELUDE = """
+import ctypes as C, json, re, sys
+stub, lib = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL), C.CDLL(sys.argv[2])
+stub.stub_take_log.restype = lib.qg_last_error.restype = C.c_char_p
+class T(C.Structure): _fields_ = [(n, C.c_int32) for n in ("kind", "bits", "ebits", "mbits")]
+P, I, L = C.c_void_p, C.c_int, C.c_int64
+lib.qgemm.argtypes = lib.qgemm_noalloc.argtypes = [P, P, P, P, T, I, I, I, L, L, L, L, P, P]
+lib.qgemm_a8.argtypes = [P, P, P, P, P, T, I, I, L, L, L, L, P, P]
+lib.qgemm_codebook.argtypes = [P, P, P, P, I, I, I, L, L, L, L, P, P]
+A = 0x10000                                                    # any aligned address: nothing is read
+def log(): return stub.stub_take_log().decode().splitlines()
+LOADED = log()
+def call(rc):
+    lines = log()
+    def ints(word): return [int(s.split()[1]) for s in lines if s.startswith(word + " ")]
+    launches = [s.split()[1:] for s in lines if s.startswith("launch ")]
+    kernel = lambda name: re.search("([a-z0-9]+(?:_[a-z0-9]+)*_kernel)", re.sub("^_ZN2qg[0-9]+", "", name)).group(1)
+    return dict(rc=rc, malloc=ints("malloc"), memset=ints("memset"),
+                launches=[(kernel(n), n, int(x), int(y)) for n, x, y, _ in launches])
+def a8(M, K, N, kind=0, bits=4, zeros=True, group=128, stream=1):
+    return call(lib.qgemm_a8(A, A, A, A, A if zeros else None, T(kind, bits, 0, 0), 0, 0, group, M, N, K, A, stream))
+def linear(M, K, N, bits=4, group=128, stream=1, entry=None):
+    return call((entry or lib.qgemm)(A, A, A, None, T(0, bits, 0, 0), 0, 0, 0, group, M, N, K, A, stream))
+def codebook(M, K, N, bits, stream=1):
+    return call(lib.qgemm_codebook(A, A, A, A, bits, 0, 0, 128, M, N, K, A, stream))
+out = []
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libstub.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "host_runtime_stub.cpp")], check=True)
+    return so
+
+
+def _run(stub, code):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + code + "\nprint(json.dumps(out))", stub, LIB], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return json.loads(r.stdout)
+
+
+def _kernels(call):
+    return [k for k, *_ in call["launches"]]
+
+
+def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
+    # more tiles than a workspace has counters for, and more with every call: nothing to allocate
+    calls = _run(stub, "out = [a8(200, 8192, 2048)] + [a8(M, 8192, 28672) for M in (1000, 4700, 4900, 9000)] + [a8(2400, 8192, 57344)]")
+    assert len(calls[0]["malloc"]) == 1                       # this one splits K
+    for c in calls[1:]:
+        assert c["rc"] == 0 and c["malloc"] == [] and c["memset"] == [] and _kernels(c)[-1] == "a8_large_kernel", c
