@@ -84,7 +84,10 @@ static thread_local std::string g_last_error;
 static std::atomic<int> g_knob[4] = {{0}, {0}, {0}, {0}};
 static int knob(int i) { return g_knob[i].load(std::memory_order_relaxed); }
 
+// A failed call's error is reported by the status, so it is read away here: the runtime keeps it until
+// hipGetLastError, and the check behind the next launch would take it for that launch's.
 static int hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();
   g_last_error = std::string(what) + ": " + hipGetErrorString(e);
   return QG_EHIP;
 }

@@ -57,6 +57,14 @@ def _kernels(call):
     return [k for k, *_ in call["launches"]]
 
 
+def test_a_failed_allocation_does_not_fail_a_call_that_needs_none(stub):
+    # eight-bit codebook, 1024 rows: no buffer for the de-quantised weight, so the fused kernel; then calls without a workspace
+    calls = _run(stub, "stub.stub_set(1, 0, 0)\nout = [codebook(1024, 4096, 4096, 8), linear(16, 8192, 2048), linear(16, 4096, 28672)]")
+    assert calls[0]["rc"] == 0 and calls[0]["malloc"] and _kernels(calls[0]) == ["large_kernel"], calls[0]
+    assert calls[1]["rc"] == -3 and calls[1]["launches"] == []        # splits K: refused, nothing enqueued
+    assert calls[2]["rc"] == 0 and _kernels(calls[2]) == ["decode_kernel"], calls[2]
+
+
 def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
     # more tiles than a workspace has counters for, and more with every call: nothing to allocate
     calls = _run(stub, "out = [a8(200, 8192, 2048)] + [a8(M, 8192, 28672) for M in (1000, 4700, 4900, 9000)] + [a8(2400, 8192, 57344)]")
