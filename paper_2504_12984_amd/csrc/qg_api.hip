@@ -136,6 +136,11 @@ static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t 
   }
   Workspace& w = *found;
   if (w.partial_bytes < partial_bytes || w.ticket_count < ticket_count) {
+    // Never under capture, not even where the capture mode allows hipMalloc: the memset would become a node of the
+    // graph, and the counters would count as cleared for calls that run before it.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }      // hipMalloc will tell
+    if (cap != hipStreamCaptureStatusNone) { g_last_error = "split-K workspace: none yet on a stream that is being captured"; return QG_EHIP; }
     const size_t pb = partial_bytes < WS_PARTIAL_BYTES ? WS_PARTIAL_BYTES : ((partial_bytes + 255) & ~size_t(255));
     const size_t tc = ticket_count < WS_TICKETS ? WS_TICKETS : ticket_count;
     unsigned char* block = nullptr;

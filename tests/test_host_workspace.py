@@ -65,6 +65,17 @@ def test_a_failed_allocation_does_not_fail_a_call_that_needs_none(stub):
     assert calls[2]["rc"] == 0 and _kernels(calls[2]) == ["decode_kernel"], calls[2]
 
 
+def test_no_workspace_is_made_on_a_capturing_stream(stub):
+    # not even where the capture mode allows it: the memset would be recorded, and the wait for a strip's other slabs
+    # in the tiled kernel would read counters that nothing has cleared
+    calls = _run(stub, "stub.stub_set(0, 1, 0)\nout = [linear(16, 8192, 2048), linear(300, 8192, 8192), linear(200, 8192, 2048)]")
+    for c in calls:
+        assert c["rc"] == -3 and c["malloc"] == [] and c["memset"] == [] and c["launches"] == [], c
+    calls = _run(stub, "linear(16, 8192, 2048)\nstub.stub_set(0, 1, 0)\nout = [linear(16, 8192, 2048), linear(300, 8192, 8192)]")
+    for c in calls:                                           # one eager call on the stream before: served
+        assert c["rc"] == 0 and c["malloc"] == [] and c["memset"] == [] and c["launches"], c
+
+
 def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
     # more tiles than a workspace has counters for, and more with every call: nothing to allocate
     calls = _run(stub, "out = [a8(200, 8192, 2048)] + [a8(M, 8192, 28672) for M in (1000, 4700, 4900, 9000)] + [a8(2400, 8192, 57344)]")
