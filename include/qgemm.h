@@ -202,8 +202,9 @@ QG_API int qgemm_noalloc(const void* A, const void* packed_W, const void* scales
  *   group 32 is QG_EUNSUPPORTED (the instruction sums 64 values of k)
  *   out_dtype QG_F16 or QG_BF16: dtype of C [M, N]
  * M >= 1 is arbitrary: up to 64 rows (more on small problems, in blocks of 64) stream the weights, larger M
- * uses an LDS-staged tiled kernel.  Workspace, stream and error conventions as for qgemm; a call on a
- * capturing stream that has no workspace yet takes the streaming kernel. */
+ * uses an LDS-staged tiled kernel.  Workspace, stream and error conventions as for qgemm, but the tiled
+ * kernel does without a workspace where none is to be had (a capturing stream that has none yet, no memory): it
+ * leaves K whole. */
 QG_API int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const void* scales,
              const uint8_t* zeros, qg_wtype t, int out_dtype, int scale_dtype, int64_t group,
              int64_t M, int64_t N, int64_t K, void* C, void* stream);

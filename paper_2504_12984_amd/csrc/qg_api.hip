@@ -158,20 +158,6 @@ static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t 
   return QG_OK;
 }
 
-// Whether get_workspace can answer without an allocation that a stream capture forbids.
-static bool can_have_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t st) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  {
-    std::lock_guard<std::mutex> lock(g_ws_mutex);
-    for (int i = 0; i < g_ws_used; ++i)
-      if (g_ws[i].dev == dev && g_ws[i].stream == st && g_ws[i].partial_bytes >= partial_bytes && g_ws[i].ticket_count >= ticket_count) return true;
-    if (g_ws_used == 32) return false;
-  }
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-}
-
 // qgemm_noalloc: the same workspace as one fixed array in device memory, part of the code
 // object (zero when it is loaded), one copy per GPU.  Its address on a device is looked up
 // once, with that device current, and kept; host code never uses the array's name otherwise.
@@ -819,8 +805,8 @@ static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bit
   return tiled < blocks;
 }
 
-// The tiled int8 kernel over all rows; `corr`: zero-points, or uintk codes.
-// QG_EUNSUPPORTED: needs a workspace and cannot have one (nothing was enqueued).
+// The tiled int8 kernel over all rows; `corr`: zero-points, or uintk codes.  K stays whole where it would be split but
+// no workspace is to be had.  QG_EUNSUPPORTED, with nothing enqueued: not even 128 rows of A fit its offsets.
 static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipStream_t st) {
   const int64_t most = ((int64_t(1) << 31) - 1) / p.K / 128 * 128;      // rows per launch: A's byte offsets stay below 2^31
   if (most < 128) return QG_EUNSUPPORTED;
@@ -832,11 +818,8 @@ static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipSt
     q.M = (int)std::min(most, M - r0);
     plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &q.splitk, &q.chunks_per_split);
     const int64_t tiles = (int64_t)((q.M + 127) / 128) * ((q.N + 255) / 256);
-    const size_t part_bytes = q.splitk > 1 ? (size_t)q.splitk * tiles * (128 * 256 * sizeof(float)) : 0;
-    if (part_bytes) {
-      if (!can_have_workspace(part_bytes, (size_t)tiles * 4, st)) return QG_EUNSUPPORTED;      // (the same answer for every block)
-      int rc = get_workspace(part_bytes, (size_t)tiles * 4, st, &q.ws, &q.tickets);
-      if (rc != QG_OK) return r0 == 0 ? QG_EUNSUPPORTED : rc;
+    if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (128 * 256 * sizeof(float)), (size_t)tiles * 4, st, &q.ws, &q.tickets) != QG_OK) {
+      q.splitk = 1; q.chunks_per_split = q.K / TILE_K;
     }
     const int rc = kA8Large[bits - 1](q, corr, st);
     if (rc != QG_OK) return rc;
@@ -880,7 +863,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
   if (!set_group_index(p)) return QG_EUNSUPPORTED;
   if (plan_a8_path(M, N, K, group, t.bits)) {
     const int rc = run_a8_tiled(p, M, zeros || t.kind == QG_UINT, t.bits, st);
-    if (rc != QG_EUNSUPPORTED) return rc;                 // no workspace to be had: blocks of 64 rows need none
+    if (rc != QG_EUNSUPPORTED) return rc;
   }
   for (int64_t r0 = 0; r0 < M; r0 += 64) {
     A8Params q = p;

@@ -76,6 +76,21 @@ def test_no_workspace_is_made_on_a_capturing_stream(stub):
         assert c["rc"] == 0 and c["malloc"] == [] and c["memset"] == [] and c["launches"], c
 
 
+@pytest.mark.parametrize("state", ["stub.stub_set(1, 0, 0)", "stub.stub_set(0, 1, 0)", "stub.stub_set(0, 1, 1)\nstub.stub_set(1, 0, 1)",
+                                   "[linear(16, 8192, 2048, stream=16 * i + 160) for i in range(32)]"],
+                         ids=["no_memory", "capture", "unanswered_query", "all_pairs_taken"])
+def test_int8_calls_that_would_split_k_do_without_a_workspace(stub, state):
+    # the tiled kernel alone, unsplit (the fourth template argument), whatever the blocks of 64 rows would have needed
+    calls = _run(stub, state + "\nout = [a8(M, K, N, group=64) for M, K, N in ((1000, 8192, 2048), (300, 8192, 4096), (131200, 16384, 512))]")
+    for c in calls:
+        assert c["rc"] == 0 and c["memset"] == [] and set(_kernels(c)) == {"a8_large_kernel"}, c
+        assert all("ELb0ELb0ELb1E" in name for _, name, _, _ in c["launches"]), c
+    assert len(calls[2]["launches"]) == 2                     # two blocks of rows, the last one short
+    calls = _run(stub, "out = [a8(M, K, N, group=64) for M, K, N in ((1000, 8192, 2048), (300, 8192, 4096))]")
+    for c in calls:                                           # and split where a workspace is there
+        assert c["rc"] == 0 and all("ELb0ELb1ELb1E" in name for _, name, _, _ in c["launches"]), c
+
+
 def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
     # more tiles than a workspace has counters for, and more with every call: nothing to allocate
     calls = _run(stub, "out = [a8(200, 8192, 2048)] + [a8(M, 8192, 28672) for M in (1000, 4700, 4900, 9000)] + [a8(2400, 8192, 57344)]")
