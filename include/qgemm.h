@@ -29,7 +29,7 @@
  *   - the return value is a qg_status (0 = ok, negative = error, nothing was
  *     enqueued); no call throws, none frees caller memory;
  *   - qgemm may use a library-owned workspace for split-K partial sums: one per
- *     (device, stream), of one fixed size (64 MiB + 64 KiB, which covers every
+ *     (device, stream), of one fixed size (36 MiB + 64 KiB, which covers every
  *     shape), allocated by the first call on that pair that splits K (one
  *     hipMalloc and one memset enqueued on the stream; nothing synchronises) and
  *     then never freed, moved or grown, so calls on different streams may overlap
@@ -168,7 +168,7 @@ QG_API int qgemm(const void* A, const void* packed_W, const void* scales, const 
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels,
  * same plan and therefore the same bits as qgemm, but the split-K partial sums and
  * arrival counters live in ONE fixed array in device memory that is part of the loaded
- * library (64 MiB + 64 KiB per GPU, held until the process ends); the call allocates
+ * library (36 MiB + 64 KiB per GPU, held until the process ends); the call allocates
  * nothing, frees nothing and does not synchronise.
  *   - The first call on a device with valid shapes -- M = 0 will do, all pointers may then
  *     be NULL -- looks the array's address up on that device and keeps it (the HIP runtime
@@ -180,7 +180,8 @@ QG_API int qgemm(const void* A, const void* packed_W, const void* scales, const 
  *     with each other) race on it and give wrong sums.  Issue them on one stream, or
  *     order the streams, or use qgemm (one workspace per stream) for the overlapping ones.
  *   - Nothing needs to be cleared between calls: a call reads back only partial sums it
- *     wrote itself, and each arrival counter is returned to zero by the kernel that used it.
+ *     wrote itself, and every arrival counter and every slot in which two partial sums meet
+ *     is returned to zero by the kernel that used it.
  *   - A request beyond the array (only a forced split factor, see qgemm_tuning.h, can
  *     make one) is refused with QG_EUNSUPPORTED and qg_last_error() says how much was
  *     asked for; nothing is enqueued.  Other errors as for qgemm. */

@@ -27,6 +27,7 @@ QG_FOR_ALL_WT(QG_DECL)
 #undef QG_DECL
 int large_launch_wt14(const GemmParams&, int, int, hipStream_t);
 int launch_reduce_tiles(const GemmParams&, int, int, hipStream_t);
+int launch_clear(void*, size_t, hipStream_t);
 // codebook indices of 1..8 bits: kernel-side weight types WT_LUT0 .. WT_LUT0 + 7
 #define QG_FOR_ALL_LUT(X) X(15) X(16) X(17) X(18) X(19) X(20) X(21) X(22)
 #define QG_DECL(i)                                                            \
@@ -99,9 +100,10 @@ static int hip_fail(hipError_t e, const char* what) {
 // this one capacity; only forced split factors (the experiment knobs) can exceed it.
 constexpr size_t WS_PARTIAL_BYTES = size_t(32) << 20;
 constexpr size_t WS_TICKETS = 16384;
-// Behind them, as large as the partial sums: the slots in which the streaming kernel's slabs meet (zero between calls,
-// so they cannot share memory with sums that stay behind).
-constexpr size_t WS_BYTES = WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned) + WS_PARTIAL_BYTES;
+// Behind them the slots in which the streaming kernel's slabs meet (up to two row tiles: 8 KiB per strip and
+// slab), zero between calls, so that they cannot share memory with sums that stay behind.
+constexpr size_t WS_SLOT_BYTES = size_t(4) << 20;
+constexpr size_t WS_BYTES = WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned) + WS_SLOT_BYTES;
 
 // qgemm: one workspace per device and stream.  Kernels of one stream run in order, so they
 // can share a workspace; kernels of different streams may overlap, so each stream gets its
@@ -144,7 +146,7 @@ static int get_workspace(size_t partial_bytes, size_t ticket_count, hipStream_t 
     const size_t pb = partial_bytes < WS_PARTIAL_BYTES ? WS_PARTIAL_BYTES : ((partial_bytes + 255) & ~size_t(255));
     const size_t tc = ticket_count < WS_TICKETS ? WS_TICKETS : ticket_count;
     unsigned char* block = nullptr;
-    const size_t cleared = ((tc * sizeof(unsigned) + 255) & ~size_t(255)) + pb;
+    const size_t cleared = ((tc * sizeof(unsigned) + 255) & ~size_t(255)) + WS_SLOT_BYTES;
     e = hipMalloc(&block, pb + cleared);
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(workspace)");
     // counters and slots start at zero; every kernel that uses them leaves them at zero
@@ -204,6 +206,15 @@ enum WsMode { WS_PER_STREAM = 0, WS_STATIC = 1 };
 static int acquire_ws(int mode, size_t partial_bytes, size_t ticket_count, hipStream_t st, GemmParams& p) {
   return mode == WS_STATIC ? get_static_scratch(partial_bytes, ticket_count, &p.ws, &p.tickets, &p.slots)
                            : get_workspace(partial_bytes, ticket_count, st, &p.ws, &p.tickets, &p.slots);
+}
+
+// Slots for a streaming kernel's exchange, in a workspace acquired for the partial sums of all its slabs.  More
+// than the workspace has (a forced split factor) lie where the partial sums would, cleared ahead of the kernel.
+static int exchange_slots(int splitk, int strips, int row_tiles, float* partial, hipStream_t st, void** slots) {
+  const size_t bytes = (size_t)(splitk - 1) * strips * (size_t)(row_tiles * 16 * TILE_N) * sizeof(float);
+  if (row_tiles > 2 || bytes <= WS_SLOT_BYTES) return QG_OK;
+  *slots = partial;
+  return launch_clear(partial, bytes, st);
 }
 
 // ---- buffer of the de-quantise-first path (forced path 4) -------------------------------------
@@ -382,6 +393,7 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
     const int NCH = p.N / TILE_N;
     size_t pbytes = (size_t)p.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float);
     int rc = acquire_ws(ws_mode, pbytes, (size_t)NCH, st, p);
+    if (rc == QG_OK) rc = exchange_slots(p.splitk, NCH, mt, p.ws, st, &p.slots);
     if (rc != QG_OK) return rc;
   }
   return wt_is_lut(wt) ? kDecodeLut[wt - WT_LUT0](p, route, variant, st) : kDecode[wt](p, route, variant, st);
@@ -878,6 +890,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
       const int NCH = q.N / TILE_N;
       float* ws = nullptr; unsigned* tk = nullptr;
       int rc = get_workspace((size_t)q.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float), (size_t)NCH, st, &ws, &tk, &q.slots);
+      if (rc == QG_OK) rc = exchange_slots(q.splitk, NCH, mt, ws, st, &q.slots);
       if (rc != QG_OK) return rc;
       q.ws = ws; q.tickets = tk;
     }

@@ -64,4 +64,17 @@ int launch_reduce_tiles(const GemmParams& p, int route, int bm, hipStream_t st) 
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
+// Memory to zero by a kernel: a memset does not go into a captured graph.
+__global__ __launch_bounds__(256) void clear_kernel(u4_t* __restrict__ dst, int64_t pieces) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < pieces) dst[i] = (u4_t){0, 0, 0, 0};
+}
+
+// bytes: a multiple of 16
+int launch_clear(void* dst, size_t bytes, hipStream_t st) {
+  const int64_t pieces = (int64_t)(bytes / 16);
+  hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, static_cast<u4_t*>(dst), pieces);
+  return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
+}
+
 }  // namespace qg

@@ -6,6 +6,10 @@ Bound: with the integers t of a chunk (min(group, 128) rows) exact, one fp32 rou
 row scale, |C - ref| <= u |ref| + (chunks + 1) 2^-24 a_scale sum |s t|, u = 2^-11 (fp16) or 2^-8 (bf16) for the
 rounding to the output type (and 2^-24 for fp16 results below its normal range).  Where every code is
 its zero-point the result is zero."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -17,6 +21,7 @@ from test_gpu_a8 import A8Case, _case, _reset_knobs, I, U  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 M, K, N = 130, 8192, 256
 
 
@@ -137,3 +142,40 @@ def test_scales_at_the_ends_of_their_range(bits, zero):
     assert (want[:, 0][fin[:, 0]] != 0).any() and (want[:, 1] != 0).any()
     # two chunks, each rounded once in fp32, and one step of bf16 (2^-133 below its normal range)
     assert ((got - want).abs()[fin] <= 2.0 ** -7 * want.abs()[fin] + 2.0 ** -133).all()
+
+
+CAPTURE = """
+import torch
+from paper_2504_12984_amd import binding as B
+M, K, N = 300, 8192, 2048
+g = torch.Generator().manual_seed(1)
+codes = torch.randint(0, 16, (K, N), dtype=torch.uint8, generator=g).cuda()
+t = B.WType(B.QG_UINT, 4)
+packed = B.repack(B.qg_pack_codes(codes, 4), t, K, N, layout=B.QG_LAYOUT_TILE128x64_I8)
+A = torch.randint(-128, 128, (M, K), dtype=torch.int8, generator=g).cuda()
+scales, out = torch.full((K // 128, N), 0.01, dtype=torch.float16, device="cuda"), torch.zeros(M, N, dtype=torch.float16, device="cuda")
+call = lambda: B.qgemm_a8(A, None, packed, scales, None, t, 128, N, out=out)
+want = (A.cpu().float() @ codes.cpu().float()) * scales[0, 0].item()
+torch.cuda.synchronize()
+side = torch.cuda.Stream()                            # nothing has run on it: no workspace
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=side):
+    call()
+def check():
+    torch.cuda.synchronize()
+    assert ((out.cpu().float() - want).abs() <= 1e-2 + 5e-3 * want.abs()).all()
+for _ in range(3):
+    out.zero_()
+    graph.replay()
+    check()
+    out.zero_()
+    with torch.cuda.stream(side):
+        call()                                        # eager, split: makes the workspace
+    check()
+print("captured")
+"""
+
+
+def test_capture_of_a_call_that_would_split_k_on_a_stream_without_a_workspace():
+    r = subprocess.run([sys.executable, "-c", CAPTURE], capture_output=True, text=True, timeout=100, cwd=ROOT)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stderr[-2000:]

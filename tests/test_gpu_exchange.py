@@ -32,6 +32,26 @@ def test_every_arrangement_and_number_of_slabs(M, variants):
             assert np.array_equal(bits_of(first), bits_of(P.gpu_c())), (variant, splitk)
 
 
+def test_more_slots_than_the_workspace_has():
+    # forced slabs: slots where the partial sums of other calls lie, cleared ahead of the kernel
+    from paper_2504_12984_amd import binding as B
+    P = Prepared(WL.Case("tree_many", 32, 2048, 8192, WL.KIND_UINT, 4, group=128, zero=8, seed=54050))
+    Q = Prepared(WL.Case("tree_few", 16, 8192, 512, WL.KIND_UINT, 4, group=128, zero=8, seed=54051))
+    R = Prepared(WL.Case("tree_tiles", 200, 8192, 512, WL.KIND_UINT, 4, group=128, zero=8, seed=54052))      # leaves partial sums behind
+    a8 = A8Case(_case("a8_tree_many", 32, 2048, 8192, WL.KIND_UINT, 4, 128, zero=8, seed=54053))
+    others = [bits_of(Q.gpu_c()), bits_of(R.gpu_c())]
+    out = torch.empty(32, 8192, dtype=torch.float16, device="cuda")
+    for splitk in (5, 16):
+        _knobs(0, splitk)
+        _check(P, P.gpu_c(), f"{splitk} slabs")
+        assert_c_close(a8.gpu(), a8.ref(), a8.case.name)
+        B.qgemm_noalloc(P.d_A, P.d_packed, P.d_scales, P.d_zeros, P.wtype, 128, 8192, out)
+        assert np.array_equal(bits_of(out), bits_of(P.gpu_c()))
+        _knobs(0, 0)
+        for X, want in zip((Q, R), others):
+            assert np.array_equal(bits_of(X.gpu_c()), want)
+
+
 def test_automatic_splits_and_other_shapes_in_between():
     cases = [Prepared(WL.Case(f"tree_auto_{i}", M, K, N, WL.KIND_INT, b, group=128, zero=None, seed=54100 + i))
              for i, (M, K, N, b) in enumerate([(1, 4096, 512, 3), (16, 8192, 128, 4), (5, 2048, 1024, 8), (32, 4096, 192, 4), (64, 4096, 512, 4)])]

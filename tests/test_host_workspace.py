@@ -91,6 +91,24 @@ def test_int8_calls_that_would_split_k_do_without_a_workspace(stub, state):
         assert c["rc"] == 0 and all("ELb0ELb1ELb1E" in name for _, name, _, _ in c["launches"]), c
 
 
+def test_workspace_sizes(stub):
+    # partial sums, counters, and slots for what the automatic plans split: fewer than 512 strips x slabs of 8 KiB
+    size, cleared = (36 << 20) + 65536, (4 << 20) + 65536
+    loaded, first, second = _run(stub, "out = [LOADED, linear(16, 8192, 2048), linear(32, 8192, 2048, entry=lib.qgemm_noalloc)]")
+    assert [int(s.split()[2]) for s in loaded if "scratch" in s] == [size]
+    assert first["malloc"] == [size] and first["memset"] == [cleared] and second["malloc"] == []
+    most = max(c["launches"][0][2] * (c["launches"][0][3] - 1) for c in _run(
+        stub, "out = [f(M, K, 64 * n) for f in (linear, a8) for M in (1, 17) for K in (2048, 4096, 8192, 16384) for n in (1, 8, 31, 63, 64, 127, 128, 129, 191, 255, 256)]"))
+    assert 128 <= most < 512
+
+
+@pytest.mark.parametrize("entry", ["lib.qgemm", "lib.qgemm_noalloc"])
+def test_forced_slabs_beyond_the_slots_are_cleared_ahead_of_the_kernel(stub, entry):
+    calls = _run(stub, "lib.qg_set_knob(1, 8)\nout = [linear(M, 8192, N, entry=%s) for M, N in ((16, 8192), (16, 16384), (32, 8192), (48, 16384))]" % entry)
+    assert [_kernels(c) for c in calls] == [["decode_kernel"], ["clear_kernel", "decode_kernel"], ["clear_kernel", "decode_kernel"], ["decode_kernel"]]
+    assert calls[1]["launches"][0][2] == 7 * 256 * 4096 // 16 // 256 and all(c["rc"] == 0 for c in calls)
+
+
 def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
     # more tiles than a workspace has counters for, and more with every call: nothing to allocate
     calls = _run(stub, "out = [a8(200, 8192, 2048)] + [a8(M, 8192, 28672) for M in (1000, 4700, 4900, 9000)] + [a8(2400, 8192, 57344)]")
