@@ -16,6 +16,7 @@
 // Compiled once per weight type (QG_WT).
 #include "qg_decode.h"
 #include "qg_static_for.h"
+#include "qg_wait.h"
 
 #ifndef QG_WT
 #error "compile with -DQG_WT=<weight type index>"
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
   // its own 64-column strip of the tile by itself and first draws a ticket (low half of the strip's counter).
   // All but the last to draw store their partial strip, wait for it, count it as done (high
   // half) and leave.  The last one keeps its own sums in registers, waits until the others are done --
-  // they have left their main loops and wait for nothing, so that wait ends -- and adds the
+  // they have left their main loops and wait for nothing, and the wait has an end of its own -- and adds the
   // slabs in slab order, its own at its place: the result does not depend on arrival order.
   if constexpr (BM <= 128) {
     if (p.splitk > 1) {
@@ -495,8 +496,8 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
         if (l == 0) __hip_atomic_fetch_add(ticket, 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
       }
-      while ((__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) != (unsigned)(p.splitk - 1))
-        __builtin_amdgcn_s_sleep(1);
+      (void)wait_for([&] { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 16; },
+                     (unsigned)(p.splitk - 1), [] { __builtin_amdgcn_s_sleep(1); });
       asm volatile("" ::: "memory");                              // no slab is read ahead of the count
       if (l == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
       // the other slabs in slab order (S of them), the loads of R row tiles in flight
