@@ -1,7 +1,6 @@
 """The tiled int8-activation kernel (qgemm_a8 on many rows) against the oracle's int8 leg, at the
 edges of its tiles: row counts around 128, strips that leave wavefronts idle, one to several chunks,
-every code width and scale group, forced K-slabs, sums at the ends of their range, and more rows
-than one launch's row sums hold.  Tolerance as for every int8 case (see test_gpu_a8.py); the
+every code width and scale group, forced K-slabs, sums at the ends of their range, and many groups.  Tolerance as for every int8 case (see test_gpu_a8.py); the
 one-hot test there runs this kernel too (256 rows)."""
 import numpy as np
 import pytest
@@ -53,7 +52,7 @@ def test_sums_at_the_ends_of_their_range(bits, a, code, zero):
 
 
 def test_more_rows_than_one_launch_takes():
-    # 1024 groups: 2048 rows of row sums fill half of the workspace, the last rows are a second launch
+    # 1024 groups; one launch here (test_gpu_a8_zero_points.py has a test of the same name that needs two)
     case = _case("a8l_blocks", 2051, 65536, 64, U, 2, 64, seed=41300)
     P = A8Case(case)
     rows = np.array([0, 1, 2046, 2047, 2048, 2049, 2050])

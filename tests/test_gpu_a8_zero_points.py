@@ -179,3 +179,31 @@ print("captured")
 def test_capture_of_a_call_that_would_split_k_on_a_stream_without_a_workspace():
     r = subprocess.run([sys.executable, "-c", CAPTURE], capture_output=True, text=True, timeout=100, cwd=ROOT)
     assert r.returncode == 0 and "captured" in r.stdout, r.stderr[-2000:]
+
+
+def test_more_rows_than_one_launch_takes():
+    # K = 2^23: 128 rows of A to a launch (32-bit offsets), the last two are a second one; uint1 against the sum of A's
+    # bytes where the code is set, in int64 on the GPU
+    from paper_2504_12984_amd import binding as B
+    M, K, N = 130, 1 << 23, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(43000)
+    A = torch.randint(-128, 128, (M, K), dtype=torch.int8, device="cuda", generator=gen)
+    codes = torch.randint(0, 2, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    t = B.WType(B.QG_UINT, 1)
+    packed = B.repack(B.qg_pack_codes(codes, 1), t, K, N, layout=B.QG_LAYOUT_TILE128x64_I8)
+    scales = torch.full((1, N), 2.0 ** -10, dtype=torch.bfloat16, device="cuda")
+    B.qg_set_knob(0, 2)
+    got = B.qgemm_a8(A, None, packed, scales, None, t, K, N, out_dtype=torch.bfloat16).double()
+    want, size = torch.zeros(M, N, device="cuda", dtype=torch.float64), torch.zeros(M, N, device="cuda", dtype=torch.float64)
+    rows = [0, 1, 127, 128, 129]
+    for m in rows:
+        for n in (0, 17, 63):
+            x = torch.where(codes[:, n] != 0, A[m], torch.zeros_like(A[m]))
+            want[m, n] = x.sum(dtype=torch.int64)
+            size[m, n] = x.view(-1, 128).sum(1, dtype=torch.int64).abs().sum()
+    bound = 2.0 ** -10 * (2.0 ** -8 * want.abs() + (K // 128 + 1) * 2.0 ** -24 * size)
+    cols = torch.tensor([0, 17, 63], device="cuda")
+    rows = torch.tensor(rows, device="cuda")
+    pick = lambda x: x[rows][:, cols]      # noqa: E731
+    assert (pick((got - want * 2.0 ** -10).abs()) <= pick(bound)).all()
