@@ -38,8 +38,8 @@
  *     destroyed and whose handle value is re-used simply inherits the workspace.
  *     hipStreamPerThread is refused (QG_EINVAL): the one handle value names a
  *     different stream in every thread.  Calls may be captured into a HIP graph
- *     once a call that splits K has run eagerly on the capture stream (so that
- *     nothing is allocated during the capture); every launch leaves counters and
+ *     once a call that splits K has run eagerly on the capture stream (nothing is
+ *     allocated during a capture: QG_EHIP without that call); every launch leaves counters and
  *     workspace ready for the next, so a graph can be replayed any number of
  *     times.  qgemm_noalloc is the same call with no allocation at all.
  *
@@ -155,7 +155,7 @@ QG_API int qdequant(const void* packed_W, const void* scales, const uint8_t* zer
 /* C[M,N] (row-major, `act`) = A[M,K] (row-major, `act`) . dequant(W).
  * Arguments as for qdequant; M >= 1 is arbitrary, C is overwritten.
  * Path choice (by shape) is internal: M <= 64 streams the weights once through
- * a split-K kernel (1, 2 or 4 tiles of 16 rows per wavefront); larger M -- and
+ * a split-K kernel (1 to 4 tiles of 16 rows per wavefront); larger M -- and
  * 33 <= M <= 64 on all but small problems -- use the LDS-staged tiled kernel, which also splits K (partial sums meet in a
  * workspace the library allocates on first use) when its 64- or
  * 128-row tiles would leave most CUs idle.  The tiled kernel needs M*K*2, the packed

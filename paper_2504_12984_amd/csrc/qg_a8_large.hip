@@ -6,9 +6,10 @@
 // through LDS, each wavefront's own codes and scales pass through LDS as well: everything is loaded
 // straight into LDS by the memory pipe, which takes no registers -- 128 accumulators, the unpacked chunk
 // and the sums in flight fill the 256 that leave two workgroups on a CU.
-// What bounds the kernel is issue: per 16x16x64 instruction and scale group two vector operations
-// per result value (two wavefronts per SIMD: an instruction every 17 clocks alone, every 25 with four
-// vector operations beside it, every 33 with six).  So the rest is kept out of the loop:
+// What bounds the kernel most is issue (counters: vector instructions take up to 0.67 of a busy CU's clocks, the
+// matrix pipe 0.4 to 0.45): per 16x16x64 instruction and scale group two vector operations per result
+// value (two wavefronts per SIMD: an instruction every 17 clocks alone, every 25 with four vector
+// operations beside it, every 33 with six).  So the rest is kept out of the loop:
 //   * Codes enter the instruction as signed bytes, times a power of two.  The sums of a chunk stay within 2^22 and
 //     start from the bits of a float, so they are read as fp32 without a convert and without the factor.
 //   * No zero-points (CORR = false): the byte is (q - 2^(b-1)) * 2^(8-b), one shift and one three-input

@@ -410,8 +410,8 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
-// hardware convert) + 1.2 per slab (the last arriver of a tile reads the slabs back one
-// pair after the other).
+// hardware convert) + 1.2 per slab.  That fit is older than the kernel's present exchange: the 1.2 is what reading
+// the slabs back one pair after the other cost, where up to LARGE_MEET slabs now meet and more have a second kernel.
 static double tiled_cost(int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
   const int over = t.bits > 4 ? t.bits - 4 : 0;
   const bool hw_convert = (t.bits == 4 || t.bits == 6 || t.bits == 8);      // e2m1, e3m2, e4m3

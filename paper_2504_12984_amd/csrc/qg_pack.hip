@@ -4,7 +4,7 @@
 //   repack_kernel     : canonical [K,N] stream -> tiled device layout
 //                       (paper, Section "Efficient Low-Precision Weight Loading",
 //                       the "Change Layout" pre-processing step)
-// Both are bound by memory: a weight passes through each once when a model is loaded.
+// A weight passes through each once when a model is loaded.
 #include "qg_common.h"
 #include "qg_static_for.h"
 
@@ -27,8 +27,8 @@ __device__ __forceinline__ uint32_t squeeze4(uint32_t x) {
 
 // 32 consecutive codes fill exactly BITS dwords.  A thread squeezes 32 codes (two 16-byte loads)
 // and a workgroup meets in LDS so that the stream leaves in 16-byte stores of whole cache lines.
-// Bound by memory: on K = 8192, N = 28672 the codes of 5 bits take 66 us = 5.7 TB/s read and written
-// (4 bits 60, 8 bits 81; a large device copy moves 5.0 TB/s).  With a thread that gathered eight
+// Bound by memory: on K = 8192, N = 28672 the codes of 5 bits take 68 us = 5.6 TB/s read and written
+// (4 bits 61, 8 bits 79; a device copy of 256 MiB moves 5.4 TB/s, one of 2 GiB 4.9).  With a thread that gathered eight
 // codes byte by byte and stored bytes it was 207 (187, 253) us: byte-wide accesses.
 constexpr int PACK_CODES = 256 * 32;      // codes per workgroup
 template <int BITS>
@@ -93,8 +93,9 @@ enum RepackMode {
 // places the codes at bit positions known at compile time.  The four wavefronts of a workgroup
 // take adjacent strips of the same rows, and workgroups are dealt out so that one XCD gets a run
 // of them: the parts of a cache line that several strips need meet in that XCD's L2.
-// Bound by memory from 4 bits on (K = 8192, N = 28672: 72 us = 4.1 TB/s at 5 bits, 98 us = 4.8 at 8;
-// narrower codes by the number of row windows, which does not shrink with them: 33 us at 1 bit).
+// Bound by the row windows, whose number does not shrink with the codes -- wavefronts wait 0.75 of their time to
+// issue them -- and at 8 bits nearly by memory (K = 8192, N = 28672: 33 us = 1.8 TB/s at 1 bit, 81 us = 3.6 at 5,
+// 97 us = 4.9 at 8; every byte is read and written once).
 // A thread that fetched every code by itself with two byte loads took 389 / 274 / 111 us.
 template <int BITS, int MODE>
 __global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__ canon, uint4* __restrict__ out, int K, int N,
