@@ -406,7 +406,8 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // 128-row tiles, K cut into 1 to 8 slabs of an even number of chunks (the kernel
 // works in pairs of chunks), at most one workgroup per CU when split.  tiled_cost estimates the
 // time in microseconds, fitted to 1300 measurements at K = 1024 .. 28672, N = 2048 .. 28672, M = 24 .. 1000 at
-// 4 bits and 700 at 3, 6 and 8: what it picks takes 0.4 % longer than the best candidate on average, 13 % at most.
+// 4 bits and 700 at 3, 6 and 8.  In a sweep of 120 cases (3, 4, 6, 8 bits, M = 96 .. 1000) what it picks takes 1.1 % longer than
+// the best candidate on average and 11 % at most, noise of the timing included.
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
@@ -496,8 +497,9 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
   // instead; it wins on all but the small problems (K = 8192, N = 28672, M = 64, 6 bits:
   // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).  Up to 48 rows the
   // streaming kernel carries three row tiles (0.92 of that).  The fits predate the second kernel that adds
-  // the slabs: from 49 rows on the tiled kernel would now be up to 18 % shorter on the small problems that stay
-  // here too (K = N = 8192, M = 64: 19.3 in eight slabs against 23.5); the choice is kept as tested.
+  // the slabs: from 49 rows on the tiled kernel would now be up to 21 % shorter on the small problems that stay
+  // here too (K = N = 8192, M = 64: 19.3 in eight slabs against 23.0, M = 56 18.3 against 23.1; K = 14336, N = 4096 6 to
+  // 10 %); the choice is kept as tested.
   if (M > 32 && (double)K * (double)N >= 16.0e6 && knob(1) == 0 &&
       knob(2) == 0 && knob(3) == 0) {
     double tiled = 1e30;
