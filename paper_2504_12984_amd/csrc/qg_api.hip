@@ -99,7 +99,6 @@ static int hip_fail(hipError_t e, const char* what) {
 // while tiles x slabs stay within 256 (at most 128 x 256 fp32 each).  So every workspace has
 // this one capacity; only forced split factors (the experiment knobs) can exceed it.
 constexpr size_t WS_PARTIAL_BYTES = size_t(32) << 20;
-constexpr size_t WS_TICKETS = 16384;
 // Behind them the slots in which the streaming kernel's slabs meet (up to two row tiles: 8 KiB per strip and
 // slab), zero between calls, so that they cannot share memory with sums that stay behind.
 constexpr size_t WS_SLOT_BYTES = size_t(4) << 20;
@@ -201,6 +200,9 @@ static int get_static_scratch(size_t partial_bytes, size_t ticket_count, float**
   *slots = base + WS_PARTIAL_BYTES + WS_TICKETS * sizeof(unsigned);
   return QG_OK;
 }
+
+// Counters of the tiled kernels, one per 64-column strip of a tile.
+static size_t tile_tickets(int64_t tiles) { return (size_t)(4 * tiles * ticket_stride(4 * tiles)); }
 
 enum WsMode { WS_PER_STREAM = 0, WS_STATIC = 1 };
 static int acquire_ws(int mode, size_t partial_bytes, size_t ticket_count, hipStream_t st, GemmParams& p) {
@@ -704,7 +706,7 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
     plan_tiled(M, N, K, t16, &bm, &q.splitk, &q.chunks_per_split);
     if (q.splitk > 1) {
       const int64_t tiles = ((M + bm - 1) / bm) * ((N + 255) / 256);
-      rc = acquire_ws(ws_mode, (size_t)q.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), (size_t)tiles * 4, st, q);
+      rc = acquire_ws(ws_mode, (size_t)q.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, q);
       if (rc != QG_OK) return rc;
     }
     rc = large_launch_wt14(q, route, bm, st);
@@ -731,7 +733,7 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
   plan_tiled(M, N, K, t, &bm, &p.splitk, &p.chunks_per_split);
   if (p.splitk > 1) {
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + 255) / 256);
-    rc = acquire_ws(ws_mode, (size_t)p.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), (size_t)tiles * 4, st, p);   // a ticket per 64-column strip
+    rc = acquire_ws(ws_mode, (size_t)p.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, p);   // a ticket per 64-column strip
     if (rc != QG_OK) return rc;
   }
   rc = wt_is_lut(wt) ? kLargeLut[wt - WT_LUT0](p, route, bm, st) : kLarge[wt](p, route, bm, st);
@@ -832,7 +834,7 @@ static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipSt
     q.M = (int)std::min(most, M - r0);
     plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &q.splitk, &q.chunks_per_split);
     const int64_t tiles = (int64_t)((q.M + 127) / 128) * ((q.N + 255) / 256);
-    if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (128 * 256 * sizeof(float)), (size_t)tiles * 4, st, &q.ws, &q.tickets) != QG_OK) {
+    if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (128 * 256 * sizeof(float)), tile_tickets(tiles), st, &q.ws, &q.tickets) != QG_OK) {
       q.splitk = 1; q.chunks_per_split = q.K / TILE_K;
     }
     const int rc = kA8Large[bits - 1](q, corr, st);

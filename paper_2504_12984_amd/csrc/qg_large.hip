@@ -476,7 +476,7 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
       };
       auto ws_off = [&](int mt) __attribute__((always_inline)) { return m0 + mt * 16 + i16 < p.M ? 16 * tid : AWAY; };
       const bool here = p.splitk <= LARGE_MEET;
-      unsigned* ticket = p.tickets + 4 * tile + w;
+      unsigned* ticket = p.tickets + ticket_stride(4 * tiles) * (4 * tile + w);
       unsigned drawn = 0;
       if (here) {
         if (l == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
