@@ -300,7 +300,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // 33 .. 48 rows carry three row tiles: a quarter less of A to load and of matrix instructions than four
   // (K = N = 8192, M = 40, u4: 17.8 us against 19.8; K = 4096, N = 28672: 25.4 against 28.2)
   const int tens = (M > 32 && M <= 48) ? 30 : 10 * mt;
-  int variant = tens + 1;                     // 4 wavefronts on one strip
+  int variant = tens + 1;                     // one strip: 4 wavefronts, with several row tiles 8
   // One row tile, short K (at most 32 chunks): as many wavefronts per strip as leaves each
   // two chunks -- 16 (every load of the strip in flight at once) up to 4-bit codes, whose
   // ring fits the 128 registers 16 wavefronts leave each; 8 from 16 chunks on; else 4.
@@ -322,8 +322,8 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // long K and enough strips to fill the chip with pairs of them: 8 wavefronts on 2
   // adjacent strips, 4 along K each -- wavefronts at the same K position share
   // their A rows in the vector cache (measured 2-4 % shorter at K = 8192, N = 28672;
-  // with 2 or 4 row tiles: 2 strips x 2 wavefronts along K, 10-15 % shorter)
-  // (with several row tiles also for short K: K = 4096, N = 28672, M = 24: 20.8 us against 22.4)
+  // with several row tiles 2 strips x 4 wavefronts along K, 10-15 % shorter, also for short K: K = 4096,
+  // N = 28672, M = 24: 20.8 us against 22.4)
   if ((KC > 32 || mt > 1) && NCH % 2 == 0 && NCH / 2 >= 192) variant = (mt == 1) ? 14 : tens + 6;
   // up to 6 bits per code a wavefront needs few enough registers for 16 of them per
   // workgroup (2 strips x 8 along K): twice the wavefronts in flight, 1-6 % shorter
@@ -340,16 +340,17 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // wavefronts at 3 bits; 8-bit codes: two strips x 4 wavefronts, 23.5 against 27.3)
   if (variant == 11 && KC > 32 && NCH > 128 && NCH < 256) variant = wt_bits(wt) <= 6 ? 10 : (NCH % 2 == 0 ? 14 : 11);
   if (knob(3) > 0) variant = knob(3);
-  if (group == 32 && !mx) variant = tens + 1;   // four groups per chunk: the 4-wavefront arrangements only
+  if (group == 32 && !mx) variant = tens + 1;   // four groups per chunk: one strip, the fewest wavefronts
   const int waves = kDecodeWaves[wt_is_lut(wt) ? 0 : wt](variant);      // the same map for every type
   // Split K over workgroups only when the column strips alone cannot fill the
   // 256 CUs, and never below 4 chunks per wavefront (2 with 16 wavefronts per strip, or with a
   // short K on at most 128 strips: K = 4096, N = 4096 .. 8192 is 15-25 % shorter with 8
-  // wavefronts and K in two).
+  // wavefronts and K in two; half as many with several row tiles: M = 45, K = N = 4096 10.1 us with one
+  // chunk per wavefront, 10.5 with two).
   int splitk = knob(1);
   if (splitk <= 0) {
     splitk = 1;
-    const int min_chunks = (waves >= 16 || (KC <= 32 && NCH <= 128)) ? 2 : 4;      // per wavefront
+    const int min_chunks = ((waves >= 16 || (KC <= 32 && NCH <= 128)) ? 2 : 4) / (mt > 1 ? 2 : 1);      // per wavefront
     // (several row tiles: 192 workgroups are enough -- K = 4096, N = 14336, M = 24 takes 12.1 us
     // unsplit against 14.7 in two; N = 6144, M = 40: 11.9 in two, 17.2 in four)
     while (NCH * splitk < 256 && !(mt > 1 && NCH * splitk >= 192) && KC / (splitk * 2) >= min_chunks * waves) splitk *= 2;

@@ -13,7 +13,12 @@
 // Codes are unpacked in registers and fed to the 16x16x32 matrix instruction
 // with W as the row operand (the paper's load -> reinterpret -> cast -> mma
 // pipeline, Section "Key Ideas", with no layout conversion and no trip through
-// LDS).  The K reduction runs inside the MFMA (across the four 8-wide k-blocks
+// LDS).  From 13 or 16 rows on A passes through LDS, each wavefront's rows through a part of its own: the matrix
+// instruction wants 16 rows in adjacent lanes, and loads in that order run at 16 bytes per clock and CU (a lane at a
+// time), loads along the rows at 40 to 54.  M = 64, K = N = 8192, u4: 22.9 -> 19.1 us; M = 45 17.9 -> 16.6; M = 16, K = 8192,
+// N = 28672, int4 27.6 -> 26.6, group 64 30.6 -> 28.0.  With fewer rows many lanes of a direct load share an address and the way
+// through LDS costs more than it saves (M = 8 there 24.7 against 25.9).
+// The K reduction runs inside the MFMA (across the four 8-wide k-blocks
 // of lanes), then across the wavefronts through LDS, then -- when K is also
 // split over workgroups -- through a binary tree of pairwise fp32 exchanges (the k-dimension parallelisation the paper names
 // in Section "End-to-End Performance").
@@ -58,8 +63,10 @@ __device__ __forceinline__ uint32_t pack_out(float lo, float hi) {
 
 // MX: the scales are 8-bit exponents, one per 32 rows and column (GPC = 4), applied by the
 // hardware converts of the e2m1 / e4m3 types; there are no zero-points.
-template <int WT, int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS = 1, bool MX = false>
+// A_LDS: A through LDS (always with several row tiles); else loaded as the matrix instruction reads it.
+template <int WT, int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS, bool MX, bool A_LDS>
 __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
+  static_assert(A_LDS || MT == 1, "several row tiles go through LDS");
   // NS adjacent strips per workgroup, NK wavefronts along K for each: wavefront w
   // works on strip w % NS and takes every NK-th chunk of the slab starting at
   // w / NS, so the NS wavefronts with the same w / NS walk the same K range at the
@@ -81,31 +88,61 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
   const int n0 = TILE_N * nc + 4 * i16;
 
   const uint4* wstrip = reinterpret_cast<const uint4*>(p.W + (int64_t)nc * KC * (1024 * BITS)) + l;
-  // MT tiles of 16 rows; rows past M re-read row M-1, their results are never stored
-  const uint16_t* arow[MT];
+  // MT tiles of 16 rows; rows past M re-read row M-1, their results are never stored.
+  // Through LDS: a load takes four rows x 256 bytes (buffer offsets below 2^31: 64 rows, K <= 2^24); eight lanes fill
+  // 128 bytes of LDS.  A wavefront's slab is [k-step][row][4 pieces], piece q of row r at slot q ^ swizzle(r), so that
+  // both the writes and the fragment reads find their banks apart.
+  const uint16_t* arow = p.A + (int64_t)min(i16, p.M - 1) * p.K + 8 * b;
+  const int apc = (l & 3) + 4 * ((l >> 3) & 3), ar4 = ((l >> 2) & 1) + 2 * (l >> 5);      // my piece of a row, my row of four
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.A), 0, (int)((uint32_t)p.M * (uint32_t)(2 * p.K)), 0x00020000);
+  auto swizzle = [](int r) __attribute__((always_inline)) { return (((r >> 2) & 1) << 1) | (((r >> 1) ^ (r >> 3)) & 1); };
+  constexpr int AQ = A_LDS ? 4 * MT : 1;                     // loads of a chunk's rows
+  uint32_t a_off[AQ];
+  int a_wr[4];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) arow[mt] = p.A + (int64_t)min(mt * 16 + i16, p.M - 1) * p.K + 8 * b;
+  for (int q = 0; q < AQ; ++q) a_off[q] = (uint32_t)min(4 * q + ar4, p.M - 1) * (uint32_t)(2 * p.K) + 16u * apc;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) a_wr[q] = (apc >> 2) * (MT * 1024) + (4 * q + ar4) * 64 + 16 * ((apc & 3) ^ swizzle(4 * q + ar4));
+  const int a_rd = i16 * 64 + 16 * (b ^ swizzle(i16));
   // no zero-points: read (valid) scale bytes instead and mask them away
   const uint8_t* zbase = p.Z ? p.Z : reinterpret_cast<const uint8_t*>(p.S);
   const uint32_t zmask = p.Z ? 0xffffffffu : 0u;
 
+  // LDS: for codebook indices the replicated lookup table (built by all wavefronts while the first loads are in
+  // flight), then a part for each wavefront: its rows of A during the main loop, its sums after it
+  constexpr int LUT_BYTES = [] { if constexpr (D::IS_LUT) return D::TABLE_DWORDS * 4; else return 0; }();
+  __shared__ __attribute__((aligned(16))) unsigned char lds_raw[LUT_BYTES + NW * MT * 4096];
+  unsigned char* my_a = lds_raw + LUT_BYTES + w * (MT * 4096);
+
+  // A in registers: as fragments two chunks like the weights; on its way to LDS two chunks with 16 wavefronts, else
+  // one, loaded again as soon as it is in LDS (M = 16, K = 8192, N = 57344, u4, 16 wavefronts: 51.5 against 53.4 us;
+  // eight with two chunks take more than the 128 registers that leave two workgroups on a CU: K = 8192,
+  // N = 14336 19.6 against 16.6 us)
+  constexpr int A_RING = !A_LDS || (NW == 16 && GPC == 1) ? DEPTH : 1;
   struct Stage {
     uint32_t r[RAW];
-    u4_t a[MT][4];
     uint2 s[GPC];          // GPC groups per chunk (group size 128 or more: 1; 64: 2; 32: 4)
     uint32_t z[GPC];
   };
   Stage st[DEPTH];
+  u4_t ar[A_RING][4 * MT];
 
+  auto issue_a = [&](auto Sc, int c) __attribute__((always_inline)) {
+    constexpr int R = decltype(Sc)::value % A_RING;
+    if constexpr (A_LDS) {
+#pragma unroll
+      for (int q = 0; q < AQ; ++q) ar[R][q] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_off[q], c * (2 * TILE_K), 0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ar[R][j] = *reinterpret_cast<const u4_t*>(arow + c * TILE_K + 32 * j);
+    }
+  };
   auto issue = [&](auto Sc, int c) __attribute__((always_inline)) {
     constexpr int S = decltype(Sc)::value;
     Stage& s = st[S];
     __builtin_amdgcn_sched_barrier(0);         // stay below the last use of the entry being refilled,
                                                // so that the refill reuses the same registers
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s.a[mt][j] = *reinterpret_cast<const u4_t*>(arow[mt] + c * TILE_K + 32 * j);
+    if constexpr (A_RING == DEPTH) issue_a(Sc, c);
     const uint4* src = wstrip + (int64_t)c * (64 * BITS);
 #pragma unroll
     for (int i = 0; i < BITS; ++i) {
@@ -142,13 +179,35 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
 
   typename D::Uniform u;
   u.init();
-  auto compute = [&](auto Sc) __attribute__((always_inline)) {
+  // `next`: the chunk after this one, or none (-1)
+  auto compute = [&](auto Sc, int next) __attribute__((always_inline)) {
     constexpr int S = decltype(Sc)::value;
     Stage& s = st[S];
+    u4_t af[2][MT];                // fragments of this k-step and the next
+    if constexpr (A_LDS) {
+#pragma unroll
+      for (int q = 0; q < 4 * MT; ++q) *reinterpret_cast<u4_t*>(my_a + a_wr[q & 3] + (q >> 2) * 1024) = ar[S % A_RING][q];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the lanes of a wavefront exchange rows: writes stay ahead of the reads
+      if constexpr (A_RING == 1) {
+        if (next >= 0) issue_a(Sc, next);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    auto fragments = [&](auto Jc) __attribute__((always_inline)) {
+      constexpr int J = decltype(Jc)::value;
+      if constexpr (J < 4)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          if constexpr (A_LDS) af[J & 1][mt] = *reinterpret_cast<const u4_t*>(my_a + a_rd + J * (MT * 1024) + mt * 1024);
+          else af[J & 1][mt] = ar[S % A_RING][J];
+        }
+    };
+    fragments(std::integral_constant<int, 0>{});
     if constexpr (MX) {
       static_assert(GPC == 4, "one scale block per k-step");
       static_for<4>([&](auto Jc) __attribute__((always_inline)) {
         constexpr int J = decltype(Jc)::value;
+        fragments(std::integral_constant<int, J + 1>{});
         MxConsts mx;
         mx.make(s.z[J]);
         static_for<4>([&](auto NTc) __attribute__((always_inline)) {
@@ -157,7 +216,7 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
           frag_mx<WT, ROUTE == ROUTE_BF16, J, NT>(s.r, mx, o);
           const u4_t wf = {o[0], o[1], o[2], o[3]};
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][NT] = mfma16<ROUTE>(wf, s.a[mt][J], acc[mt][NT]);
+          for (int mt = 0; mt < MT; ++mt) acc[mt][NT] = mfma16<ROUTE>(wf, af[J & 1][mt], acc[mt][NT]);
         });
       });
       return;
@@ -167,34 +226,31 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     for (int g = 0; g < GPC; ++g) D::make_consts(gc[g], s.s[g], D::IS_LUT ? 0u : (s.z[g] & zmask), p.zbias, p.scale_bf16);
     static_for<4>([&](auto Jc) __attribute__((always_inline)) {
       constexpr int J = decltype(Jc)::value;
+      fragments(std::integral_constant<int, J + 1>{});
       static_for<4>([&](auto NTc) __attribute__((always_inline)) {
         constexpr int NT = decltype(NTc)::value;
         uint32_t o[4];
         D::template frag<J, NT>(s.r, gc[J * GPC / 4], u, o);          // k-step J lies in group J*GPC/4 of the chunk
         const u4_t wf = {o[0], o[1], o[2], o[3]};      // unpacked once, used by every row tile
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt][NT] = mfma16<ROUTE>(wf, s.a[mt][J], acc[mt][NT]);
+        for (int mt = 0; mt < MT; ++mt) acc[mt][NT] = mfma16<ROUTE>(wf, af[J & 1][mt], acc[mt][NT]);
       });
     });
   };
 
   auto chunk_of = [&](int i) __attribute__((always_inline)) { return c0 + wk + min(i, mine - 1) * NK; };
 
-  // LDS: the reduction buffer after the main loop; during it, for codebook indices, the
-  // replicated lookup table (built by all wavefronts while the first loads are in flight)
-  constexpr int RED_BYTES = NW * 16 * 64 * 4;
-  constexpr int LUT_BYTES = [] { if constexpr (D::IS_LUT) return D::TABLE_DWORDS * 4 + 512; else return 0; }();
-  __shared__ __attribute__((aligned(16))) unsigned char lds_raw[RED_BYTES > LUT_BYTES ? RED_BYTES : LUT_BYTES];
-
   static_assert(!D::IS_LUT || NW * 64 >= 256, "one level per thread");
   uint32_t my_level = 0;
   if constexpr (D::IS_LUT) my_level = D::fetch(p.T, tid);
   // prologue: DEPTH chunks in flight (past-the-end stages re-load my last chunk)
-  if (mine > 0)
+  if (mine > 0) {
+    if constexpr (A_RING == 1) issue_a(std::integral_constant<int, 0>{}, chunk_of(0));
     static_for<DEPTH>([&](auto Sc) __attribute__((always_inline)) { issue(Sc, chunk_of(decltype(Sc)::value)); });
-  if constexpr (D::IS_LUT) {
+  }
+  if constexpr (D::IS_LUT) {      // (the levels are staged where nothing has been written yet)
     uint32_t* table = reinterpret_cast<uint32_t*>(lds_raw);
-    D::build(table, reinterpret_cast<uint16_t*>(lds_raw + D::TABLE_DWORDS * 4), my_level, tid, NW * 64);
+    D::build(table, reinterpret_cast<uint16_t*>(lds_raw + LUT_BYTES), my_level, tid, NW * 64);
     u.set_table(table, l);
   }
   if (mine > 0) {
@@ -202,50 +258,50 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     // steady state: no branches, so the compiler can wait on exact load counts
     for (; i + 2 * DEPTH <= mine; i += DEPTH)
       static_for<DEPTH>([&](auto Sc) __attribute__((always_inline)) {
-        compute(Sc);
+        compute(Sc, chunk_of(i + decltype(Sc)::value + 1));
         issue(Sc, chunk_of(i + decltype(Sc)::value + DEPTH));
       });
     // drain
+    auto after = [&](int n) __attribute__((always_inline)) { return n + 1 < mine ? chunk_of(n + 1) : -1; };
     static_for<DEPTH>([&](auto Sc) __attribute__((always_inline)) {
       constexpr int S = decltype(Sc)::value;
       if (i + S < mine) {
-        compute(Sc);
+        compute(Sc, after(i + S));
         if (i + S + DEPTH < mine) issue(Sc, chunk_of(i + S + DEPTH));
       }
     });
     i += DEPTH;
     static_for<DEPTH>([&](auto Sc) __attribute__((always_inline)) {
-      if (i + decltype(Sc)::value < mine) compute(Sc);
+      if (i + decltype(Sc)::value < mine) compute(Sc, after(i + decltype(Sc)::value));
     });
   }
 
-  // ---- reduce over the NW wavefronts through LDS, one 16-row tile at a time -----------------
-  if constexpr (D::IS_LUT) __syncthreads();                // every wavefront is done with the table
-  float* red = reinterpret_cast<float*>(lds_raw);          // [NW][16 column offsets][64 lanes]
+  // ---- reduce over the NW wavefronts through LDS: all row tiles at once, each wavefront's sums where its A was -----
+  float* red = reinterpret_cast<float*>(lds_raw + LUT_BYTES);      // [NW][MT][16 column offsets][64 lanes]
   constexpr int PER = 16 / NK;                             // column offsets per thread
   const int idx0 = PER * wk;
   float sum[MT][PER];
   // lanes whose row is past M carry nothing: they stay out of the LDS traffic, of the
   // split-K exchange and of the final store
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const bool row_ok = mt * 16 + i16 < p.M;
-    if (mt) __syncthreads();
-    if (row_ok) {
+  for (int mt = 0; mt < MT; ++mt)
+    if (mt * 16 + i16 < p.M) {
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[(w * 16 + 4 * r + nt) * 64 + l] = acc[mt][nt][r];   // column offset 4r + nt
+        for (int r = 0; r < 4; ++r) red[((w * MT + mt) * 16 + 4 * r + nt) * 64 + l] = acc[mt][nt][r];   // column offset 4r + nt
     }
-    __syncthreads();
+  __syncthreads();
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int e = 0; e < PER; ++e) sum[mt][e] = 0.f;
-    if (row_ok) {
+    if (mt * 16 + i16 < p.M) {
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
         float t = 0.f;
 #pragma unroll
-        for (int kk = 0; kk < NK; ++kk) t += red[((kk * NS + ws) * 16 + idx0 + e) * 64 + l];
+        for (int kk = 0; kk < NK; ++kk) t += red[(((kk * NS + ws) * MT + mt) * 16 + idx0 + e) * 64 + l];
         sum[mt][e] = t;
       }
     }
@@ -338,16 +394,32 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
 #define QG_CAT2(a, b) a##b
 #define QG_CAT(a, b) QG_CAT2(a, b)
 
+// One row tile: from how many rows on A goes through LDS (17: never).  u8 and i4 on K = 8192, N = 28672 (several strips)
+// gain 2 to 5 % at 16 rows, 2 % at 13; one strip with 8 wavefronts 5 % at 16 rows (K = 8192, N = 14336, u4) and nothing
+// below (K = N = 4096 3 % longer at 13), less unpacking nothing at all (e2m1, bf16 there 17.8 -> 18.3); with 4 wavefronts only group 32 gains (K = 4096, N = 28672 19.3 -> 17.2 us; u8 on
+// K = N = 8192 13.3 -> 14.0).  16 wavefronts on one strip have half a chunk each at a time and nothing to hide the way behind
+// (K = 4096, N = 14336, u3 8.6 -> 8.8); above 4 bits their registers do not hold it (f6, bf16, N = 28672 39 -> 49); and
+// codebook lookups keep LDS busy already (4 bits, M = 16, N = 28672: two layers 59.5 -> 60.0).
+constexpr int lds_rows(int wt, int gpc, int nw, int ns) {
+  if (wt_is_lut(wt) || (nw == 16 && (ns == 1 || wt_bits(wt) > 4)) || (ns == 1 && gpc < 4 && (nw == 4 || wt_natural(wt)))) return 17;
+  return ns > 1 || gpc == 4 ? 13 : 16;
+}
+
 template <int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS = 1, bool MX = false>
 static int launch_cfg(const GemmParams& p, hipStream_t st) {
   if ((p.N / TILE_N) % NS) return QG_EINVAL;
-  auto kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX>;
+  constexpr int ROWS = MT > 1 ? 0 : lds_rows(QG_WT, GPC, NW, NS);
+  auto kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, (ROWS <= 16)>;
+  if constexpr (MT == 1 && ROWS <= 16) if (p.M < ROWS) kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, false>;
   dim3 grid((unsigned)(p.N / TILE_N / NS), (unsigned)p.splitk), block(NW * 64);
   hipLaunchKernelGGL(kern, grid, block, 0, st, p);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
-// variant = 10 * (row tiles: 1, 2, 3, 4) + (0: 8 wavefronts per strip, 1: 4 wavefronts, 2: 16 wavefronts)
+// variant = 10 * (row tiles: 1, 2, 3, 4) + arrangement.  One row tile: 0: 8 wavefronts on a strip, 1: 4, 2: 16, and
+// those with several strips.  Several row tiles always 8 wavefronts, 1: on one strip, 6: 4 along K on each of two (two on a SIMD: one
+// unpacks while the other's matrix instructions run; with 4 wavefronts M = 64, K = N = 8192 takes 20.5 us against 19.8, K = 8192,
+// N = 28672 56.9 against 52.1, M = 32 there 42.5 against 38.4)
 template <int ROUTE, int GPC>
 static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
   if constexpr (GPC == 4 && (QG_WT == 9 || QG_WT == 13)) {
@@ -359,23 +431,26 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
         case 14: return launch_cfg<ROUTE, 4, 8, 2, 1, 2, true>(p, st);
         case 15: return launch_cfg<ROUTE, 4, 16, 2, 1, 2, true>(p, st);
         case 16: return launch_cfg<ROUTE, 4, 16, 2, 1, 4, true>(p, st);
-        case 21: return launch_cfg<ROUTE, 4, 4, 2, 2, 1, true>(p, st);
-        case 26: return launch_cfg<ROUTE, 4, 4, 2, 2, 2, true>(p, st);
-        case 31: return launch_cfg<ROUTE, 4, 4, 2, 3, 1, true>(p, st);
-        case 36: return launch_cfg<ROUTE, 4, 4, 2, 3, 2, true>(p, st);
-        case 46: return launch_cfg<ROUTE, 4, 4, 2, 4, 2, true>(p, st);
-        case 41: return launch_cfg<ROUTE, 4, 4, 2, 4, 1, true>(p, st);
+        case 21: return launch_cfg<ROUTE, 4, 8, 2, 2, 1, true>(p, st);
+        case 26: return launch_cfg<ROUTE, 4, 8, 2, 2, 2, true>(p, st);
+        case 31: return launch_cfg<ROUTE, 4, 8, 2, 3, 1, true>(p, st);
+        case 36: return launch_cfg<ROUTE, 4, 8, 2, 3, 2, true>(p, st);
+        case 46: return launch_cfg<ROUTE, 4, 8, 2, 4, 2, true>(p, st);
+        case 41: return launch_cfg<ROUTE, 4, 8, 2, 4, 1, true>(p, st);
         default: return QG_EINVAL;
       }
     }
   }
   if (p.scale_e8m0) return QG_EUNSUPPORTED;
-  if constexpr (GPC == 4) {          // group size 32: the 4-wavefront arrangements only
+  if constexpr (GPC == 4) {          // group size 32: the one-strip arrangement with the fewest wavefronts only
+    // wide codes, four groups' constants and three or four row tiles do not fit the registers of eight wavefronts
+    // (u8, M = 64, K = N = 8192: 39.2 us against 29.4 with four)
+    constexpr int G32_WAVES = wt_bits(QG_WT) > 5 ? 4 : 8;
     switch (variant) {
       case 11: return launch_cfg<ROUTE, 4, 4, 2, 1>(p, st);
-      case 21: return launch_cfg<ROUTE, 4, 4, 2, 2>(p, st);
-      case 31: return launch_cfg<ROUTE, 4, 4, 2, 3>(p, st);
-      case 41: return launch_cfg<ROUTE, 4, 4, 2, 4>(p, st);
+      case 21: return launch_cfg<ROUTE, 4, 8, 2, 2>(p, st);
+      case 31: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 3>(p, st);
+      case 41: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 4>(p, st);
       default: return QG_EINVAL;
     }
   } else {
@@ -386,12 +461,12 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     case 14: return launch_cfg<ROUTE, GPC, 8, 2, 1, 2>(p, st);     // 2 strips x 4
     case 15: return launch_cfg<ROUTE, GPC, 16, 2, 1, 2>(p, st);    // 2 strips x 8
     case 16: return launch_cfg<ROUTE, GPC, 16, 2, 1, 4>(p, st);    // 4 strips x 4
-    case 21: return launch_cfg<ROUTE, GPC, 4, 2, 2>(p, st);
-    case 26: return launch_cfg<ROUTE, GPC, 4, 2, 2, 2>(p, st);     // 2 row tiles, 2 strips x 2
-    case 31: return launch_cfg<ROUTE, GPC, 4, 2, 3>(p, st);
-    case 36: return launch_cfg<ROUTE, GPC, 4, 2, 3, 2>(p, st);     // 3 row tiles, 2 strips x 2
-    case 46: return launch_cfg<ROUTE, GPC, 4, 2, 4, 2>(p, st);     // 4 row tiles, 2 strips x 2
-    case 41: return launch_cfg<ROUTE, GPC, 4, 2, 4>(p, st);
+    case 21: return launch_cfg<ROUTE, GPC, 8, 2, 2>(p, st);
+    case 26: return launch_cfg<ROUTE, GPC, 8, 2, 2, 2>(p, st);     // 2 row tiles, 2 strips x 4
+    case 31: return launch_cfg<ROUTE, GPC, 8, 2, 3>(p, st);
+    case 36: return launch_cfg<ROUTE, GPC, 8, 2, 3, 2>(p, st);     // 3 row tiles, 2 strips x 4
+    case 46: return launch_cfg<ROUTE, GPC, 8, 2, 4, 2>(p, st);     // 4 row tiles, 2 strips x 4
+    case 41: return launch_cfg<ROUTE, GPC, 8, 2, 4>(p, st);
     default: return QG_EINVAL;
   }
   }
@@ -400,10 +475,8 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
 // number of wavefronts along K per strip of a variant (the host sizes split-K with it)
 int QG_CAT(decode_waves_wt, QG_WT)(int variant) {
   switch (variant) {
-    case 10: case 15: return 8;
+    case 10: case 15: case 21: case 31: case 41: return 8;
     case 12: return 16;
-    case 14: case 16: return 4;
-    case 26: case 36: case 46: return 2;
     default: return 4;
   }
 }
