@@ -1,8 +1,8 @@
 // Prefill-sized matmul with int8 activations: LDS-staged A, register-resident W, the integer
 // matrix instruction (see qg_a8_gemm.hip for what is computed and how the codes are laid out).
 //
-// A workgroup of 4 wavefronts computes a 128 x 256 tile of C; wavefront w owns 64 columns and
-// all 128 rows, so a weight is unpacked once per 128 rows.  The 128 x 128-byte slab of A is shared
+// A workgroup of 4 wavefronts computes a 128 x 256 tile of C -- or 64 x 256 where 128 rows would leave CUs idle --;
+// wavefront w owns 64 columns and all rows, so a weight is unpacked once per 128 rows.  The 128 x 128-byte slab of A is shared
 // through LDS, each wavefront's own codes and scales pass through LDS as well: everything is loaded
 // straight into LDS by the memory pipe, which takes no registers -- 128 accumulators, the unpacked chunk
 // and the sums in flight fill the 256 that leave two workgroups on a CU.
@@ -28,6 +28,7 @@
 // Compiled once per code width (QG_BITS).
 #include "qg_common.h"
 #include "qg_static_for.h"
+#include "qg_wait.h"
 
 #ifndef QG_BITS
 #error "compile with -DQG_BITS=<1..8>"
@@ -83,9 +84,9 @@ __device__ __forceinline__ uint32_t quad_less(const uint32_t (&r)[4 * BITS], uin
   return (x + up) ^ SIGN;
 }
 
-template <int BITS, int GPC, bool SBF16, bool SPLIT, bool CORR>
+template <int BITS, int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
 __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_m, int tiles_n, int per_xcd) {
-  constexpr int RAW = 4 * BITS, BM = 128, MTS = BM / 16, BUF = BM * 128;
+  constexpr int RAW = 4 * BITS, MTS = BM / 16, BUF = BM * 128, A_LOADS = BM / 32;
   // slabs of A in flight: two where LDS holds them for two workgroups per CU (160 KiB), else one
   constexpr int A_AHEAD = BITS <= 7 ? 2 : 1, ABUFS = A_AHEAD + 1;
   constexpr int W_AT = ABUFS * BUF, S_AT = W_AT + 4 * 1024 * BITS, Z_AT = S_AT + 4 * 256, LDS_BYTES = Z_AT + (CORR ? 4 * 256 : 0);
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
   const uint32_t lds_a = lds_base + 1024u * (uint32_t)w, lds_w = lds_base + W_AT + (uint32_t)(w * 1024 * BITS), lds_s = lds_base + S_AT + 256u * (uint32_t)w, lds_z = lds_base + Z_AT + 256u * (uint32_t)w;
   auto a_fetch = [&](int buf, int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < A_LOADS; ++i) {
       const uint32_t off = ((i & 1) ? a_vodd : a_voff) + (uint32_t)(32 * i) * (uint32_t)p.K;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                    :: "s"(lds_a + (uint32_t)(buf * BUF + i * 4096)), "v"(off), "s"(a_rsrc), "s"(c * TILE_K) : "memory");
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
       });
     });
     // my part of the next chunk is in LDS (loads return in order: all but the newest slab)
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(A_AHEAD == 2 ? 4 : 0) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(A_AHEAD == 2 ? A_LOADS : 0) : "memory");
     __syncthreads();
     abuf_i = abuf_i == ABUFS - 1 ? 0 : abuf_i + 1;
   };
@@ -334,93 +335,127 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
 
   if (!active) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the slab loaded past the end
-  // ---- split-K: partial tiles meet in the workspace (the exchange of the 16-bit tiled kernel: stores that
-  // write through and loads that bypass the caches, one arrival counter per 64-column strip of a tile,
-  // the wavefront that arrives last sums the slabs in slab order) ---------------------------------
+  auto store_row = [&](int m, const f4_t (&v)[4]) __attribute__((always_inline)) {      // row scale, one rounding to the output type
+    const float as = p.a_scale ? p.a_scale[m] : 1.0f;
+    uint32_t o[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f2_t f = {v[2 * h][r] * as, v[2 * h + 1][r] * as};
+        o[2 * r + h] = p.out_bf16 ? __builtin_bit_cast(uint32_t, __builtin_convertvector(f, b2_t))
+                                  : __builtin_bit_cast(uint32_t, __builtin_convertvector(f, h2_t));
+      }
+    u4_t* dst = reinterpret_cast<u4_t*>(p.C + (int64_t)m * p.N + n16);
+    dst[0] = (u4_t){o[0], o[1], o[2], o[3]};
+    dst[1] = (u4_t){o[4], o[5], o[6], o[7]};
+  };
+  // ---- split-K: partial tiles meet in the workspace as in the 16-bit tiled kernel: a wavefront draws a ticket of its
+  // 64-column strip; all but the last store their sums, count them as done and leave; the last keeps its own in
+  // registers, waits for the count -- the others wait for nothing -- and adds the slabs in slab order (M = 200, K = N = 8192,
+  // four slabs of 128-row tiles: 45.4 us when all stored and the last read one slab after the other, its own too, 43.0 now) ----
   if constexpr (SPLIT) {
     constexpr int SC1 = 16;                                   // cache policy: device coherence
+    constexpr int AWAY = 0x40000000;                          // beyond the resource: loads give zeros, stores nothing
     auto ws_rsrc = [&](int sp) __attribute__((always_inline)) {
       return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (BM * A8_BN), 0, BM * A8_BN * 4, 0x00020000);
     };
-    {
-      const __amdgpu_buffer_rsrc_t mine = ws_rsrc(slab);
-#pragma unroll
-      for (int mt = 0; mt < MTS; ++mt)
-        if (m0 + mt * 16 + i16 < p.M) {
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[mt][nt]), mine, 16 * tid, (mt * 4 + nt) * 4096, SC1);
-        }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // my partial strip is out before my ticket is drawn
-    unsigned* ticket = p.tickets + 4 * tile + w;
+    auto ws_off = [&](int mt) __attribute__((always_inline)) { return m0 + mt * 16 + i16 < p.M ? 16 * tid : AWAY; };
+    unsigned* ticket = p.tickets + ticket_stride(4 * tiles) * (4 * tile + w);
     unsigned drawn = 0;
     if (l == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    drawn = __builtin_amdgcn_readfirstlane(drawn);
-    if (drawn != (unsigned)(p.splitk - 1)) return;
-#pragma unroll
-    for (int mt = 0; mt < MTS; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = (f4_t){0.f, 0.f, 0.f, 0.f};
-    for (int sp = 0; sp < p.splitk; ++sp) {
-      const __amdgpu_buffer_rsrc_t r = ws_rsrc(sp);
+    drawn = __builtin_amdgcn_readfirstlane(drawn) & 0xffffu;
+    if (drawn != (unsigned)(p.splitk - 1)) {
+      const __amdgpu_buffer_rsrc_t mine = ws_rsrc(slab);
 #pragma unroll
       for (int mt = 0; mt < MTS; ++mt) {
-        if (m0 + mt * 16 + i16 < p.M) {                        // rows past M were not written
-          u4_t v[4];
+        const int off = ws_off(mt);
 #pragma unroll
-          for (int nt = 0; nt < 4; ++nt) v[nt] = __builtin_amdgcn_raw_buffer_load_b128(r, 16 * tid, (mt * 4 + nt) * 4096, SC1);
+        for (int nt = 0; nt < 4; ++nt)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, acc[mt][nt]), mine, off, (mt * 4 + nt) * 4096, SC1);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // my partial strip is out before it counts as done
+      if (l == 0) __hip_atomic_fetch_add(ticket, 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    (void)wait_for([&] { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 16; },
+                   (unsigned)(p.splitk - 1), [] { __builtin_amdgcn_s_sleep(1); });
+    asm volatile("" ::: "memory");                              // no slab is read ahead of the count
+    if (l == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+    // R row tiles at a time, S slabs' loads in flight
+    constexpr int R = 2, S = 4;
 #pragma unroll
-          for (int nt = 0; nt < 4; ++nt) acc[mt][nt] += __builtin_bit_cast(f4_t, v[nt]);
+    for (int h = 0; h < MTS; h += R) {
+      f4_t sum[R][4];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) sum[i][nt] = (f4_t){0.f, 0.f, 0.f, 0.f};
+      for (int sp = 0; sp < p.splitk; sp += S) {
+        u4_t x[S][R][4];
+#pragma unroll
+        for (int y = 0; y < S; ++y) {
+          const __amdgpu_buffer_rsrc_t r = ws_rsrc(min(sp + y, p.splitk - 1));
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            const int off = sp + y < p.splitk && sp + y != slab ? ws_off(h + i) : AWAY;
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) x[y][i][nt] = __builtin_amdgcn_raw_buffer_load_b128(r, off, ((h + i) * 4 + nt) * 4096, SC1);
+          }
         }
+#pragma unroll
+        for (int y = 0; y < S; ++y)
+          if (sp + y < p.splitk) {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+              for (int nt = 0; nt < 4; ++nt) sum[i][nt] += sp + y == slab ? acc[h + i][nt] : __builtin_bit_cast(f4_t, x[y][i][nt]);
+          }
+      }
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int m = m0 + (h + i) * 16 + i16;
+        if (m < p.M) store_row(m, sum[i]);
       }
     }
-    if (l == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+    return;
   }
 
-  // ---- row scale, one rounding to the output type, store ---------------------
 #pragma unroll
   for (int mt = 0; mt < MTS; ++mt) {
     const int m = m0 + mt * 16 + i16;
-    if (m < p.M) {
-      const float as = p.a_scale ? p.a_scale[m] : 1.0f;
-      uint32_t o[8];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const f2_t f = {acc[mt][2 * h][r] * as, acc[mt][2 * h + 1][r] * as};
-          o[2 * r + h] = p.out_bf16 ? __builtin_bit_cast(uint32_t, __builtin_convertvector(f, b2_t))
-                                    : __builtin_bit_cast(uint32_t, __builtin_convertvector(f, h2_t));
-        }
-      u4_t* dst = reinterpret_cast<u4_t*>(p.C + (int64_t)m * p.N + n16);
-      dst[0] = (u4_t){o[0], o[1], o[2], o[3]};
-      dst[1] = (u4_t){o[4], o[5], o[6], o[7]};
-    }
+    if (m < p.M) store_row(m, acc[mt]);
   }
 }
 
 #define QG_CAT2(a, b) a##b
 #define QG_CAT(a, b) QG_CAT2(a, b)
 
-template <int GPC, bool SBF16, bool SPLIT, bool CORR>
+template <int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
 static int launch_one(const A8Params& p, hipStream_t st) {
-  const int tiles_m = (p.M + 127) / 128, tiles_n = (p.N + A8_BN - 1) / A8_BN;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + A8_BN - 1) / A8_BN;
   const int per_xcd = (tiles_m * tiles_n * p.splitk + 7) / 8;
-  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, SBF16, SPLIT, CORR>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, per_xcd);
+  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, BM, SBF16, SPLIT, CORR>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, per_xcd);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
-template <int GPC, bool SBF16>
+template <int GPC, int BM, bool SBF16>
 static int launch_scales(const A8Params& p, bool corr, hipStream_t st) {
-  if (corr) return p.splitk > 1 ? launch_one<GPC, SBF16, true, true>(p, st) : launch_one<GPC, SBF16, false, true>(p, st);
-  return p.splitk > 1 ? launch_one<GPC, SBF16, true, false>(p, st) : launch_one<GPC, SBF16, false, false>(p, st);
+  if (corr) return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, true>(p, st) : launch_one<GPC, BM, SBF16, false, true>(p, st);
+  return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, false>(p, st) : launch_one<GPC, BM, SBF16, false, false>(p, st);
 }
 
-// corr: zero-points, or uintk codes
-int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, bool corr, hipStream_t st) {
-  if (p.group == 64) return p.scale_bf16 ? launch_scales<2, true>(p, corr, st) : launch_scales<2, false>(p, corr, st);
-  return p.scale_bf16 ? launch_scales<1, true>(p, corr, st) : launch_scales<1, false>(p, corr, st);
+template <int BM>
+static int launch_rows(const A8Params& p, bool corr, hipStream_t st) {
+  if (p.group == 64) return p.scale_bf16 ? launch_scales<2, BM, true>(p, corr, st) : launch_scales<2, BM, false>(p, corr, st);
+  return p.scale_bf16 ? launch_scales<1, BM, true>(p, corr, st) : launch_scales<1, BM, false>(p, corr, st);
+}
+
+// corr: zero-points, or uintk codes; bm: rows of a tile, 64 or 128
+int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, bool corr, int bm, hipStream_t st) {
+  if (bm == 64) return launch_rows<64>(p, corr, st);
+  if (bm == 128) return launch_rows<128>(p, corr, st);
+  return QG_EINVAL;
 }
 
 }  // namespace qg

@@ -39,11 +39,11 @@ QG_FOR_ALL_LUT(QG_DECL)
 #define QG_DECL_A8(b) int a8_launch_bits##b(const A8Params&, int, int, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
-#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, bool, hipStream_t);
+#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, bool, int, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
 typedef int (*a8_fn)(const A8Params&, int, int, hipStream_t);
-typedef int (*a8_large_fn)(const A8Params&, bool, hipStream_t);
+typedef int (*a8_large_fn)(const A8Params&, bool, int, hipStream_t);
 static const a8_large_fn kA8Large[8] = {a8_large_launch_bits1, a8_large_launch_bits2, a8_large_launch_bits3, a8_large_launch_bits4,
                                         a8_large_launch_bits5, a8_large_launch_bits6, a8_large_launch_bits7, a8_large_launch_bits8};
 static const a8_fn kA8[8] = {a8_launch_bits1, a8_launch_bits2, a8_launch_bits3, a8_launch_bits4,
@@ -775,30 +775,36 @@ static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* c
   *waves_out = waves; *splitk_out = (KC + cps - 1) / cps; *cps_out = cps;
 }
 
-// Tiled int8 kernel: split-K of `rows` rows, and the estimated time in microseconds.  Host arithmetic only.
-// Workgroups (128 x 256 tiles times K-slabs) sit two to a CU.  A chunk of K takes 1.14 us (+ 0.07 per bit above 4)
-// alone on a CU and 1.95 (+ 0.14) with a neighbour, group 64 a quarter more; a launch 7 us; the exchange of
-// partial sums 2.5 + 2.35 per slab + 0.22 per MB (fitted to M = 65 .. 1000, K = 1024 .. 14336, N = 2048 .. 28672 at 4
-// and 8 bits: within 15 % there, and the split it picks within 8 % of the best of 1, 2, 4 and 8).
-static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* splitk_out, int* cps_out) {
+// Tiled int8 kernel: tile height and split-K of `rows` rows, and the estimated time in microseconds.  Host arithmetic only.
+// Workgroups (64 or 128 x 256 tiles times K-slabs) sit two to a CU.  A chunk of K takes a 128-row tile 1.45 us alone
+// on a CU and 2.3 with a neighbour, a 64-row tile 1.0 and 1.5 (2 % more per bit above 4, group 64 30 %); a launch 6 us; the
+// exchange of partial sums 4 + 0.12 per MB + 1.2 per slab of 64 rows that the last one of a tile reads.  Fitted to M = 65 .. 1000,
+// K = 2048 .. 14336, N = 4096 .. 28672, u4, i8, groups 64 and 128 (640 points, 7 % rms); what it picks takes 3.6 % longer than the best
+// of all heights and splits on average.  64-row tiles: M = 300, K = N = 8192, u4 60.7 -> 46.0 us in three slabs, M = 128
+// 37.4 -> 28.6, K = N = 4096, M = 200 35.4 -> 22.5; 128-row tiles stay where they fill the chip.
+static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* bm_out, int* splitk_out, int* cps_out) {
   const int KC = (int)(K / TILE_K);
-  const int64_t tiles = ((rows + 127) / 128) * ((N + 255) / 256);
-  const int over = bits > 4 ? bits - 4 : 0;
-  const double f = group == 64 ? 1.25 : 1.0, c1 = f * (1.14 + 0.07 * over), c2 = f * (1.95 + 0.14 * over);
+  const double f = (group == 64 ? 1.3 : 1.0) * (1.0 + 0.02 * (bits > 4 ? bits - 4 : 0));
   double best = 1e30;
-  int splitk = 1;
-  for (int sk = 1; sk <= 8; sk *= 2) {
-    const int cps = (KC + sk - 1) / sk;
-    const size_t part = (size_t)sk * tiles * (128 * 256 * sizeof(float));
-    if (sk > 1 && (cps < 4 || tiles * sk > 256 || part > WS_PARTIAL_BYTES)) continue;
-    const int64_t full = tiles * sk / 512, rest = tiles * sk % 512;
-    const double mb = (double)sk * (double)rows * (double)N * 4.0 / 1e6;
-    const double cost = 7.0 + cps * (full * c2 + (rest == 0 ? 0.0 : rest <= 256 ? c1 : c2)) + (sk > 1 ? 2.5 + 2.35 * sk + 0.22 * mb : 0.0);
-    if (cost < best) { best = cost; splitk = sk; }
-  }
-  if (knob(1) > 0) splitk = knob(1);
+  int splitk = 1, bm = 128;
+  for (int cand = 64; cand <= 128; cand *= 2)
+    for (int sk : {1, 2, 3, 4, 6, 8}) {
+      if (knob(2) > 0 && cand != knob(2)) continue;
+      const int64_t tiles_m = (rows + cand - 1) / cand, tiles = tiles_m * ((N + 255) / 256);
+      const int cps = (KC + sk - 1) / sk;
+      const size_t part = (size_t)sk * tiles * (cand * 256 * sizeof(float));
+      if (sk > 1 && (cps < 4 || tiles * sk > 512 || part > WS_PARTIAL_BYTES)) continue;
+      const int64_t full = tiles * sk / 512, rest = tiles * sk % 512;
+      const double alone = cand == 64 ? 1.0 : 1.45, pair = cand == 64 ? 1.5 : 2.3;
+      const double loop = f * cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
+      const double mb = (double)sk * (double)rows * (double)N * 4.0e-6;
+      const double cost = 6.0 + loop + (sk == 1 ? 0.0 : 4.0 + 0.12 * mb + 1.2 * (sk - 1) * (double)rows / (64.0 * tiles_m));
+      if (cost < best) { best = cost; splitk = sk; bm = cand; }
+    }
+  if (knob(1) > 0) splitk = std::min(knob(1), 4096);      // (a strip's counter has 16 bits for its slabs)
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
+  *bm_out = bm;
   *splitk_out = (KC + cps - 1) / cps;
   *cps_out = cps;
   return best;
@@ -817,8 +823,8 @@ static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bit
   const double block = 8.5 + 0.165e-6 * (1.0 + 0.06 * (bits > 4 ? bits - 4 : 0)) * (double)K * (double)N;
   const int rem = (int)(M % 64);
   const double blocks = block * ((double)(M / 64) + (rem == 0 ? 0.0 : rem <= 16 ? 0.55 : rem <= 32 ? 0.65 : 1.0));
-  int sk, cps;
-  const double tiled = plan_a8_tiled(M, N, K, group, bits, &sk, &cps);
+  int bm, sk, cps;
+  const double tiled = plan_a8_tiled(M, N, K, group, bits, &bm, &sk, &cps);
   return tiled < blocks;
 }
 
@@ -833,12 +839,13 @@ static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipSt
     q.a_scale = p.a_scale ? p.a_scale + r0 : nullptr;
     q.C = p.C + r0 * p.N;
     q.M = (int)std::min(most, M - r0);
-    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &q.splitk, &q.chunks_per_split);
-    const int64_t tiles = (int64_t)((q.M + 127) / 128) * ((q.N + 255) / 256);
-    if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (128 * 256 * sizeof(float)), tile_tickets(tiles), st, &q.ws, &q.tickets) != QG_OK) {
+    int bm;
+    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &bm, &q.splitk, &q.chunks_per_split);
+    const int64_t tiles = (int64_t)((q.M + bm - 1) / bm) * ((q.N + 255) / 256);
+    if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, &q.ws, &q.tickets) != QG_OK) {
       q.splitk = 1; q.chunks_per_split = q.K / TILE_K;
     }
-    const int rc = kA8Large[bits - 1](q, corr, st);
+    const int rc = kA8Large[bits - 1](q, corr, bm, st);
     if (rc != QG_OK) return rc;
   }
   return QG_OK;

@@ -197,12 +197,16 @@ __device__ __forceinline__ void tile_position(int tile, int tiles_m, int tiles_n
   *tn = (tile % panel) / gsize;
 }
 
-// Arrival counters of split-K calls, and their spacing: every counter has a cache line of its own while all fit.
+// Arrival counters of split-K calls, and their spacing: as far apart as all of them fit, a cache line each at most.
 // Counters on one line queue up in the memory-side cache: a tile's eight 4 bytes apart cost 2.3 us (two slabs)
 // to 3.8 us (eight) more per call than 128 bytes apart (M = 64, K x N = 16.8 M).
 constexpr int WS_TICKETS = 16384;
 constexpr int TICKET_LINE = 32;
-__host__ __device__ constexpr int ticket_stride(int64_t counters) { return counters * TICKET_LINE <= WS_TICKETS ? TICKET_LINE : 1; }
+__host__ __device__ constexpr int ticket_stride(int64_t counters) {
+  int stride = TICKET_LINE;
+  while (stride > 1 && counters * stride > WS_TICKETS) stride /= 2;
+  return stride;
+}
 
 // The 16x16 tiled kernel's own choice of 64-row tiles: when 128-row tiles would occupy at
 // most half of the 256 CUs (column tiles are 256 wide).
