@@ -758,12 +758,16 @@ int qgemm_codebook(const void* A, const void* packed_W, const void* codebook, co
                    WS_PER_STREAM, codebook, true);
 }
 
-// int8 activations: wavefronts per strip, row tiles and split-K of one block of at most 64 rows
+// int8 activations: row tiles of up to 64 rows -- 33 to 48 rows carry three, as in the 16-bit kernel (M = 45, u4: K = N = 8192
+// 17.4 -> 15.3 us, N = 28672 46.7 -> 39.0)
+static int a8_row_tiles(int64_t M) { return M > 32 && M <= 48 ? 3 : row_tiles(M); }
+
+// int8 activations: wavefronts per strip and split-K of one block of at most 64 rows
 static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* cps_out) {
-  const int KC = K / TILE_K, NCH = N / TILE_N;
-  // eight wavefronts per strip on long K; four with four row tiles (their accumulators and
+  const int KC = K / TILE_K, NCH = N / TILE_N, mt = a8_row_tiles(M);
+  // eight wavefronts per strip on long K; four with three or four row tiles (their accumulators and
   // the ring do not fit the registers eight wavefronts leave each) and on short K
-  int waves = (KC >= 16 && row_tiles(M) < 4) ? 8 : 4;
+  int waves = (KC >= 16 && mt < 3) ? 8 : 4;
   int splitk = knob(1);
   if (splitk <= 0) {
     splitk = 1;
@@ -811,18 +815,16 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
 }
 
 // int8 activations on more than 64 rows: the tiled kernel, or blocks of 64 rows through the streaming kernel?
-// The latter take 8.5 us + 0.165 per million weights (6 % more per bit above 4) each (a last block of up to 16 rows 0.55 of that, of up to 32
-// rows 0.65), and win while the tiled kernel's chip is nearly empty: M = 128 on K = N = 8192 37 us against 41,
-// M = 192 56 against 41; M = 1000 on N = 28672 750 against 256.  Zero-points make both a little longer (at most 8 % where
-// the two are close) and need no rule of their own: 200 cases, M = 96 .. 384, K = 2048 .. 14336, N = 4096 .. 28672, u4, i4,
-// u8, i8, groups 64 and 128, within 6 % of the better of the two, two 8-bit ones within 17 %.
+// The latter take 8 us + 0.16 per million weights (6 % more per bit above 4) each (a last block of up to 16 rows 0.48 of that, of
+// up to 32 rows 0.65, 48 0.85), and win while the tiled kernel's chip is nearly empty: M = 65 on K = N = 8192 26.9 us against 28.5,
+// M = 128 36.7 against 29.1; M = 96 on K = N = 4096 a tie (19.7); M = 1000 on N = 28672 750 against 287.
 static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bits) {
   if (knob(0) == 2 || knob(0) == 3) return knob(0) == 2;
   if (M <= 64) return false;
   if (M > 1024) return true;
-  const double block = 8.5 + 0.165e-6 * (1.0 + 0.06 * (bits > 4 ? bits - 4 : 0)) * (double)K * (double)N;
+  const double block = 8.0 + 0.16e-6 * (1.0 + 0.06 * (bits > 4 ? bits - 4 : 0)) * (double)K * (double)N;
   const int rem = (int)(M % 64);
-  const double blocks = block * ((double)(M / 64) + (rem == 0 ? 0.0 : rem <= 16 ? 0.55 : rem <= 32 ? 0.65 : 1.0));
+  const double blocks = block * ((double)(M / 64) + (rem == 0 ? 0.0 : rem <= 16 ? 0.48 : rem <= 32 ? 0.65 : rem <= 48 ? 0.85 : 1.0));
   int bm, sk, cps;
   const double tiled = plan_a8_tiled(M, N, K, group, bits, &bm, &sk, &cps);
   return tiled < blocks;
@@ -897,7 +899,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
     q.M = (int)((M - r0 < 64) ? (M - r0) : 64);
     int waves;
     plan_a8(q.M, q.N, q.K, &waves, &q.splitk, &q.chunks_per_split);
-    const int mt = row_tiles(q.M);
+    const int mt = a8_row_tiles(q.M);
     if (q.splitk > 1) {
       const int NCH = q.N / TILE_N;
       float* ws = nullptr; unsigned* tk = nullptr;

@@ -60,4 +60,3 @@ def test_arrangements_against_the_oracle(variant, M):
         B.qg_set_knob(1, splitk)
         B.qg_set_knob(3, variant)
         assert_c_close(P.gpu_c(), P.oracle_c(), f"{P.case.name} {splitk}")
-
