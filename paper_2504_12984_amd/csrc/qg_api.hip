@@ -408,9 +408,11 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // Split-K serves the lower row tiles when they would leave CUs idle.  Candidates: 64- or
 // 128-row tiles, K cut into 1 to 8 slabs of an even number of chunks (the kernel
 // works in pairs of chunks), at most one workgroup per CU when split.  tiled_cost estimates the
-// time in microseconds, fitted to 1300 measurements at K = 1024 .. 28672, N = 2048 .. 28672, M = 24 .. 1000 at
-// 4 bits and 700 at 3, 6 and 8.  In a sweep of 120 cases (3, 4, 6, 8 bits, M = 96 .. 1000) what it picks takes 1.1 % longer than
-// the best candidate on average and 11 % at most, noise of the timing included.
+// time in microseconds; the shape of the estimate and the widths' factors are a fit to 2000 measurements at K = 1024 .. 28672,
+// N = 2048 .. 28672, M = 24 .. 1000 at 3, 4, 6 and 8 bits, its constants to the exchange as it is now: u4, K = 2048 .. 14336,
+// N = 4096 .. 28672, M = 65 .. 768 (70 cases): what it picks takes 0.4 % longer than the best candidate on average and 5 % at most; with
+// the constants from before the counters had lines of their own 2.2 % and 15 % (M = 200, K = 5120, N = 13824 44.1 -> 38.3 us,
+// M = 300, K = N = 4096 23.3 -> 21.5).
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
@@ -421,12 +423,12 @@ static double tiled_cost(int bm, int sk, int cps, int64_t M, int64_t N, int64_t 
   const bool hw_convert = (t.bits == 4 || t.bits == 6 || t.bits == 8);      // e2m1, e3m2, e4m3
   const double unpack = t.kind == QG_FLOAT ? (hw_convert ? 1.0 + 0.04 * over : 1.5) : 1.0 + 0.085 * over;
   // a chunk alone on a CU, and with a second workgroup there
-  const double alone = unpack * (bm == 64 ? 0.95 : 1.30), pair = unpack * (bm == 64 ? 1.65 : 2.6);
+  const double alone = unpack * (bm == 64 ? 0.99 : 1.32), pair = unpack * (bm == 64 ? 1.66 : 2.86);
   const int64_t n = ((M + bm - 1) / bm) * ((N + 255) / 256) * sk, full = n / 512, rest = n % 512;
   const double loop = cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
   const double read = 0.19e-6 * (double)K * (double)N * t.bits / 8.0;       // the weights from memory
   const double mb = (double)sk * (double)M * (double)N * 4.0e-6;            // partial sums
-  return 4.0 + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? 4.0 + 0.385 * mb : 3.0 + 0.335 * mb);
+  return 3.9 + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? 3.6 + 0.26 * mb : 2.6 + 0.42 * mb);
 }
 
 static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out, int* splitk_out, int* cps_out,
