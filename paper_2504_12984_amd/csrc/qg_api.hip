@@ -324,7 +324,9 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // their A rows in the vector cache (measured 2-4 % shorter at K = 8192, N = 28672;
   // with several row tiles 2 strips x 4 wavefronts along K, 10-15 % shorter, also for short K: K = 4096,
   // N = 28672, M = 24: 20.8 us against 22.4)
-  if ((KC > 32 || mt > 1) && NCH % 2 == 0 && NCH / 2 >= 192) variant = (mt == 1) ? 14 : tens + 6;
+  // (several row tiles from 257 strips on: eight wavefronts of theirs fill a CU, and 257 .. 383 strips, one each, would be a
+  // round and a fraction: K = 8192, N = 20480, M = 20 35.6 us)
+  if ((KC > 32 || mt > 1) && NCH % 2 == 0 && (NCH / 2 >= 192 || (mt > 1 && NCH > 256))) variant = (mt == 1) ? 14 : tens + 6;
   // up to 6 bits per code a wavefront needs few enough registers for 16 of them per
   // workgroup (2 strips x 8 along K): twice the wavefronts in flight, 1-6 % shorter
   if (KC > 32 && variant == 14 && wt_bits(wt) <= 6 && group != 64) variant = 15;
@@ -501,10 +503,9 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
   // at N = 8192 -- while the tiled kernel shares A through LDS among four strips and splits K
   // instead; it wins on all but the small problems (K = 8192, N = 28672, M = 64, 6 bits:
   // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).  Up to 48 rows the
-  // streaming kernel carries three row tiles (0.92 of that).  The fits predate the second kernel that adds
-  // the slabs: from 49 rows on the tiled kernel would now be up to 21 % shorter on the small problems that stay
-  // here too (K = N = 8192, M = 64: 19.3 in eight slabs against 23.0, M = 56 18.3 against 23.1; K = 14336, N = 4096 6 to
-  // 10 %); the choice is kept as tested.
+  // streaming kernel carries three row tiles (0.92 of that).  The fits are older than the streaming kernel's way of A
+  // through LDS and the tiled kernel's exchange; where they put the line the two are close (u4, M = 64: K = N = 8192 18.4 here,
+  // 19.3 tiled in eight slabs; K = 8192, N = 28672 52.1 against 42.6), and the choice is kept as tested.
   if (M > 32 && (double)K * (double)N >= 16.0e6 && knob(1) == 0 &&
       knob(2) == 0 && knob(3) == 0) {
     double tiled = 1e30;
