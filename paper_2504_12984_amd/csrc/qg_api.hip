@@ -420,17 +420,40 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
 // hardware convert) + 1.2 per slab.  That fit is older than the kernel's present exchange: the 1.2 is what reading
 // the slabs back one pair after the other cost, where up to LARGE_MEET slabs now meet and more have a second kernel.
-static double tiled_cost(int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
+struct TiledFit { double start, alone64, pair64, alone128, pair128, meet, meet_mb, many, many_mb; };
+static constexpr TiledFit TILED_FIT = {3.9, 0.99, 1.66, 1.32, 2.86, 3.6, 0.26, 2.6, 0.42};
+// The first fit.  It settles which calls can do without a workspace (under capture, or without memory): one that it leaves whole
+// has always been served there, and is served whole there still if the fit of today splits it.
+static constexpr TiledFit TILED_FIT_WHOLE = {4.0, 0.95, 1.65, 1.30, 2.6, 4.0, 0.385, 3.0, 0.335};
+
+static double tiled_cost(const TiledFit& f, int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
   const int over = t.bits > 4 ? t.bits - 4 : 0;
   const bool hw_convert = (t.bits == 4 || t.bits == 6 || t.bits == 8);      // e2m1, e3m2, e4m3
   const double unpack = t.kind == QG_FLOAT ? (hw_convert ? 1.0 + 0.04 * over : 1.5) : 1.0 + 0.085 * over;
   // a chunk alone on a CU, and with a second workgroup there
-  const double alone = unpack * (bm == 64 ? 0.99 : 1.32), pair = unpack * (bm == 64 ? 1.66 : 2.86);
+  const double alone = unpack * (bm == 64 ? f.alone64 : f.alone128), pair = unpack * (bm == 64 ? f.pair64 : f.pair128);
   const int64_t n = ((M + bm - 1) / bm) * ((N + 255) / 256) * sk, full = n / 512, rest = n % 512;
   const double loop = cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
   const double read = 0.19e-6 * (double)K * (double)N * t.bits / 8.0;       // the weights from memory
   const double mb = (double)sk * (double)M * (double)N * 4.0e-6;            // partial sums
-  return 3.9 + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? 3.6 + 0.26 * mb : 2.6 + 0.42 * mb);
+  return f.start + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? f.meet + f.meet_mb * mb : f.many + f.many_mb * mb);
+}
+
+// The cheapest tile height and split-K under a fit (more than 64 rows whose 128-row tiles leave half of the CUs idle); its cost.
+static double best_tiled(const TiledFit& f, int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out, int* splitk_out) {
+  const int KC = (int)(K / TILE_K);
+  const int64_t tiles_n = (N + 255) / 256;
+  double best = 1e30;
+  for (int bm = 64; bm <= 128; bm *= 2)
+    for (int sk = 1; sk <= 8; ++sk) {
+      const int64_t tiles_m = (M + bm - 1) / bm;
+      int cps = (KC + sk - 1) / sk;
+      if (sk > 1 && (cps & 1)) ++cps;
+      if (sk > 1 && (cps < 4 || (KC + cps - 1) / cps != sk || tiles_m * tiles_n * sk > 256)) continue;
+      const double cost = tiled_cost(f, bm, sk, cps, M, N, K, t);
+      if (cost < best) { best = cost; *bm_out = bm; *splitk_out = sk; }
+    }
+  return best;
 }
 
 static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out, int* splitk_out, int* cps_out,
@@ -456,16 +479,7 @@ static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out,
       }
       if (cost_out) *cost_out = best;
     } else if (splitk <= 0) {
-      double best = 1e30;
-      for (int cand_bm = 64; cand_bm <= 128; cand_bm *= 2)
-        for (int sk = 1; sk <= 8; ++sk) {
-          const int64_t tiles_m = (M + cand_bm - 1) / cand_bm;
-          int cps = (KC + sk - 1) / sk;
-          if (sk > 1 && (cps & 1)) ++cps;
-          if (sk > 1 && (cps < 4 || (KC + cps - 1) / cps != sk || tiles_m * tiles_n * sk > 256)) continue;
-          const double cost = tiled_cost(cand_bm, sk, cps, M, N, K, t);
-          if (cost < best) { best = cost; bm = cand_bm; splitk = sk; }
-        }
+      const double best = best_tiled(TILED_FIT, M, N, K, t, &bm, &splitk);
       if (cost_out) *cost_out = best;
     }
   }
@@ -476,6 +490,14 @@ static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out,
   *bm_out = bm;
   *splitk_out = (KC + cps - 1) / cps;
   *cps_out = cps;
+}
+
+// No workspace is to be had for a planned split: whether the call is one that runs whole then (see TILED_FIT_WHOLE), and its tile height.
+static bool tiled_runs_whole(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm) {
+  if (knob(1) > 0 || knob(2) > 0 || M <= 64 || !large_prefers_64_rows(M, N)) return false;
+  int splitk = 0;
+  (void)best_tiled(TILED_FIT_WHOLE, M, N, K, t, bm, &splitk);
+  return splitk == 1;
 }
 
 // The tiled kernels' 32-bit byte offsets: A, the packed weight and the scale array each below 2 GiB.
@@ -711,7 +733,8 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
     if (q.splitk > 1) {
       const int64_t tiles = ((M + bm - 1) / bm) * ((N + 255) / 256);
       rc = acquire_ws(ws_mode, (size_t)q.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, q);
-      if (rc != QG_OK) return rc;
+      if (rc != QG_OK && !tiled_runs_whole(M, N, K, t16, &bm)) return rc;
+      if (rc != QG_OK) { q.splitk = 1; q.chunks_per_split = (int)(K / TILE_K); }
     }
     rc = large_launch_wt14(q, route, bm, st);
     return rc == QG_OK && q.splitk > LARGE_MEET ? launch_reduce_tiles(q, route, bm, st) : rc;
@@ -738,7 +761,8 @@ static int qgemm_run(const void* A, const void* packed_W, const void* scales, co
   if (p.splitk > 1) {
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + 255) / 256);
     rc = acquire_ws(ws_mode, (size_t)p.splitk * (size_t)tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, p);   // a ticket per 64-column strip
-    if (rc != QG_OK) return rc;
+    if (rc != QG_OK && !tiled_runs_whole(M, N, K, t, &bm)) return rc;
+    if (rc != QG_OK) { p.splitk = 1; p.chunks_per_split = (int)(K / TILE_K); }
   }
   rc = wt_is_lut(wt) ? kLargeLut[wt - WT_LUT0](p, route, bm, st) : kLarge[wt](p, route, bm, st);
   return rc == QG_OK && p.splitk > LARGE_MEET ? launch_reduce_tiles(p, route, bm, st) : rc;
@@ -908,6 +932,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
       float* ws = nullptr; unsigned* tk = nullptr;
       int rc = get_workspace((size_t)q.splitk * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float), (size_t)NCH, st, &ws, &tk, &q.slots);
       if (rc == QG_OK) rc = exchange_slots(q.splitk, NCH, mt, ws, st, &q.slots);
+      if (rc != QG_OK && M > 64 && r0 == 0) return run_a8_tiled(p, M, zeros || t.kind == QG_UINT, t.bits, st);      // no workspace: the tiled kernel does without
       if (rc != QG_OK) return rc;
       q.ws = ws; q.tickets = tk;
     }
