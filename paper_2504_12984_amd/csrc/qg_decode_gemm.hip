@@ -6,7 +6,7 @@
 // DEPTH chunks in flight at all times in a ring of registers (the software
 // pipelining the paper calls essential, Sections "An Example of Tilus Program"
 // and "End-to-End Performance"): per chunk BITS 16-byte loads of packed codes,
-// four 16-byte loads of A (one per k-step, L2-resident), one load each of
+// four 16-byte loads of A per row tile (L2-resident), one load each of
 // scales and zero-points.  The steady-state loop has no branches and refills a
 // ring entry right after it has been consumed, so the compiler waits on exact
 // outstanding-load counts instead of draining the queue.
@@ -15,8 +15,8 @@
 // pipeline, Section "Key Ideas", with no layout conversion and no trip through
 // LDS).  From 13 or 16 rows on A passes through LDS, each wavefront's rows through a part of its own: the matrix
 // instruction wants 16 rows in adjacent lanes, and loads in that order run at 16 bytes per clock and CU (a lane at a
-// time), loads along the rows at 40 to 54.  M = 64, K = N = 8192, u4: 22.9 -> 19.1 us; M = 45 17.9 -> 16.6; M = 16, K = 8192,
-// N = 28672, int4 27.6 -> 26.6, group 64 30.6 -> 28.0.  With fewer rows many lanes of a direct load share an address and the way
+// time), loads along the rows at 40 to 54.  M = 64, K = N = 8192, u4: 22.9 -> 18.4 us; M = 45 17.9 -> 16.1; M = 16, K = 8192,
+// N = 28672, int4 27.6 -> 26.0, group 64 30.6 -> 27.7.  With fewer rows many lanes of a direct load share an address and the way
 // through LDS costs more than it saves (M = 8 there 24.7 against 25.9).
 // The K reduction runs inside the MFMA (across the four 8-wide k-blocks
 // of lanes), then across the wavefronts through LDS, then -- when K is also
