@@ -196,9 +196,11 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
     Stage& s = st[S];
     u4_t af[2][MT];                // fragments of this k-step and the next
     if constexpr (A_LDS) {
+      // the lanes of a wavefront exchange rows: the last chunk's reads stay ahead of the writes, the writes ahead of the reads
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
       for (int q = 0; q < 4 * MT; ++q) *reinterpret_cast<u4_t*>(my_a + a_wr[q & 3] + (q >> 2) * 1024) = ar[S % A_RING][q];
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the lanes of a wavefront exchange rows: writes stay ahead of the reads
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       if constexpr (A_RING == 1) {
         if (next >= 0) issue_a(Sc, next);
         __builtin_amdgcn_sched_barrier(0);
@@ -292,6 +294,7 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
   constexpr int PER = 16 / NK;                             // column offsets per thread
   const int idx0 = PER * wk;
   float sum[MT][PER];
+  if constexpr (A_LDS) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the last rows have been read
   // lanes whose row is past M carry nothing: they stay out of the LDS traffic, of the
   // split-K exchange and of the final store
 #pragma unroll

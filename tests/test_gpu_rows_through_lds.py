@@ -60,3 +60,18 @@ def test_arrangements_against_the_oracle(variant, M):
         B.qg_set_knob(1, splitk)
         B.qg_set_knob(3, variant)
         assert_c_close(P.gpu_c(), P.oracle_c(), f"{P.case.name} {splitk}")
+
+
+@pytest.mark.parametrize("variant,M,workgroups", [
+    (14, 16, 5), (14, 3, 9), (15, 13, 13), (15, 16, 9), (16, 16, 5), (16, 1, 13), (26, 20, 13), (26, 32, 9), (36, 40, 5), (46, 64, 9),
+    (10, 16, 5), (12, 16, 3), (21, 27, 5), (31, 33, 5), (41, 64, 5)])
+def test_long_k_whole(variant, M, workgroups):
+    """More chunks than a wavefront has in flight, an odd number of them (41): every chunk's rows pass through the same part of
+    LDS.  Several strips per workgroup, K longer than 32 chunks: strips dealt to XCDs in runs, workgroup counts that eight does not divide."""
+    from paper_2504_12984_amd import binding as B
+    strips = {14: 2, 15: 2, 16: 4, 26: 2, 36: 2, 46: 2}.get(variant, 1)
+    P = Prepared(WL.Case(f"long_{variant}_{M}", M, 128 * 41, 64 * strips * workgroups, WL.KIND_UINT, 4 if variant % 2 else 3, group=64 if M % 3 == 0 else 128,
+                         zero="random", zero_hi=7, act="bf16" if M % 2 else "f16", scale_dtype="f16", seed=54100 + variant + M))
+    B.qg_set_knob(1, 1)
+    B.qg_set_knob(3, variant)
+    assert_c_close(P.gpu_c(), P.oracle_c(), P.case.name)
