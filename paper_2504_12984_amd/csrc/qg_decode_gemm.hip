@@ -86,12 +86,13 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
   // then share lines of scales and zero-points in.  Reading the weights alone, K = 8192, N = 28672, 4 bits, takes 18.3 us
   // this way and 19.9 dealt out in turn; the kernel, M = 1, u4 24.6 -> 23.8.  (One strip per workgroup, or split
   // K: up to 4 % longer; K <= 4096: u5, K = 2048, N = 30720 9.2 -> 9.5.)
+  // (Chosen without a branch, and the workgroups counted from N: behind a branch, or with the grid's size from the launch, the
+  // kernel's arguments come in two trips instead of one.  M = 1, u4, K = 1024, N = 32768 6.08 us with the branch, 5.93 now.)
   int group = blockIdx.x;
-  if constexpr (NS > 1)
-    if (p.splitk == 1 && KC > 32) {
-      const int x = group & 7, each = (int)gridDim.x >> 3;
-      group = x * each + min(x, (int)gridDim.x & 7) + (group >> 3);
-    }
+  if constexpr (NS > 1) {
+    const int x = group & 7, groups = NCH / NS, run = x * (groups >> 3) + min(x, groups & 7) + (group >> 3);
+    group = (p.splitk == 1 && KC > 32) ? run : group;
+  }
   const int nc = group * NS + ws;
   const int c0 = split * p.chunks_per_split;
   const int c1 = min(KC, c0 + p.chunks_per_split);
