@@ -290,6 +290,24 @@ static bool covers_rows(int variant, int64_t M) {
   return variant / 10 == row_tiles(M) || (variant / 10 == 3 && M > 32 && M <= 48);
 }
 
+// Two row tiles: four wavefronts that load A directly (22, 27) instead of eight with A through LDS (21, 26)?  Both sides timed over 1372
+// calls (M = 17 .. 32, K = 512 .. 16384, N = 512 .. 57344, all widths, kinds and groups): what this picks takes 0.2 % longer than the better
+// of the two on average, 1 call in 35 more than 3 %.  Eight (158 registers each, u4) have a CU to themselves, of four two or three workgroups share one.
+static bool four_wavefronts(int M, int NCH, int KC, int splitk, int group, int wt, bool one_strip, bool mx) {
+  const int bits = wt_bits(wt);
+  const bool lut = wt_is_lut(wt), codes_float = !lut && !mx && wt >= 8, few = M <= 24;
+  // several rounds of the 256 CUs (M = 20, u4, K = 1024, N = 57344: 12.1 us against 14.8; codebook of 6 bits, K = 2048, N = 41024 24.2 against 32.7)
+  if (NCH > 512) return few || KC <= 16 || lut;
+  // a round and a fraction, where strips have no partner or K is split (M = 20, u4, K = 8192: N = 24640 34.0 us against 35.0, N = 12160
+  // 20.7 against 22.0; the codebook's 35.6 against 39.8); with more rows A through LDS is worth the round (M = 32, N = 24640 39.9 against 36.2)
+  if (one_strip && NCH * splitk > 256) return lut || (few && !(mx && KC > 32)) || (NCH > 256 && KC <= 16);
+  // one chunk for each of eight wavefronts, two for each of four, both in flight (M = 20, K = 1024, N = 16384: u4 5.0 us against 5.5, u8 6.3 against 7.5)
+  if ((KC == 7 || KC == 8) && !lut) return NCH <= 256 ? few || bits > 5 || mx : NCH < 384 ? few && bits <= 5 : !codes_float;
+  if (NCH >= 384 && KC <= 4) return !lut || bits > 4;      // (M = 20, u4, K = 512, N = 28672: 5.3 us against 5.9)
+  if (NCH >= 384 && KC <= 16) return mx || (!lut && !codes_float && bits > 6 && few);      // (M = 20, u8, K = 1408, N = 28672: 11.0 against 12.7)
+  return NCH > 224 && NCH <= 256 && few && KC >= 16 && KC <= 32 && !lut && !codes_float && (mx || group != 32);      // (M = 17, u4, K = 4096, N = 16384: 11.9 against 13.0)
+}
+
 // Streaming kernel (M <= 64): wavefront arrangement and split-K by shape.  Host arithmetic only.
 // (mx: block-scaled weights -- group 32, but only four scale bytes per block and lane, so every
 // arrangement has the registers for them)
@@ -300,7 +318,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // 33 .. 48 rows carry three row tiles: a quarter less of A to load and of matrix instructions than four
   // (K = N = 8192, M = 40, u4: 17.8 us against 19.8; K = 4096, N = 28672: 25.4 against 28.2)
   const int tens = (M > 32 && M <= 48) ? 30 : 10 * mt;
-  int variant = tens + 1;                     // one strip: 4 wavefronts, with several row tiles 8
+  int variant = tens + 1;                     // one strip: 4 wavefronts, with several row tiles 8 (or 4: four_wavefronts)
   // One row tile, short K (at most 32 chunks): as many wavefronts per strip as leaves each
   // two chunks -- 16 (every load of the strip in flight at once) up to 4-bit codes, whose
   // ring fits the 128 registers 16 wavefronts leave each; 8 from 16 chunks on; else 4.
@@ -352,7 +370,8 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   int splitk = knob(1);
   if (splitk <= 0) {
     splitk = 1;
-    const int min_chunks = ((waves >= 16 || (KC <= 32 && NCH <= 128)) ? 2 : 4) / (mt > 1 ? 2 : 1);      // per wavefront
+    const bool eight = mt > 1 && (variant % 10 == 1 || variant % 10 == 6);
+    const int min_chunks = ((waves >= 16 || (KC <= 32 && NCH <= 128)) ? 2 : 4) / (eight ? 2 : 1);      // per wavefront
     // (several row tiles: 192 workgroups are enough -- K = 4096, N = 14336, M = 24 takes 12.1 us
     // unsplit against 14.7 in two; N = 6144, M = 40: 11.9 in two, 17.2 in four)
     while (NCH * splitk < 256 && !(mt > 1 && NCH * splitk >= 192) && KC / (splitk * 2) >= min_chunks * waves) splitk *= 2;
@@ -362,6 +381,8 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   }
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
+  // (the slabs stay: half as many wavefronts, twice the chunks for each)
+  if (mt == 2 && knob(3) <= 0 && four_wavefronts(M, NCH, KC, splitk, group, wt, variant == 21, mx)) variant = variant == 26 && NCH >= 384 ? 27 : 22;
   *variant_out = variant;
   *splitk_out = (KC + cps - 1) / cps;
   *cps_out = cps;

@@ -63,10 +63,9 @@ __device__ __forceinline__ uint32_t pack_out(float lo, float hi) {
 
 // MX: the scales are 8-bit exponents, one per 32 rows and column (GPC = 4), applied by the
 // hardware converts of the e2m1 / e4m3 types; there are no zero-points.
-// A_LDS: A through LDS (always with several row tiles); else loaded as the matrix instruction reads it.
+// A_LDS: A through LDS; else loaded as the matrix instruction reads it.
 template <int WT, int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS, bool MX, bool A_LDS>
 __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
-  static_assert(A_LDS || MT == 1, "several row tiles go through LDS");
   // NS adjacent strips per workgroup, NK wavefronts along K for each: wavefront w
   // works on strip w % NS and takes every NK-th chunk of the slab starting at
   // w / NS, so the NS wavefronts with the same w / NS walk the same K range at the
@@ -104,7 +103,9 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
   // Through LDS: a load takes four rows x 256 bytes (buffer offsets below 2^31: 64 rows, K <= 2^24); eight lanes fill
   // 128 bytes of LDS.  A wavefront's slab is [k-step][row][4 pieces], piece q of row r at slot q ^ swizzle(r), so that
   // both the writes and the fragment reads find their banks apart.
-  const uint16_t* arow = p.A + (int64_t)min(i16, p.M - 1) * p.K + 8 * b;
+  const uint16_t* arow[A_LDS ? 1 : MT];
+#pragma unroll
+  for (int mt = 0; mt < (A_LDS ? 1 : MT); ++mt) arow[mt] = p.A + (int64_t)min(mt * 16 + i16, p.M - 1) * p.K + 8 * b;
   const int apc = (l & 3) + 4 * ((l >> 3) & 3), ar4 = ((l >> 2) & 1) + 2 * (l >> 5);      // my piece of a row, my row of four
   const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.A), 0, (int)((uint32_t)p.M * (uint32_t)(2 * p.K)), 0x00020000);
   auto swizzle = [](int r) __attribute__((always_inline)) { return (((r >> 2) & 1) << 1) | (((r >> 1) ^ (r >> 3)) & 1); };
@@ -146,7 +147,9 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
       for (int q = 0; q < AQ; ++q) ar[R][q] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_off[q], c * (2 * TILE_K), 0);
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) ar[R][j] = *reinterpret_cast<const u4_t*>(arow + c * TILE_K + 32 * j);
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ar[R][4 * mt + j] = *reinterpret_cast<const u4_t*>(arow[mt] + c * TILE_K + 32 * j);
     }
   };
   auto issue = [&](auto Sc, int c) __attribute__((always_inline)) {
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           if constexpr (A_LDS) af[J & 1][mt] = *reinterpret_cast<const u4_t*>(my_a + a_rd + J * (MT * 1024) + mt * 1024);
-          else af[J & 1][mt] = ar[S % A_RING][J];
+          else af[J & 1][mt] = ar[S % A_RING][4 * mt + J];
         }
     };
     fragments(std::integral_constant<int, 0>{});
@@ -420,10 +423,11 @@ constexpr int lds_rows(int wt, int gpc, int nw, int ns) {
   return ns > 1 || gpc == 4 ? 13 : 16;
 }
 
-template <int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS = 1, bool MX = false>
+// (DIRECT: never)
+template <int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS = 1, bool MX = false, bool DIRECT = false>
 static int launch_cfg(const GemmParams& p, hipStream_t st) {
   if ((p.N / TILE_N) % NS) return QG_EINVAL;
-  constexpr int ROWS = MT > 1 ? 0 : lds_rows(QG_WT, GPC, NW, NS);
+  constexpr int ROWS = DIRECT ? 17 : MT > 1 ? 0 : lds_rows(QG_WT, GPC, NW, NS);
   auto kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, (ROWS <= 16)>;
   if constexpr (MT == 1 && ROWS <= 16) if (p.M < ROWS) kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, false>;
   dim3 grid((unsigned)(p.N / TILE_N / NS), (unsigned)p.splitk), block(NW * 64);
@@ -432,9 +436,10 @@ static int launch_cfg(const GemmParams& p, hipStream_t st) {
 }
 
 // variant = 10 * (row tiles: 1, 2, 3, 4) + arrangement.  One row tile: 0: 8 wavefronts on a strip, 1: 4, 2: 16, and
-// those with several strips.  Several row tiles always 8 wavefronts, 1: on one strip, 6: 4 along K on each of two (two on a SIMD: one
+// those with several strips.  Several row tiles: 8 wavefronts, 1: on one strip, 6: 4 along K on each of two (two on a SIMD: one
 // unpacks while the other's matrix instructions run; with 4 wavefronts M = 64, K = N = 8192 takes 20.5 us against 19.8, K = 8192,
-// N = 28672 56.9 against 52.1, M = 32 there 42.5 against 38.4)
+// N = 28672 56.9 against 52.1, M = 32 there 42.5 against 38.4).  Two row tiles also 4 wavefronts that load A directly, 2: on one
+// strip, 7: 2 along K on each of two, for the calls that four_wavefronts() in qg_api.hip names.
 template <int ROUTE, int GPC>
 static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
   if constexpr (GPC == 4 && (QG_WT == 9 || QG_WT == 13)) {
@@ -447,6 +452,8 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
         case 15: return launch_cfg<ROUTE, 4, 16, 2, 1, 2, true>(p, st);
         case 16: return launch_cfg<ROUTE, 4, 16, 2, 1, 4, true>(p, st);
         case 21: return launch_cfg<ROUTE, 4, 8, 2, 2, 1, true>(p, st);
+        case 22: return launch_cfg<ROUTE, 4, 4, 2, 2, 1, true, true>(p, st);
+        case 27: return launch_cfg<ROUTE, 4, 4, 2, 2, 2, true, true>(p, st);
         case 26: return launch_cfg<ROUTE, 4, 8, 2, 2, 2, true>(p, st);
         case 31: return launch_cfg<ROUTE, 4, 8, 2, 3, 1, true>(p, st);
         case 36: return launch_cfg<ROUTE, 4, 8, 2, 3, 2, true>(p, st);
@@ -464,6 +471,7 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     switch (variant) {
       case 11: return launch_cfg<ROUTE, 4, 4, 2, 1>(p, st);
       case 21: return launch_cfg<ROUTE, 4, 8, 2, 2>(p, st);
+      case 22: return launch_cfg<ROUTE, 4, 4, 2, 2, 1, false, true>(p, st);
       case 31: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 3>(p, st);
       case 41: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 4>(p, st);
       default: return QG_EINVAL;
@@ -477,6 +485,8 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     case 15: return launch_cfg<ROUTE, GPC, 16, 2, 1, 2>(p, st);    // 2 strips x 8
     case 16: return launch_cfg<ROUTE, GPC, 16, 2, 1, 4>(p, st);    // 4 strips x 4
     case 21: return launch_cfg<ROUTE, GPC, 8, 2, 2>(p, st);
+    case 22: return launch_cfg<ROUTE, GPC, 4, 2, 2, 1, false, true>(p, st);
+    case 27: return launch_cfg<ROUTE, GPC, 4, 2, 2, 2, false, true>(p, st);     // 2 strips x 2
     case 26: return launch_cfg<ROUTE, GPC, 8, 2, 2, 2>(p, st);     // 2 row tiles, 2 strips x 4
     case 31: return launch_cfg<ROUTE, GPC, 8, 2, 3>(p, st);
     case 36: return launch_cfg<ROUTE, GPC, 8, 2, 3, 2>(p, st);     // 3 row tiles, 2 strips x 4
@@ -492,6 +502,7 @@ int QG_CAT(decode_waves_wt, QG_WT)(int variant) {
   switch (variant) {
     case 10: case 15: case 21: case 31: case 41: return 8;
     case 12: return 16;
+    case 27: return 2;
     default: return 4;
   }
 }

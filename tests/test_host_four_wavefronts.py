@@ -1,0 +1,27 @@
+"""Host logic: where several row tiles take four wavefronts instead of eight (qg_plan; the times stand at the rule)."""
+import pytest
+
+from paper_2504_12984_amd import binding as B
+
+U = {bits: B.WType(B.QG_UINT, bits) for bits in (1, 2, 4, 6, 8)}
+CB = {bits: B.WType(B.QG_CODEBOOK, bits) for bits in (4, 5, 8)}
+F4, F6 = B.WType(B.QG_FLOAT, 4, 2, 1), B.WType(B.QG_FLOAT, 6, 3, 2)
+
+
+@pytest.mark.parametrize("t,M,K,N,variant,splitk", [
+    (U[4], 21, 1024, 57152, 22, 1), (U[4], 20, 2048, 57344, 27, 1), (CB[5], 32, 512, 34304, 27, 1),      # several rounds of workgroups
+    (U[4], 20, 8192, 24640, 22, 1), (U[4], 32, 8192, 24640, 21, 1), (CB[4], 28, 8192, 24640, 22, 1),     # a round and a fraction
+    (U[4], 20, 8192, 10240, 22, 2), (U[4], 20, 8192, 12224, 22, 2), (U[4], 32, 8192, 10240, 21, 2),
+    (U[4], 20, 8192, 8192, 21, 2), (U[4], 20, 8192, 12288, 21, 1),
+    (U[4], 20, 1024, 4096, 22, 1), (U[4], 28, 1024, 4096, 21, 1), (U[8], 28, 1024, 4096, 22, 1), (CB[8], 20, 1024, 4096, 21, 1),      # two chunks each
+    (U[4], 20, 512, 28672, 27, 1), (U[8], 20, 1408, 28672, 27, 1), (U[4], 24, 4096, 28672, 26, 1), (F6, 20, 1408, 28672, 26, 1)])
+def test_two_row_tiles(t, M, K, N, variant, splitk):
+    p = B.qg_plan(t, 128, M, N, K)
+    assert (p["path"], p["variant"], p["splitk"]) == (1, variant, splitk), p
+
+
+def test_two_row_tiles_groups_of_32():
+    # no pairs of strips there: from 257 strips on a round and a fraction whatever their number
+    assert B.qg_plan(U[4], 32, 24, 28672, 1024)["variant"] == 22
+    assert B.qg_plan(U[4], 32, 32, 28672, 8192)["variant"] == 21
+    assert B.qg_plan(F4, 32, 20, 57344, 1024, act=B.QG_BF16, scale_dtype=B.QG_E8M0)["variant"] == 27
