@@ -39,8 +39,8 @@ extern "C" {
  *           layout only)
  *   knob 3: wavefront arrangement of the streaming kernel, 10 * row tiles + a digit.  One row tile:
  *           10 / 11 / 12 are 8 / 4 / 16 wavefronts on one strip, 14 / 15 are 8 / 16 on 2 adjacent strips, 16 is
- *           16 on 4.  Several: 21, 31, 41 are 8 wavefronts on one strip, 26, 36, 46 are 8 on 2; 22 and 27
- *           are 4 on one strip and on 2.  Its row tiles
+ *           16 on 4.  Several: 21, 31, 41 are 8 wavefronts on one strip, 26, 36, 46 are 8 on 2; 22, 32, 42
+ *           are 4 on one strip, 27, 37, 47 4 on 2.  Group 32 with 16-bit scales takes no forced one.  Its row tiles
  *           must be the ones M needs (1 up to 16 rows, 2 up to 32, 3 up to 48, 4 from 33 to 64), else QG_EINVAL.
  * Knobs 0, 1 and 3 apply to QG_LAYOUT_TILE128x64 only. */
 QG_API int qg_set_knob(int knob, int value);

@@ -290,11 +290,31 @@ static bool covers_rows(int variant, int64_t M) {
   return variant / 10 == row_tiles(M) || (variant / 10 == 3 && M > 32 && M <= 48);
 }
 
-// Two row tiles: four wavefronts that load A directly (22, 27) instead of eight with A through LDS (21, 26)?  Both sides timed over 1372
+// Three and four row tiles, both with A through LDS (770 calls, M = 33 .. 64; times: eight wavefronts against four).
+static bool four_wavefronts_many(bool four_tiles, int NCH, int KC, int group, int wt, bool one_strip, bool mx) {
+  const int bits = wt_bits(wt);
+  const bool lut = wt_is_lut(wt), narrow_lut = lut && bits <= 4;
+  // four groups' constants, or four row tiles, beside wide codes do not fit the registers of eight (8-bit integers, four row tiles spill 36 to 60
+  // bytes a lane: M = 64, K = 2048, N = 16384 15.1 us against 13.5, group 64, K = 1024, N = 14336 11.6 against 8.7; group 32, K = N = 8192 39.2 against 29.4)
+  if (group == 32 && !mx && bits > 5) return true;
+  if (four_tiles && bits == 8 && wt < 8) return true;
+  if (one_strip) {
+    if (narrow_lut) return !four_tiles && NCH > 256;      // (building the table costs what four leave: M = 40, K = 512, N = 24640 12.4 against 9.6)
+    // one chunk for each of eight, two for each of four (M = 33, u8, K = 1024, N = 16384 8.5 against 7.6); a round and a fraction, or all CUs just
+    // full (M = 33, u8, K = 1024, N = 24640 14.3 against 10.2; M = 40, u4, K = 2048, N = 16384 10.2 against 9.5)
+    return (KC <= 8 && (four_tiles || KC <= 4 || KC >= 7)) || (!four_tiles && (NCH > 256 || (NCH > 224 && !lut)));
+  }
+  // pairs of strips: short K (M = 52, 8-bit codebook, K = 1024, N = 32768 19.6 against 17.7; M = 40, e3m2, K = 512, N = 28672 8.2 against 7.3), several rounds
+  if (narrow_lut) return !four_tiles && NCH > 512;
+  return (NCH >= 384 && KC <= 4) || (four_tiles && lut && KC <= 8) || (!four_tiles && NCH > 512);
+}
+
+// Several row tiles: four wavefronts instead of eight?  Two row tiles: they load A directly (22, 27), eight through LDS (21, 26).  Both sides timed over 1372
 // calls (M = 17 .. 32, K = 512 .. 16384, N = 512 .. 57344, all widths, kinds and groups): what this picks takes 0.2 % longer than the better
 // of the two on average, 1 call in 35 more than 3 %.  Eight (158 registers each, u4) have a CU to themselves, of four two or three workgroups share one.
 static bool four_wavefronts(int M, int NCH, int KC, int splitk, int group, int wt, bool one_strip, bool mx) {
   const int bits = wt_bits(wt);
+  if (M > 32) return four_wavefronts_many(M > 48, NCH, KC, group, wt, one_strip, mx);
   const bool lut = wt_is_lut(wt), codes_float = !lut && !mx && wt >= 8, few = M <= 24;
   // several rounds of the 256 CUs (M = 20, u4, K = 1024, N = 57344: 12.1 us against 14.8; codebook of 6 bits, K = 2048, N = 41024 24.2 against 32.7)
   if (NCH > 512) return few || KC <= 16 || lut;
@@ -382,7 +402,8 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
   // (the slabs stay: half as many wavefronts, twice the chunks for each)
-  if (mt == 2 && knob(3) <= 0 && four_wavefronts(M, NCH, KC, splitk, group, wt, variant == 21, mx)) variant = variant == 26 && NCH >= 384 ? 27 : 22;
+  if (mt > 1 && (knob(3) <= 0 || (group == 32 && !mx)) && four_wavefronts(M, NCH, KC, splitk, group, wt, variant == tens + 1, mx))
+    variant = variant == tens + 6 && (mt > 2 || NCH >= 384) ? tens + 7 : tens + 2;
   *variant_out = variant;
   *splitk_out = (KC + cps - 1) / cps;
   *cps_out = cps;

@@ -438,8 +438,8 @@ static int launch_cfg(const GemmParams& p, hipStream_t st) {
 // variant = 10 * (row tiles: 1, 2, 3, 4) + arrangement.  One row tile: 0: 8 wavefronts on a strip, 1: 4, 2: 16, and
 // those with several strips.  Several row tiles: 8 wavefronts, 1: on one strip, 6: 4 along K on each of two (two on a SIMD: one
 // unpacks while the other's matrix instructions run; with 4 wavefronts M = 64, K = N = 8192 takes 20.5 us against 19.8, K = 8192,
-// N = 28672 56.9 against 52.1, M = 32 there 42.5 against 38.4).  Two row tiles also 4 wavefronts that load A directly, 2: on one
-// strip, 7: 2 along K on each of two, for the calls that four_wavefronts() in qg_api.hip names.
+// N = 28672 56.9 against 52.1, M = 32 there 42.5 against 38.4).  Also 4 wavefronts, 2: on one strip, 7: 2 along K on each of
+// two, for the calls that four_wavefronts() in qg_api.hip names; two row tiles then load A directly.
 template <int ROUTE, int GPC>
 static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
   if constexpr (GPC == 4 && (QG_WT == 9 || QG_WT == 13)) {
@@ -456,24 +456,27 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
         case 27: return launch_cfg<ROUTE, 4, 4, 2, 2, 2, true, true>(p, st);
         case 26: return launch_cfg<ROUTE, 4, 8, 2, 2, 2, true>(p, st);
         case 31: return launch_cfg<ROUTE, 4, 8, 2, 3, 1, true>(p, st);
+        case 32: return launch_cfg<ROUTE, 4, 4, 2, 3, 1, true>(p, st);
         case 36: return launch_cfg<ROUTE, 4, 8, 2, 3, 2, true>(p, st);
+        case 37: return launch_cfg<ROUTE, 4, 4, 2, 3, 2, true>(p, st);
         case 46: return launch_cfg<ROUTE, 4, 8, 2, 4, 2, true>(p, st);
+        case 47: return launch_cfg<ROUTE, 4, 4, 2, 4, 2, true>(p, st);
         case 41: return launch_cfg<ROUTE, 4, 8, 2, 4, 1, true>(p, st);
+        case 42: return launch_cfg<ROUTE, 4, 4, 2, 4, 1, true>(p, st);
         default: return QG_EINVAL;
       }
     }
   }
   if (p.scale_e8m0) return QG_EUNSUPPORTED;
-  if constexpr (GPC == 4) {          // group size 32: the one-strip arrangement with the fewest wavefronts only
-    // wide codes, four groups' constants and three or four row tiles do not fit the registers of eight wavefronts
-    // (u8, M = 64, K = N = 8192: 39.2 us against 29.4 with four)
-    constexpr int G32_WAVES = wt_bits(QG_WT) > 5 ? 4 : 8;
+  if constexpr (GPC == 4) {          // group size 32: the one-strip arrangements only
     switch (variant) {
       case 11: return launch_cfg<ROUTE, 4, 4, 2, 1>(p, st);
       case 21: return launch_cfg<ROUTE, 4, 8, 2, 2>(p, st);
       case 22: return launch_cfg<ROUTE, 4, 4, 2, 2, 1, false, true>(p, st);
-      case 31: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 3>(p, st);
-      case 41: return launch_cfg<ROUTE, 4, G32_WAVES, 2, 4>(p, st);
+      case 32: return launch_cfg<ROUTE, 4, 4, 2, 3>(p, st);
+      case 42: return launch_cfg<ROUTE, 4, 4, 2, 4>(p, st);
+      case 31: if constexpr (wt_bits(QG_WT) <= 5) return launch_cfg<ROUTE, 4, 8, 2, 3>(p, st); else return QG_EINVAL;
+      case 41: if constexpr (wt_bits(QG_WT) <= 5) return launch_cfg<ROUTE, 4, 8, 2, 4>(p, st); else return QG_EINVAL;
       default: return QG_EINVAL;
     }
   } else {
@@ -489,8 +492,12 @@ static int launch_variant(const GemmParams& p, int variant, hipStream_t st) {
     case 27: return launch_cfg<ROUTE, GPC, 4, 2, 2, 2, false, true>(p, st);     // 2 strips x 2
     case 26: return launch_cfg<ROUTE, GPC, 8, 2, 2, 2>(p, st);     // 2 row tiles, 2 strips x 4
     case 31: return launch_cfg<ROUTE, GPC, 8, 2, 3>(p, st);
+    case 32: return launch_cfg<ROUTE, GPC, 4, 2, 3>(p, st);
     case 36: return launch_cfg<ROUTE, GPC, 8, 2, 3, 2>(p, st);     // 3 row tiles, 2 strips x 4
+    case 37: return launch_cfg<ROUTE, GPC, 4, 2, 3, 2>(p, st);
+    case 42: return launch_cfg<ROUTE, GPC, 4, 2, 4>(p, st);
     case 46: return launch_cfg<ROUTE, GPC, 8, 2, 4, 2>(p, st);     // 4 row tiles, 2 strips x 4
+    case 47: return launch_cfg<ROUTE, GPC, 4, 2, 4, 2>(p, st);
     case 41: return launch_cfg<ROUTE, GPC, 8, 2, 4>(p, st);
     default: return QG_EINVAL;
   }
@@ -502,7 +509,7 @@ int QG_CAT(decode_waves_wt, QG_WT)(int variant) {
   switch (variant) {
     case 10: case 15: case 21: case 31: case 41: return 8;
     case 12: return 16;
-    case 27: return 2;
+    case 27: case 37: case 47: return 2;
     default: return 4;
   }
 }

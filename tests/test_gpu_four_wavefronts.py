@@ -21,7 +21,7 @@ def _case(name, M, K, N, i, kind=WL.KIND_UINT, bits=4, group=128):
     return Prepared(WL.Case(name, M, K, N, kind, bits, group=group, act="bf16" if i % 2 else "f16", scale_dtype="f16", seed=55000 + i, **zero))
 
 
-@pytest.mark.parametrize("variant,M", [(22, 17), (22, 24), (22, 32), (27, 18), (27, 31)])
+@pytest.mark.parametrize("variant,M", [(22, 17), (22, 24), (22, 32), (27, 18), (27, 31), (32, 33), (37, 48), (42, 49), (47, 64)])
 @pytest.mark.parametrize("K,bits,group", [(256, 4, 128), (1024, 8, 64), (1408, 3, 128), (3712, 5, 64)])
 def test_arrangements(variant, M, K, bits, group):
     from paper_2504_12984_amd import binding as B
@@ -34,9 +34,11 @@ def test_arrangements(variant, M, K, bits, group):
 
 
 @pytest.mark.parametrize("M,K,N,bits,group", [(20, 512, 33472, 4, 128), (17, 1024, 4096, 4, 32), (24, 1024, 16384, 8, 64), (18, 4096, 8256, 4, 128),
-                                              (32, 1024, 33408, 6, 128), (20, 512, 24576, 3, 64)])
+                                              (32, 1024, 33408, 6, 128), (20, 512, 24576, 3, 64),
+                                              (33, 1024, 2048, 4, 128), (48, 512, 24576, 4, 64), (64, 2048, 2048, 8, 128), (49, 512, 18432, 8, 64),
+                                              (45, 1408, 512, 6, 32), (63, 1024, 320, 8, 32)])
 def test_automatic_choice(M, K, N, bits, group):
     from paper_2504_12984_amd import binding as B
     P = _case(f"four_auto_{M}_{K}_{N}", M, K, N, M + bits, bits=bits, group=group)
-    assert B.qg_plan(P.wtype, group, M, N, K)["variant"] in (22, 27)
+    assert B.qg_plan(P.wtype, group, M, N, K)["variant"] in (22, 27, 32, 37, 42, 47)
     assert_c_close(P.gpu_c(), P.oracle_c(), P.case.name)

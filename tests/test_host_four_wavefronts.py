@@ -25,3 +25,14 @@ def test_two_row_tiles_groups_of_32():
     assert B.qg_plan(U[4], 32, 24, 28672, 1024)["variant"] == 22
     assert B.qg_plan(U[4], 32, 32, 28672, 8192)["variant"] == 21
     assert B.qg_plan(F4, 32, 20, 57344, 1024, act=B.QG_BF16, scale_dtype=B.QG_E8M0)["variant"] == 27
+
+
+@pytest.mark.parametrize("t,group,M,K,N,variant", [
+    (U[8], 128, 64, 2048, 2048, 42), (U[8], 64, 49, 512, 18432, 47), (U[6], 128, 64, 8192, 4096, 41),      # registers
+    (U[6], 32, 40, 4096, 2048, 32), (U[8], 32, 64, 1024, 8192, 42), (U[4], 32, 64, 4096, 2048, 41),
+    (U[4], 128, 33, 1024, 8192, 32), (U[4], 128, 33, 768, 8192, 31), (CB[4], 128, 40, 1024, 8192, 31), (CB[8], 128, 52, 1024, 16384, 42),      # two chunks each
+    (U[8], 128, 33, 512, 24640, 32), (CB[4], 128, 40, 512, 24640, 32), (CB[4], 128, 52, 512, 24640, 41), (F6, 128, 40, 2048, 16384, 32),      # a round and a fraction, all CUs
+    (F6, 128, 40, 512, 28672, 37), (CB[8], 128, 52, 1024, 16512, 47), (F6, 128, 40, 512, 18432, 36)])                     # pairs of strips
+def test_three_and_four_row_tiles(t, group, M, K, N, variant):
+    p = B.qg_plan(t, group, M, N, K)
+    assert (p["path"], p["variant"]) == (1, variant), p
