@@ -418,9 +418,17 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(GemmParams p) {
 // K = N = 8192 13.3 -> 14.0).  16 wavefronts on one strip have half a chunk each at a time and nothing to hide the way behind
 // (K = 4096, N = 14336, u3 8.6 -> 8.8); above 4 bits their registers do not hold it (f6, bf16, N = 28672 39 -> 49); and
 // codebook lookups keep LDS busy already (4 bits, M = 16, N = 28672: two layers 59.5 -> 60.0).
+// Four strips from 16 rows on (int4, M = 13, K = 2048, N = 57344 15.9 -> 17.1).
 constexpr int lds_rows(int wt, int gpc, int nw, int ns) {
   if (wt_is_lut(wt) || (nw == 16 && (ns == 1 || wt_bits(wt) > 4)) || (ns == 1 && gpc < 4 && (nw == 4 || wt_natural(wt)))) return 17;
-  return ns > 1 || gpc == 4 ? 13 : 16;
+  return (ns > 1 && ns < 4) || gpc == 4 ? 13 : 16;
+}
+
+// Wavefronts with two chunks each have both in flight when A is loaded directly, and only the first one's rows on the way through LDS.
+// Where the unpack is short enough for that to show they load it directly (16 rows: u4, K = 4096, N = 8192 6.9 us against 7.5, e2m2 8.1 against 8.9;
+// u6, K = 2048, N = 16384 7.3 against 7.8; int3, K = 1024, N = 28672, two strips 6.1 against 6.7; u8, K = N = 4096 7.8 against 7.3, so not there).
+constexpr bool two_chunks_direct(int wt, int nw, int ns, bool mx) {
+  return !mx && (wt_bits(wt) <= 5 || (ns == 1 && nw == 8 && (wt_bits(wt) == 6 || wt >= 8)));
 }
 
 // (DIRECT: never)
@@ -429,7 +437,8 @@ static int launch_cfg(const GemmParams& p, hipStream_t st) {
   if ((p.N / TILE_N) % NS) return QG_EINVAL;
   constexpr int ROWS = DIRECT ? 17 : MT > 1 ? 0 : lds_rows(QG_WT, GPC, NW, NS);
   auto kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, (ROWS <= 16)>;
-  if constexpr (MT == 1 && ROWS <= 16) if (p.M < ROWS) kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, false>;
+  if constexpr (MT == 1 && ROWS <= 16)
+    if (p.M < ROWS || (two_chunks_direct(QG_WT, NW, NS, MX) && p.chunks_per_split > NW / NS && p.chunks_per_split <= 2 * (NW / NS))) kern = decode_kernel<QG_WT, ROUTE, GPC, NW, DEPTH, MT, NS, MX, false>;
   dim3 grid((unsigned)(p.N / TILE_N / NS), (unsigned)p.splitk), block(NW * 64);
   hipLaunchKernelGGL(kern, grid, block, 0, st, p);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
