@@ -456,17 +456,20 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // N = 2048 .. 28672, M = 24 .. 1000 at 3, 4, 6 and 8 bits, its constants to the exchange as it is now: u4, K = 2048 .. 14336,
 // N = 4096 .. 28672, M = 65 .. 768 (70 cases): what it picks takes 0.4 % longer than the best candidate on average and 5 % at most; with
 // the constants from before the counters had lines of their own 2.2 % and 15 % (M = 200, K = 5120, N = 13824 44.1 -> 38.3 us,
-// M = 300, K = N = 4096 23.3 -> 21.5).
+// M = 300, K = N = 4096 23.3 -> 21.5).  Three slabs that meet in the kernel cost 0.8 us more for every 64 rows of a tile, which its last wavefronts
+// read twice: without that they were picked too often on short K, which those cases lack (829 calls of all kinds and widths, K = 512 .. 16384, N = 512 .. 28672,
+// M = 65 .. 1000, every candidate timed: 1.05 % longer than the best on average, 1.27 without; M = 112, K = 3072, N = 11008, u4 24.9 us in three
+// slabs of 128 rows, 20.4 in two of 64; M = 929, K = 2304, N = 2112 24.4 against 20.4 whole; M = 93, K = 2944, N = 11072, int2, group 32 26.6 against 20.9).
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
 // hardware convert) + 1.2 per slab.  That fit is older than the kernel's present exchange: the 1.2 is what reading
 // the slabs back one pair after the other cost, where up to LARGE_MEET slabs now meet and more have a second kernel.
-struct TiledFit { double start, alone64, pair64, alone128, pair128, meet, meet_mb, many, many_mb; };
-static constexpr TiledFit TILED_FIT = {3.9, 0.99, 1.66, 1.32, 2.86, 3.6, 0.26, 2.6, 0.42};
+struct TiledFit { double start, alone64, pair64, alone128, pair128, meet, meet_mb, many, many_mb, third; };
+static constexpr TiledFit TILED_FIT = {3.9, 0.99, 1.66, 1.32, 2.86, 3.6, 0.26, 2.6, 0.42, 0.8};
 // The first fit.  It settles which calls can do without a workspace (under capture, or without memory): one that it leaves whole
 // has always been served there, and is served whole there still if the fit of today splits it.
-static constexpr TiledFit TILED_FIT_WHOLE = {4.0, 0.95, 1.65, 1.30, 2.6, 4.0, 0.385, 3.0, 0.335};
+static constexpr TiledFit TILED_FIT_WHOLE = {4.0, 0.95, 1.65, 1.30, 2.6, 4.0, 0.385, 3.0, 0.335, 0.0};
 
 static double tiled_cost(const TiledFit& f, int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
   const int over = t.bits > 4 ? t.bits - 4 : 0;
@@ -478,7 +481,8 @@ static double tiled_cost(const TiledFit& f, int bm, int sk, int cps, int64_t M, 
   const double loop = cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
   const double read = 0.19e-6 * (double)K * (double)N * t.bits / 8.0;       // the weights from memory
   const double mb = (double)sk * (double)M * (double)N * 4.0e-6;            // partial sums
-  return f.start + std::max(loop, read) + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? f.meet + f.meet_mb * mb : f.many + f.many_mb * mb);
+  const double third = sk == 3 ? f.third * (double)M / (64.0 * (double)((M + bm - 1) / bm)) : 0.0;
+  return f.start + std::max(loop, read) + third + (sk == 1 ? 0.0 : sk <= LARGE_MEET ? f.meet + f.meet_mb * mb : f.many + f.many_mb * mb);
 }
 
 // The cheapest tile height and split-K under a fit (more than 64 rows whose 128-row tiles leave half of the CUs idle); its cost.
