@@ -460,21 +460,23 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
 // read twice: without that they were picked too often on short K, which those cases lack (829 calls of all kinds and widths, K = 512 .. 16384, N = 512 .. 28672,
 // M = 65 .. 1000, every candidate timed: 1.05 % longer than the best on average, 1.27 without; M = 112, K = 3072, N = 11008, u4 24.9 us in three
 // slabs of 128 rows, 20.4 in two of 64; M = 929, K = 2304, N = 2112 24.4 against 20.4 whole; M = 93, K = 2944, N = 11072, int2, group 32 26.6 against 20.9).
+// Codebooks of more than 4 bits are looked up code by code, a chunk takes 1.9 of what u4 takes (98 calls: 0.2 % longer than the best on average, 1.5 with
+// the integer type's factor; 8 bits, M = 128, K = 4096, N = 14336 41.3 us in two slabs, 38.6 in four).
 // Up to 64 rows (one 64-row tile per column tile) a fit of its own, to K = 4096 .. 28672,
 // N = 4096 .. 28672 at 4, 6 and 8 bits: 6 + chunks per workgroup x (1.41 + 0.11 per bit
 // above 4; float codes, whose unpack is longer: 1.6 + 0.41 per bit above 4, + 0.4 without a
 // hardware convert) + 1.2 per slab.  That fit is older than the kernel's present exchange: the 1.2 is what reading
 // the slabs back one pair after the other cost, where up to LARGE_MEET slabs now meet and more have a second kernel.
-struct TiledFit { double start, alone64, pair64, alone128, pair128, meet, meet_mb, many, many_mb, third; };
-static constexpr TiledFit TILED_FIT = {3.9, 0.99, 1.66, 1.32, 2.86, 3.6, 0.26, 2.6, 0.42, 0.8};
+struct TiledFit { double start, alone64, pair64, alone128, pair128, meet, meet_mb, many, many_mb, third, lookup; };
+static constexpr TiledFit TILED_FIT = {3.9, 0.99, 1.66, 1.32, 2.86, 3.6, 0.26, 2.6, 0.42, 0.8, 1.9};
 // The first fit.  It settles which calls can do without a workspace (under capture, or without memory): one that it leaves whole
 // has always been served there, and is served whole there still if the fit of today splits it.
-static constexpr TiledFit TILED_FIT_WHOLE = {4.0, 0.95, 1.65, 1.30, 2.6, 4.0, 0.385, 3.0, 0.335, 0.0};
+static constexpr TiledFit TILED_FIT_WHOLE = {4.0, 0.95, 1.65, 1.30, 2.6, 4.0, 0.385, 3.0, 0.335, 0.0, 0.0};
 
 static double tiled_cost(const TiledFit& f, int bm, int sk, int cps, int64_t M, int64_t N, int64_t K, qg_wtype t) {
   const int over = t.bits > 4 ? t.bits - 4 : 0;
   const bool hw_convert = (t.bits == 4 || t.bits == 6 || t.bits == 8);      // e2m1, e3m2, e4m3
-  const double unpack = t.kind == QG_FLOAT ? (hw_convert ? 1.0 + 0.04 * over : 1.5) : 1.0 + 0.085 * over;
+  const double unpack = t.kind == QG_CODEBOOK && t.bits > 4 && f.lookup > 0.0 ? f.lookup : t.kind == QG_FLOAT ? (hw_convert ? 1.0 + 0.04 * over : 1.5) : 1.0 + 0.085 * over;
   // a chunk alone on a CU, and with a second workgroup there
   const double alone = unpack * (bm == 64 ? f.alone64 : f.alone128), pair = unpack * (bm == 64 ? f.pair64 : f.pair128);
   const int64_t n = ((M + bm - 1) / bm) * ((N + 255) / 256) * sk, full = n / 512, rest = n % 512;
@@ -538,11 +540,13 @@ static void plan_tiled(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm_out,
   *cps_out = cps;
 }
 
-// No workspace is to be had for a planned split: whether the call is one that runs whole then (see TILED_FIT_WHOLE), and its tile height.
+// No workspace is to be had for a planned split: whether the call is one that runs whole then, and its tile height: those that the
+// first fit leaves whole (see TILED_FIT_WHOLE), and codebooks where the integer type of the width is left whole.
 static bool tiled_runs_whole(int64_t M, int64_t N, int64_t K, qg_wtype t, int* bm) {
   if (knob(1) > 0 || knob(2) > 0 || M <= 64 || !large_prefers_64_rows(M, N)) return false;
   int splitk = 0;
   (void)best_tiled(TILED_FIT_WHOLE, M, N, K, t, bm, &splitk);
+  if (splitk > 1 && t.kind == QG_CODEBOOK) (void)best_tiled(TILED_FIT, M, N, K, qg_wtype{QG_UINT, t.bits, 0, 0}, bm, &splitk);
   return splitk == 1;
 }
 
