@@ -36,7 +36,7 @@ extern "C" {
  *           then takes its wavefronts per strip, 4 / 8, or 16 with M = 1)
  *   knob 1: forced split-K factor (streaming kernel; tiled kernel with 64- or 128-row tiles)
  *   knob 2: forced row-tile height of the tiled kernel (64 / 128 / 256; 64 on the first
- *           layout only)
+ *           layout only); of the int8 tiled kernel 64 or 128, other values leave its choice alone
  *   knob 3: wavefront arrangement of the streaming kernel, 10 * row tiles + a digit.  One row tile:
  *           10 / 11 / 12 are 8 / 4 / 16 wavefronts on one strip, 14 / 15 are 8 / 16 on 2 adjacent strips, 16 is
  *           16 on 4.  Several: 21, 31, 41 are 8 wavefronts on one strip, 26, 36, 46 are 8 on 2; 22, 32, 42

@@ -870,7 +870,7 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
   int splitk = 1, bm = 128;
   for (int cand = 64; cand <= 128; cand *= 2)
     for (int sk : {1, 2, 3, 4, 6, 8}) {
-      if (knob(2) > 0 && cand != knob(2)) continue;
+      if ((knob(2) == 64 || knob(2) == 128) && cand != knob(2)) continue;      // (no other height here: chosen as without)
       const int64_t tiles_m = (rows + cand - 1) / cand, tiles = tiles_m * ((N + 255) / 256);
       const int cps = (KC + sk - 1) / sk;
       const size_t part = (size_t)sk * tiles * (cand * 256 * sizeof(float));

@@ -115,3 +115,11 @@ def test_int8_calls_that_do_not_split_k_take_no_workspace(stub):
     assert len(calls[0]["malloc"]) == 1                       # this one splits K
     for c in calls[1:]:
         assert c["rc"] == 0 and c["malloc"] == [] and c["memset"] == [] and _kernels(c)[-1] == "a8_large_kernel", c
+
+
+def test_a_forced_height_that_int8_tiles_do_not_have_changes_nothing(stub):
+    calls = "[a8(M, K, N) for M, K, N in ((65, 8192, 28672), (300, 8192, 8192), (1000, 8192, 28672), (2000, 4096, 8192))]"
+    got = _run(stub, f"out = {calls}\nlib.qg_set_knob(2, 256)\nout += {calls}\nlib.qg_set_knob(2, 64)\nout += {calls}")
+    launches = [c["launches"] for c in got]
+    assert launches[:4] == launches[4:8] and all(_kernels(c) == ["a8_large_kernel"] for c in got[1:4])
+    assert all("Li64E" in n for c in got[9:] for _, n, _, _ in c["launches"])
