@@ -41,7 +41,9 @@
  *     once a call that splits K has run eagerly on the capture stream (nothing is
  *     allocated during a capture: QG_EHIP without that call); every launch leaves counters and
  *     workspace ready for the next, so a graph can be replayed any number of
- *     times.  qgemm_noalloc is the same call with no allocation at all.
+ *     times.  Where no workspace is to be had (a capture, no memory, more than 32 streams) calls with
+ *     more than 64 rows that gain little by splitting K run with K whole instead of failing
+ *     (qg_last_error() then still tells what was missing); which ones is left open.  qgemm_noalloc is the same call with no allocation at all.
  *
  * De-quantisation (the paper names the step but prints no formula; this is the
  * standard affine group form):

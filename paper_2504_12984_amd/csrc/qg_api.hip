@@ -96,7 +96,7 @@ static int hip_fail(hipError_t e, const char* what) {
 // ---- split-K workspace (partial sums + arrival counters) -----------------------------------
 // What the automatic plans can ask for is bounded: the streaming kernel splits K only while
 // strips x slabs stay below 512 (16 KiB of partial sums each at most), the tiled kernel only
-// while tiles x slabs stay within 256 (at most 128 x 256 fp32 each).  So every workspace has
+// while tiles x slabs stay within 256 (at most 128 x 256 fp32 each), the int8 one within 512 and this size.  So every workspace has
 // this one capacity; only forced split factors (the experiment knobs) can exceed it.
 constexpr size_t WS_PARTIAL_BYTES = size_t(32) << 20;
 // Behind them the slots in which the streaming kernel's slabs meet (up to two row tiles: 8 KiB per strip and
@@ -294,10 +294,12 @@ static bool covers_rows(int variant, int64_t M) {
 static bool four_wavefronts_many(bool four_tiles, int NCH, int KC, int group, int wt, bool one_strip, bool mx) {
   const int bits = wt_bits(wt);
   const bool lut = wt_is_lut(wt), narrow_lut = lut && bits <= 4;
-  // four groups' constants, or four row tiles, beside wide codes do not fit the registers of eight (8-bit integers, four row tiles spill 36 to 60
-  // bytes a lane: M = 64, K = 2048, N = 16384 15.1 us against 13.5, group 64, K = 1024, N = 14336 11.6 against 8.7; group 32, K = N = 8192 39.2 against 29.4)
+  // four groups' constants, or four row tiles, beside wide codes do not fit the registers of eight (spilled bytes a lane, two groups a chunk, f16 / bf16
+  // activations: u8 60 / 60, u7 36 / 92, e4m3 36 / 28, with one 24 / 68, e3m2 16 / 36, u6 12 / 16, which is too little to matter with one.  M = 64:
+  // u8, K = 2048, N = 16384 15.1 us against 13.5, group 64, K = 1024, N = 14336 11.6 against 8.7; bf16, K = N = 8192: u7, group 64 29.7 against 24.7, e4m3 27.9
+  // against 23.3, e3m2 24.8 against 23.3; group 32, u8 39.2 against 29.4)
   if (group == 32 && !mx && bits > 5) return true;
-  if (four_tiles && bits == 8 && wt < 8) return true;
+  if (four_tiles && !lut && ((wt < 8 && bits + (group == 64 ? 1 : 0) >= 7) || wt == 11 || wt == 13)) return true;
   if (one_strip) {
     if (narrow_lut) return !four_tiles && NCH > 256;      // (building the table costs what four leave: M = 40, K = 512, N = 24640 12.4 against 9.6)
     // one chunk for each of eight, two for each of four (M = 33, u8, K = 1024, N = 16384 8.5 against 7.6); a round and a fraction, or all CUs just
@@ -380,7 +382,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
   // wavefronts at 3 bits; 8-bit codes: two strips x 4 wavefronts, 23.5 against 27.3)
   if (variant == 11 && KC > 32 && NCH > 128 && NCH < 256) variant = wt_bits(wt) <= 6 ? 10 : (NCH % 2 == 0 ? 14 : 11);
   if (knob(3) > 0) variant = knob(3);
-  if (group == 32 && !mx) variant = tens + 1;   // four groups per chunk: one strip, the fewest wavefronts
+  if (group == 32 && !mx) variant = tens + 1;   // four groups per chunk: one strip
   const int waves = kDecodeWaves[wt_is_lut(wt) ? 0 : wt](variant);      // the same map for every type
   // Split K over workgroups only when the column strips alone cannot fill the
   // 256 CUs, and never below 4 chunks per wavefront (2 with 16 wavefronts per strip, or with a
@@ -575,9 +577,9 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
   // at N = 8192 -- while the tiled kernel shares A through LDS among four strips and splits K
   // instead; it wins on all but the small problems (K = 8192, N = 28672, M = 64, 6 bits:
   // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).  Up to 48 rows the
-  // streaming kernel carries three row tiles (0.92 of that).  The fits are older than the streaming kernel's way of A
-  // through LDS and the tiled kernel's exchange; where they put the line the two are close (u4, M = 64: K = N = 8192 18.4 here,
-  // 19.3 tiled in eight slabs; K = 8192, N = 28672 52.1 against 42.6), and the choice is kept as tested.
+  // streaming kernel carries three row tiles (0.92 of that).  Both fits are older than the kernels: the streaming estimate is 25.4 us
+  // at M = 45, K = N = 8192, u4, where 16.1 are measured.  What they choose (u4, M = 64): K = N = 8192 streaming, 18.4 us against 19.3 tiled in
+  // eight slabs; K = 8192, N = 28672 tiled, 42.6 against 52.1.  Between the two the line has not been fitted again.
   if (M > 32 && (double)K * (double)N >= 16.0e6 && knob(1) == 0 &&
       knob(2) == 0 && knob(3) == 0) {
     double tiled = 1e30;

@@ -42,3 +42,11 @@ def test_automatic_choice(M, K, N, bits, group):
     P = _case(f"four_auto_{M}_{K}_{N}", M, K, N, M + bits, bits=bits, group=group)
     assert B.qg_plan(P.wtype, group, M, N, K)["variant"] in (22, 27, 32, 37, 42, 47)
     assert_c_close(P.gpu_c(), P.oracle_c(), P.case.name)
+
+
+@pytest.mark.parametrize("bits,ebits,mbits,act", [(6, 3, 2, "f16"), (8, 4, 3, "bf16")])
+def test_wide_floats_on_four_row_tiles(bits, ebits, mbits, act):
+    from paper_2504_12984_amd import binding as B
+    P = Prepared(WL.Case(f"four_f{bits}", 63, 2176, 512, WL.KIND_FLOAT, bits, ebits, mbits, group=128, act=act, scale_dtype="f16", zero=None, seed=55100 + bits))
+    assert B.qg_plan(P.wtype, 128, 63, 512, 2176)["variant"] == 42
+    assert_c_close(P.gpu_c(), P.oracle_c(), P.case.name)

@@ -3,9 +3,10 @@ import pytest
 
 from paper_2504_12984_amd import binding as B
 
-U = {bits: B.WType(B.QG_UINT, bits) for bits in (1, 2, 4, 6, 8)}
+U = {bits: B.WType(B.QG_UINT, bits) for bits in (1, 2, 4, 6, 7, 8)}
 CB = {bits: B.WType(B.QG_CODEBOOK, bits) for bits in (4, 5, 8)}
 F4, F6 = B.WType(B.QG_FLOAT, 4, 2, 1), B.WType(B.QG_FLOAT, 6, 3, 2)
+F7, F8 = B.WType(B.QG_FLOAT, 7, 3, 3), B.WType(B.QG_FLOAT, 8, 4, 3)
 
 
 @pytest.mark.parametrize("t,M,K,N,variant,splitk", [
@@ -29,6 +30,7 @@ def test_two_row_tiles_groups_of_32():
 
 @pytest.mark.parametrize("t,group,M,K,N,variant", [
     (U[8], 128, 64, 2048, 2048, 42), (U[8], 64, 49, 512, 18432, 47), (U[6], 128, 64, 8192, 4096, 41),      # registers
+    (U[7], 128, 64, 8192, 4096, 42), (U[6], 64, 64, 8192, 4096, 42), (U[7], 128, 48, 8192, 4096, 31), (F8, 128, 64, 8192, 4096, 42), (F6, 128, 49, 2048, 8192, 42), (F7, 128, 64, 8192, 4096, 41),
     (U[6], 32, 40, 4096, 2048, 32), (U[8], 32, 64, 1024, 8192, 42), (U[4], 32, 64, 4096, 2048, 41),
     (U[4], 128, 33, 1024, 8192, 32), (U[4], 128, 33, 768, 8192, 31), (CB[4], 128, 40, 1024, 8192, 31), (CB[8], 128, 52, 1024, 16384, 42),      # two chunks each
     (U[8], 128, 33, 512, 24640, 32), (CB[4], 128, 40, 512, 24640, 32), (CB[4], 128, 52, 512, 24640, 41), (F6, 128, 40, 2048, 16384, 32),      # a round and a fraction, all CUs
