@@ -578,8 +578,8 @@ static int plan_path(int64_t M, int64_t N, int64_t K, int64_t group, qg_wtype t)
   // instead; it wins on all but the small problems (K = 8192, N = 28672, M = 64, 6 bits:
   // 59 us against 75; K = N = 8192: a tie; K = 14336, N = 4096: 32 against 26).  Up to 48 rows the
   // streaming kernel carries three row tiles (0.92 of that).  Both fits are older than the kernels: the streaming estimate is 25.4 us
-  // at M = 45, K = N = 8192, u4, where 16.1 are measured.  What they choose (u4, M = 64): K = N = 8192 streaming, 18.4 us against 19.3 tiled in
-  // eight slabs; K = 8192, N = 28672 tiled, 42.6 against 52.1.  Between the two the line has not been fitted again.
+  // at M = 45, K = N = 8192, u4, where 16.8 are measured.  What they choose (u4, M = 64): K = N = 8192 streaming, 18.4 us against 19.3 tiled in
+  // eight slabs; K = 8192, N = 28672 tiled, 43.7 against 50.0.  Between the two the line has not been fitted again.
   if (M > 32 && (double)K * (double)N >= 16.0e6 && knob(1) == 0 &&
       knob(2) == 0 && knob(3) == 0) {
     double tiled = 1e30;
@@ -863,8 +863,8 @@ static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* c
 // on a CU and 2.3 with a neighbour, a 64-row tile 1.0 and 1.5 (2 % more per bit above 4, group 64 30 %); a launch 6 us; the
 // exchange of partial sums 4 + 0.12 per MB + 1.2 per slab of 64 rows that the last one of a tile reads.  Fitted to M = 65 .. 1000,
 // K = 2048 .. 14336, N = 4096 .. 28672, u4, i8, groups 64 and 128 (640 points, 7 % rms); what it picks takes 3.6 % longer than the best
-// of all heights and splits on average.  64-row tiles: M = 300, K = N = 8192, u4 60.7 -> 46.0 us in three slabs, M = 128
-// 37.4 -> 28.6, K = N = 4096, M = 200 35.4 -> 22.5; 128-row tiles stay where they fill the chip.
+// of all heights and splits on average.  64-row tiles: M = 300, K = N = 8192, u4 60.6 -> 44.4 us in three slabs, M = 128
+// 36.9 -> 29.2, K = N = 4096, M = 200 36.1 -> 23.2; 128-row tiles stay where they fill the chip.
 static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* bm_out, int* splitk_out, int* cps_out) {
   const int KC = (int)(K / TILE_K);
   const double f = (group == 64 ? 1.3 : 1.0) * (1.0 + 0.02 * (bits > 4 ? bits - 4 : 0));

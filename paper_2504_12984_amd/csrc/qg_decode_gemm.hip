@@ -13,9 +13,10 @@
 // Codes are unpacked in registers and fed to the 16x16x32 matrix instruction
 // with W as the row operand (the paper's load -> reinterpret -> cast -> mma
 // pipeline, Section "Key Ideas", with no layout conversion and no trip through
-// LDS).  From 13 or 16 rows on A passes through LDS, each wavefront's rows through a part of its own: the matrix
+// LDS).  From 13 or 16 rows on A passes through LDS where that pays (lds_rows, two_chunks_direct; two row tiles on four
+// wavefronts load it directly), each wavefront's rows through a part of its own: the matrix
 // instruction wants 16 rows in adjacent lanes, and loads in that order run at 16 bytes per clock and CU (a lane at a
-// time), loads along the rows at 40 to 54.  M = 64, K = N = 8192, u4: 22.9 -> 18.4 us; M = 45 17.9 -> 16.1; M = 16, K = 8192,
+// time), loads along the rows at 40 to 54.  M = 64, K = N = 8192, u4: 23.0 -> 19.7 us; M = 45 18.1 -> 16.8; M = 16, K = 8192,
 // N = 28672, int4 27.6 -> 26.0, group 64 30.6 -> 27.7.  With fewer rows many lanes of a direct load share an address and the way
 // through LDS costs more than it saves (M = 8 there 24.7 against 25.9).
 // The K reduction runs inside the MFMA (across the four 8-wide k-blocks
