@@ -432,7 +432,7 @@ constexpr bool two_chunks_direct(int wt, int nw, int ns, bool mx) {
   return !mx && (wt_bits(wt) <= 5 || (ns == 1 && nw == 8 && (wt_bits(wt) == 6 || wt >= 8)));
 }
 
-// (DIRECT: never)
+// DIRECT: A is loaded directly whatever lds_rows says.
 template <int ROUTE, int GPC, int NW, int DEPTH, int MT, int NS = 1, bool MX = false, bool DIRECT = false>
 static int launch_cfg(const GemmParams& p, hipStream_t st) {
   if ((p.N / TILE_N) % NS) return QG_EINVAL;
