@@ -87,39 +87,65 @@ enum RepackMode {
 };
 
 // One wavefront builds one chunk.  A lane's columns are adjacent (four of them, two in the second
-// layout), so what it needs of a row is ONE field of the canonical stream; a row's 64 columns of a
-// chunk are 8*BITS bytes, read once by the 16 (32) lanes of a k-block.  A lane fetches the
-// 8-byte window that holds its field from each of its 32 (64) rows -- all independent loads -- and
-// places the codes at bit positions known at compile time.  The four wavefronts of a workgroup
-// take adjacent strips of the same rows, and workgroups are dealt out so that one XCD gets a run
-// of them: the parts of a cache line that several strips need meet in that XCD's L2.
-// Bound by the row windows, whose number does not shrink with the codes -- wavefronts wait 0.75 of their time to
-// issue them -- and at 8 bits nearly by memory (K = 8192, N = 28672: 33 us = 1.8 TB/s at 1 bit, 81 us = 3.6 at 5,
-// 97 us = 4.9 at 8; every byte is read and written once).
-// A thread that fetched every code by itself with two byte loads took 389 / 274 / 111 us.
+// layout), so what it needs of a row is ONE field of the canonical stream, and the four wavefronts of a workgroup
+// take adjacent strips of the same 128 rows.  Their part of a row, 32*BITS bytes, goes to LDS in 16-byte loads
+// (a last workgroup of fewer than four strips: 8-byte ones, which no row is a fraction of), and a lane picks the two dwords with its field
+// from each of its 32 (64) rows there.  Workgroups are dealt out so that one XCD gets a run of
+// them: the parts of a cache line that two of them need meet in that XCD's L2.
+// Bound by memory from 4 bits on (K = 8192, N = 28672: 41 us = 5.7 TB/s at 4 bits, 48 = 6.1 at 5, 94 = 5.0 at 8; every byte is read and
+// written once), below that by the placing of the codes (24.5 us = 2.4 TB/s at 1 bit).  When each lane fetched its 8-byte
+// windows from global memory, an address per lane and row, their issue took 60, 68, 97 and 32 us (second layout 89, 101, 122, 54).
 template <int BITS, int MODE>
 __global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__ canon, uint4* __restrict__ out, int K, int N,
                                                      uint32_t flip, int groups_n, int64_t total, int64_t per_xcd) {
   constexpr int COLS = (MODE == REPACK_R32 || MODE == REPACK_R32_PLAIN) ? 2 : 4;     // adjacent columns of a lane
   constexpr int LANES = TILE_N / COLS;                                               // lanes per k-block
   constexpr uint32_t CODE = (1u << BITS) - 1u;
+  // Rows in LDS: 8 * BITS dwords each, 16 more after every run that a k-block has of consecutive rows, so that the up to
+  // 16 dwords that each k-block of a wavefront reads at a time lie in banks of their own
+  constexpr int RUN = MODE == REPACK_I8 ? 16 : 8, ROW = 8 * BITS;
+  auto row_at = [](int k) __attribute__((always_inline)) { return k * ROW + (k / RUN) * 16; };
+  __shared__ __attribute__((aligned(16))) uint32_t rows[TILE_K * ROW + TILE_K / RUN * 16];
   const int64_t logical = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (logical >= total) return;
-  const int l = threadIdx.x & 63;
-  const int kc = (int)(logical / groups_n);
-  const int nc = (int)(logical % groups_n) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (nc >= N / TILE_N) return;
-  const int i = l % LANES, b = l / LANES;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kc = (int)(logical / groups_n), nc0 = (int)(logical % groups_n) * 4, nc = nc0 + w;
   const int64_t row_bytes = (int64_t)(N / 8) * BITS;
-  // the 8-byte window that holds my field, inside the segment; SH: the field's place in it
-  const int fbit = COLS * i * BITS, dw = min(fbit >> 5, 2 * BITS - 2), sh = fbit - 32 * dw;
-  const uint8_t* src = canon + (int64_t)TILE_K * kc * row_bytes + (int64_t)nc * (8 * BITS) + 4 * dw;
+  const uint8_t* src = canon + (int64_t)TILE_K * kc * row_bytes + (int64_t)nc0 * (8 * BITS);
+  const int strips = min(4, N / TILE_N - nc0);
+  if (strips == 4) {
+    u4_any v[BITS];
+#pragma unroll
+    for (int q = 0; q < BITS; ++q) {                    // piece tid + 256 q; a row has 2 * BITS
+      const int piece = tid + 256 * q, k = piece / (2 * BITS), at = piece % (2 * BITS);
+      v[q] = *reinterpret_cast<const u4_any*>(src + k * row_bytes + 16 * at);
+    }
+#pragma unroll
+    for (int q = 0; q < BITS; ++q) {
+      const int piece = tid + 256 * q, k = piece / (2 * BITS), at = piece % (2 * BITS);
+      *reinterpret_cast<uint4*>(rows + row_at(k) + 4 * at) = make_uint4(v[q].x, v[q].y, v[q].z, v[q].w);
+    }
+  } else {
+    for (int piece = tid; piece < TILE_K * BITS * strips; piece += 256) {
+      const int k = piece / (BITS * strips), at = piece % (BITS * strips);
+      const u2_any v = *reinterpret_cast<const u2_any*>(src + k * row_bytes + 8 * at);
+      *reinterpret_cast<uint2*>(rows + row_at(k) + 2 * at) = make_uint2(v.x, v.y);
+    }
+  }
+  __syncthreads();
+  if (w >= strips) return;
+  const int i = l % LANES, b = l / LANES;
+  // my field: bits sh .. sh + COLS * BITS - 1 of two dwords (the second one, where the first has all of it, is any dword
+  // of `rows`: behind the last row lie 16 more)
+  const int fbit = COLS * i * BITS, sh = fbit & 31;
+  const uint32_t* mine = rows + 2 * BITS * w + (fbit >> 5);
   uint32_t flips = flip;
 #pragma unroll
   for (int c = 1; c < COLS; ++c) flips |= flip << (c * BITS);
-  auto field = [&](int k) __attribute__((always_inline)) {
-    const u2_any v = *reinterpret_cast<const u2_any*>(src + k * row_bytes);
-    return (uint32_t)((((uint64_t)v.y << 32) | v.x) >> sh) ^ flips;
+  const uint32_t* mine_b = mine + row_at(RUN * b);
+  auto field = [&](int k) __attribute__((always_inline)) {        // row k + RUN * b
+    const uint32_t* at = mine_b + row_at(k);
+    return __builtin_amdgcn_alignbit(at[1], at[0], (uint32_t)sh) ^ flips;
   };
   uint32_t r[4 * BITS];
 #pragma unroll
@@ -129,7 +155,7 @@ __global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__
       constexpr int J = decltype(Gc)::value / 4, V = decltype(Gc)::value % 4;
       uint32_t f[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) f[e] = field(64 * J + 16 * b + 4 * V + e);
+      for (int e = 0; e < 4; ++e) f[e] = field(64 * J + 4 * V + e);
       static_for<4>([&](auto Nc) __attribute__((always_inline)) {
         constexpr int NT = decltype(Nc)::value, bit = ((J * 4 + NT) * 4 + V) * BITS, h = bit >> 3, p = bit & 7;
         uint32_t q = 0;
@@ -147,7 +173,7 @@ __global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__
   } else {
     static_for<64 / COLS>([&](auto Gc) __attribute__((always_inline)) {
       constexpr int J = decltype(Gc)::value / 4, V = decltype(Gc)::value % 4;
-      const int k = (COLS == 4 ? 32 : 16) * J + 8 * b + 2 * V;
+      constexpr int k = (COLS == 4 ? 32 : 16) * J + 2 * V;
       const uint32_t f0 = field(k), f1 = field(k + 1);
       static_for<COLS>([&](auto Nc) __attribute__((always_inline)) {
         constexpr int NT = decltype(Nc)::value, T = (J * COLS + NT) * 4 + V;
