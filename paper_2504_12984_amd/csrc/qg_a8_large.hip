@@ -1,7 +1,8 @@
 // Prefill-sized matmul with int8 activations: LDS-staged A, register-resident W, the integer
 // matrix instruction (see qg_a8_gemm.hip for what is computed and how the codes are laid out).
 //
-// A workgroup of 4 wavefronts computes a 128 x 256 tile of C -- or 64 x 256 where 128 rows would leave CUs idle --;
+// A workgroup of 4 wavefronts computes a 128 x 256 tile of C -- or 64 x 256 where 128 rows would leave CUs idle,
+// or (one launch, both heights) be more than the rows or the round that are left --;
 // wavefront w owns 64 columns and all rows, so a weight is unpacked once per 128 rows.  The 128 x 128-byte slab of A is shared
 // through LDS, each wavefront's own codes and scales pass through LDS as well: everything is loaded
 // straight into LDS by the memory pipe, which takes no registers -- 128 accumulators, the unpacked chunk
@@ -84,31 +85,28 @@ __device__ __forceinline__ uint32_t quad_less(const uint32_t (&r)[4 * BITS], uin
   return (x + up) ^ SIGN;
 }
 
-template <int BITS, int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
-__global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_m, int tiles_n, int per_xcd) {
-  constexpr int RAW = 4 * BITS, MTS = BM / 16, BUF = BM * 128, A_LOADS = BM / 32;
+// LDS of a tile: A slabs, each wavefront's codes, scales, zero-points
+template <int BITS, int BM, bool CORR>
+struct A8Lds {
+  static constexpr int BUF = BM * 128;
   // slabs of A in flight: two where LDS holds them for two workgroups per CU (160 KiB), else one
-  constexpr int A_AHEAD = BITS <= 7 ? 2 : 1, ABUFS = A_AHEAD + 1;
-  constexpr int W_AT = ABUFS * BUF, S_AT = W_AT + 4 * 1024 * BITS, Z_AT = S_AT + 4 * 256, LDS_BYTES = Z_AT + (CORR ? 4 * 256 : 0);
-  static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];   // A slabs, each wavefront's codes, scales, zero-points
+  static constexpr int A_AHEAD = BITS <= 7 ? 2 : 1, ABUFS = A_AHEAD + 1;
+  static constexpr int W_AT = ABUFS * BUF, S_AT = W_AT + 4 * 1024 * BITS, Z_AT = S_AT + 4 * 256, BYTES = Z_AT + (CORR ? 4 * 256 : 0);
+};
 
-  const int tiles = tiles_m * tiles_n;
-  const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (logical >= tiles * p.splitk) return;
-  const int slab = SPLIT ? logical / tiles : 0, tile = SPLIT ? logical % tiles : logical;
-  const int panel = A8_GROUP_M * tiles_n;
-  const int first_m = (tile / panel) * A8_GROUP_M;
-  const int gsize = min(tiles_m - first_m, A8_GROUP_M);
-  const int tm = first_m + (tile % panel) % gsize;
-  const int tn = (tile % panel) / gsize;
+// Rows m0 .. m0 + BM - 1 of column tile tn over the chunks of a slab.  A split tile's partial sums are at number `tile` of
+// the workspace, WS_BM rows each.
+template <int BITS, int GPC, int BM, int WS_BM, bool SBF16, bool SPLIT, bool CORR>
+__device__ __forceinline__ void a8_tile(const A8Params& p, uint8_t* lds, int tiles, int tile, int slab, int m0, int tn) {
+  constexpr int RAW = 4 * BITS, MTS = BM / 16, A_LOADS = BM / 32;
+  typedef A8Lds<BITS, BM, CORR> L;
+  constexpr int BUF = L::BUF, A_AHEAD = L::A_AHEAD, ABUFS = L::ABUFS, W_AT = L::W_AT, S_AT = L::S_AT, Z_AT = L::Z_AT;
 
   const int tid = threadIdx.x, l = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = l >> 4, i16 = l & 15;
   const int KC = p.K / TILE_K, NCH = p.N / TILE_N;
   const int kbeg = slab * p.chunks_per_split, kend = min(KC, kbeg + p.chunks_per_split);
-  const int m0 = tm * BM;
   const int ncw = tn * (A8_BN / TILE_N) + w;
   const bool active = ncw < NCH;
   const int nc = active ? ncw : NCH - 1;                 // idle wavefronts shadow a valid strip
@@ -358,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
     constexpr int SC1 = 16;                                   // cache policy: device coherence
     constexpr int AWAY = 0x40000000;                          // beyond the resource: loads give zeros, stores nothing
     auto ws_rsrc = [&](int sp) __attribute__((always_inline)) {
-      return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (BM * A8_BN), 0, BM * A8_BN * 4, 0x00020000);
+      return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (WS_BM * A8_BN), 0, BM * A8_BN * 4, 0x00020000);
     };
     auto ws_off = [&](int mt) __attribute__((always_inline)) { return m0 + mt * 16 + i16 < p.M ? 16 * tid : AWAY; };
     unsigned* ticket = p.tickets + ticket_stride(4 * tiles) * (4 * tile + w);
@@ -428,33 +426,78 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
   }
 }
 
+// Tiles of BM rows, or (BM = 128) `full` of 128 rows and `half` of 64.  The rows are cut into tiles_m row tiles of BM
+// and, where at most 64 are left behind them, a last one of 64 (`half` tiles, one per column); of the former the last
+// `cut` in panel order are computed as two halves (`half` tiles too: two each).  An XCD gets a run of either kind: `ahead` of the
+// full ones, then its halves, then the rest.
+template <int BITS, int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
+__global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_m, int tiles_n, int full, int half, int ahead) {
+  typedef A8Lds<BITS, BM, CORR> L;
+  static_assert(2 * L::BYTES <= 160 * 1024, "two workgroups per CU");
+  __shared__ __attribute__((aligned(16))) uint8_t lds[L::BYTES];
+  const int nfull = SPLIT ? full * p.splitk : full, nhalf = SPLIT ? half * p.splitk : half;
+  const int xcd = (int)(blockIdx.x % 8), j = (int)(blockIdx.x / 8);
+  const int fx = (nfull + 7) / 8, hx = (nhalf + 7) / 8, lead = min(fx, ahead);
+  const int panel = A8_GROUP_M * tiles_n;
+  auto position = [&](int tile, int* tm, int* tn) __attribute__((always_inline)) {
+    const int first_m = (tile / panel) * A8_GROUP_M;
+    const int gsize = min(tiles_m - first_m, A8_GROUP_M);
+    *tm = first_m + (tile % panel) % gsize;
+    *tn = (tile % panel) / gsize;
+  };
+  int tm, tn;
+  if (BM == 64 || j < lead || j >= lead + hx) {
+    const int at = j < lead ? j : j - hx, logical = xcd * fx + at;
+    if (at >= fx || logical >= nfull) return;
+    const int slab = SPLIT ? logical / full : 0, tile = SPLIT ? logical % full : logical;
+    position(tile, &tm, &tn);
+    a8_tile<BITS, GPC, BM, BM, SBF16, SPLIT, CORR>(p, lds, full + half, tile, slab, tm * BM, tn);
+  } else if constexpr (BM == 128) {
+    const int logical = xcd * hx + (j - lead);
+    if (logical >= nhalf) return;
+    const int slab = SPLIT ? logical / half : 0, i = SPLIT ? logical % half : logical;
+    const int cut2 = 2 * (tiles_m * tiles_n - full);
+    int m0;
+    if (i < cut2) {
+      position(full + i / 2, &tm, &tn);
+      m0 = tm * 128 + 64 * (i & 1);
+    } else {
+      m0 = tiles_m * 128; tn = i - cut2;
+    }
+    a8_tile<BITS, GPC, 64, 128, SBF16, SPLIT, CORR>(p, lds, full + half, full + i, slab, m0, tn);
+  }
+}
+
 #define QG_CAT2(a, b) a##b
 #define QG_CAT(a, b) QG_CAT2(a, b)
 
 template <int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
-static int launch_one(const A8Params& p, hipStream_t st) {
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + A8_BN - 1) / A8_BN;
-  const int per_xcd = (tiles_m * tiles_n * p.splitk + 7) / 8;
-  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, BM, SBF16, SPLIT, CORR>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, per_xcd);
+static int launch_one(const A8Params& p, int cut, hipStream_t st) {
+  const bool last64 = BM == 128 && p.M % 128 >= 1 && p.M % 128 <= 64;
+  const int tiles_m = last64 ? p.M / 128 : (p.M + BM - 1) / BM, tiles_n = (p.N + A8_BN - 1) / A8_BN;
+  if (cut < 0 || cut > tiles_m * tiles_n || (cut && (BM != 128 || SPLIT))) return QG_EINVAL;
+  const int full = tiles_m * tiles_n - cut, half = 2 * cut + (last64 ? tiles_n : 0);
+  const int per_xcd = (full * p.splitk + 7) / 8 + (half * p.splitk + 7) / 8;
+  hipLaunchKernelGGL((a8_large_kernel<QG_BITS, GPC, BM, SBF16, SPLIT, CORR>), dim3((unsigned)(8 * per_xcd)), dim3(256), 0, st, p, tiles_m, tiles_n, full, half, tiles_ahead(full));
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
 template <int GPC, int BM, bool SBF16>
-static int launch_scales(const A8Params& p, bool corr, hipStream_t st) {
-  if (corr) return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, true>(p, st) : launch_one<GPC, BM, SBF16, false, true>(p, st);
-  return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, false>(p, st) : launch_one<GPC, BM, SBF16, false, false>(p, st);
+static int launch_scales(const A8Params& p, bool corr, int cut, hipStream_t st) {
+  if (corr) return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, true>(p, cut, st) : launch_one<GPC, BM, SBF16, false, true>(p, cut, st);
+  return p.splitk > 1 ? launch_one<GPC, BM, SBF16, true, false>(p, cut, st) : launch_one<GPC, BM, SBF16, false, false>(p, cut, st);
 }
 
 template <int BM>
-static int launch_rows(const A8Params& p, bool corr, hipStream_t st) {
-  if (p.group == 64) return p.scale_bf16 ? launch_scales<2, BM, true>(p, corr, st) : launch_scales<2, BM, false>(p, corr, st);
-  return p.scale_bf16 ? launch_scales<1, BM, true>(p, corr, st) : launch_scales<1, BM, false>(p, corr, st);
+static int launch_rows(const A8Params& p, bool corr, int cut, hipStream_t st) {
+  if (p.group == 64) return p.scale_bf16 ? launch_scales<2, BM, true>(p, corr, cut, st) : launch_scales<2, BM, false>(p, corr, cut, st);
+  return p.scale_bf16 ? launch_scales<1, BM, true>(p, corr, cut, st) : launch_scales<1, BM, false>(p, corr, cut, st);
 }
 
-// corr: zero-points, or uintk codes; bm: rows of a tile, 64 or 128
-int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, bool corr, int bm, hipStream_t st) {
-  if (bm == 64) return launch_rows<64>(p, corr, st);
-  if (bm == 128) return launch_rows<128>(p, corr, st);
+// corr: zero-points, or uintk codes; bm: rows of a tile, 64 or 128; cut: so many of the latter as two halves
+int QG_CAT(a8_large_launch_bits, QG_BITS)(const A8Params& p, bool corr, int bm, int cut, hipStream_t st) {
+  if (bm == 64) return launch_rows<64>(p, corr, cut, st);
+  if (bm == 128) return launch_rows<128>(p, corr, cut, st);
   return QG_EINVAL;
 }
 

@@ -39,11 +39,11 @@ QG_FOR_ALL_LUT(QG_DECL)
 #define QG_DECL_A8(b) int a8_launch_bits##b(const A8Params&, int, int, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
-#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, bool, int, hipStream_t);
+#define QG_DECL_A8(b) int a8_large_launch_bits##b(const A8Params&, bool, int, int, hipStream_t);
 QG_DECL_A8(1) QG_DECL_A8(2) QG_DECL_A8(3) QG_DECL_A8(4) QG_DECL_A8(5) QG_DECL_A8(6) QG_DECL_A8(7) QG_DECL_A8(8)
 #undef QG_DECL_A8
 typedef int (*a8_fn)(const A8Params&, int, int, hipStream_t);
-typedef int (*a8_large_fn)(const A8Params&, bool, int, hipStream_t);
+typedef int (*a8_large_fn)(const A8Params&, bool, int, int, hipStream_t);
 static const a8_large_fn kA8Large[8] = {a8_large_launch_bits1, a8_large_launch_bits2, a8_large_launch_bits3, a8_large_launch_bits4,
                                         a8_large_launch_bits5, a8_large_launch_bits6, a8_large_launch_bits7, a8_large_launch_bits8};
 static const a8_fn kA8[8] = {a8_launch_bits1, a8_launch_bits2, a8_launch_bits3, a8_launch_bits4,
@@ -865,11 +865,17 @@ static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* c
 // K = 2048 .. 14336, N = 4096 .. 28672, u4, i8, groups 64 and 128 (640 points, 7 % rms); what it picks takes 3.6 % longer than the best
 // of all heights and splits on average.  64-row tiles: M = 300, K = N = 8192, u4 60.6 -> 44.4 us in three slabs, M = 128
 // 36.9 -> 29.2, K = N = 4096, M = 200 36.1 -> 23.2; 128-row tiles stay where they fill the chip.
-static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* bm_out, int* splitk_out, int* cps_out) {
+// A chunk of K on the fullest CU.  One launch of both heights (a8_large_kernel): a last row tile of at most 64 rows costs that and no
+// more, and 128-row tiles beyond whole rounds of 256 are computed as halves where that is shorter.  us, before and now: K = 8192, N = 28672,
+// u4, M = 300 139.4 and 110.2, M = 600 218.2 and 194.1, M = 1000 284.9 and 272.3; u8 in groups of 64, M = 300 190.8 and 132.9, M = 600
+// 296.5 and 241.8; K = 4096, N = 14336, u4, M = 600 74.1 and 59.0.  No such tile and no better cut: as before (M = 512 146.7 and 148).
+static double a8_round(int64_t high, int64_t low) { return tiles_level(high, low, 1.15, 0.75, low == 0 ? 0.3 : 0.25); }
+
+static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, int bits, int* bm_out, int* splitk_out, int* cps_out, int* cut_out) {
   const int KC = (int)(K / TILE_K);
   const double f = (group == 64 ? 1.3 : 1.0) * (1.0 + 0.02 * (bits > 4 ? bits - 4 : 0));
   double best = 1e30;
-  int splitk = 1, bm = 128;
+  int splitk = 1, bm = 128, cut = 0;
   for (int cand = 64; cand <= 128; cand *= 2)
     for (int sk : {1, 2, 3, 4, 6, 8}) {
       if ((knob(2) == 64 || knob(2) == 128) && cand != knob(2)) continue;      // (no other height here: chosen as without)
@@ -877,16 +883,22 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
       const int cps = (KC + sk - 1) / sk;
       const size_t part = (size_t)sk * tiles * (cand * 256 * sizeof(float));
       if (sk > 1 && (cps < 4 || tiles * sk > 512 || part > WS_PARTIAL_BYTES)) continue;
-      const int64_t full = tiles * sk / 512, rest = tiles * sk % 512;
-      const double alone = cand == 64 ? 1.0 : 1.45, pair = cand == 64 ? 1.5 : 2.3;
-      const double loop = f * cps * (full * pair + (rest == 0 ? 0.0 : rest <= 256 ? alone : pair));
+      // workgroups of 128 rows and of 64: what is over whole rounds of the former may be cut in halves (not under a forced split).  Split tiles
+      // count as 128-row ones all, also a last row tile of 64: its workgroups end early, but the others' last one waits for
+      // neither (counted as what they are, K = N = 8192, M = 150 went from 34.3 to 40.4 us, K = 14336, N = 4096, M = 400 from 52.3 to 58.7).
+      const int64_t low = cand == 64 ? tiles : sk == 1 && large_last64(rows) ? (N + 255) / 256 : 0, high = tiles - low;
+      const int64_t over = cand == 128 && sk == 1 && knob(1) <= 0 ? high % 256 : 0;
+      const double whole = a8_round(high * sk, low * sk), mixed = over ? a8_round(high - over, low + 2 * over) : whole;
+      const int c = mixed < whole ? (int)over : 0;
+      const double loop = f * cps * std::min(whole, mixed);
       const double mb = (double)sk * (double)rows * (double)N * 4.0e-6;
       const double cost = 6.0 + loop + (sk == 1 ? 0.0 : 4.0 + 0.12 * mb + 1.2 * (sk - 1) * (double)rows / (64.0 * tiles_m));
-      if (cost < best) { best = cost; splitk = sk; bm = cand; }
+      if (cost < best) { best = cost; splitk = sk; bm = cand; cut = c; }
     }
   if (knob(1) > 0) splitk = std::min(knob(1), 4096);      // (a strip's counter has 16 bits for its slabs)
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
+  *cut_out = cut;
   *bm_out = bm;
   *splitk_out = (KC + cps - 1) / cps;
   *cps_out = cps;
@@ -904,8 +916,8 @@ static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bit
   const double block = 8.0 + 0.16e-6 * (1.0 + 0.06 * (bits > 4 ? bits - 4 : 0)) * (double)K * (double)N;
   const int rem = (int)(M % 64);
   const double blocks = block * ((double)(M / 64) + (rem == 0 ? 0.0 : rem <= 16 ? 0.48 : rem <= 32 ? 0.65 : rem <= 48 ? 0.85 : 1.0));
-  int bm, sk, cps;
-  const double tiled = plan_a8_tiled(M, N, K, group, bits, &bm, &sk, &cps);
+  int bm, sk, cps, cut;
+  const double tiled = plan_a8_tiled(M, N, K, group, bits, &bm, &sk, &cps, &cut);
   return tiled < blocks;
 }
 
@@ -920,13 +932,13 @@ static int run_a8_tiled(const A8Params& p, int64_t M, bool corr, int bits, hipSt
     q.a_scale = p.a_scale ? p.a_scale + r0 : nullptr;
     q.C = p.C + r0 * p.N;
     q.M = (int)std::min(most, M - r0);
-    int bm;
-    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &bm, &q.splitk, &q.chunks_per_split);
+    int bm, cut;
+    plan_a8_tiled(q.M, q.N, q.K, q.group, bits, &bm, &q.splitk, &q.chunks_per_split, &cut);
     const int64_t tiles = (int64_t)((q.M + bm - 1) / bm) * ((q.N + 255) / 256);
     if (q.splitk > 1 && get_workspace((size_t)q.splitk * tiles * (size_t)(bm * 256) * sizeof(float), tile_tickets(tiles), st, &q.ws, &q.tickets) != QG_OK) {
       q.splitk = 1; q.chunks_per_split = q.K / TILE_K;
     }
-    const int rc = kA8Large[bits - 1](q, corr, bm, st);
+    const int rc = kA8Large[bits - 1](q, corr, bm, cut, st);
     if (rc != QG_OK) return rc;
   }
   return QG_OK;

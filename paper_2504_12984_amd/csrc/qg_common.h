@@ -1,5 +1,6 @@
 // Shared host/device definitions of the gfx950 quantised-matmul library.
 #pragma once
+#include <algorithm>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -188,6 +189,27 @@ inline bool set_group_index(P& p) {
 constexpr int LARGE_BN = 256;
 constexpr int LARGE_GROUP_M = 4;
 constexpr int LARGE_MEET = 3;      // up to so many K-slabs meet inside the tiled kernel, more in reduce_tiles_kernel
+// Tiled kernels, workgroups of 128 and of 64 rows in one launch, two to a CU: how many of the former an XCD (32 CUs) starts ahead of the
+// latter.  Where they come out at an odd number a CU, one each, so that a CU has one of either kind and none
+// is left alone at the end; where at an even one, all, and the lower ones fill the end.
+inline int tiles_ahead(int64_t full) { return (full / 256) % 2 ? 32 : 1 << 30; }
+// What `high` workgroups of 128 rows and `low` of 64 take on 256 CUs, as the sum of `a` for each of the former that a CU has and
+// `b` for each of the latter, plus `one` where the last of the fullest CU has no neighbour: the least level that holds all of them.
+inline double tiles_level(int64_t high, int64_t low, double a, double b, double one) {
+  const int64_t each = high / 256, r = high % 256;         // r CUs have one more
+  const int kmax = (int)((low + 255) / 256);
+  double best = 1e30;
+  for (int k = 0; k <= kmax; ++k)
+    for (int extra = 0; extra <= (r > 0); ++extra) {
+      const double level = k * b + extra * a;
+      if (r > 0 && level < a) continue;
+      const int64_t room = r * (int64_t)((level - (r > 0 ? a : 0.0)) / b + 1e-6) + (256 - r) * (int64_t)(level / b + 1e-6);
+      if (room >= low) best = std::min(best, each * a + level + ((each + extra + k) % 2 ? one : 0.0));
+    }
+  return best;
+}
+// Row tiles of 128: a last one of 64 for rows that fill no more
+__host__ __device__ constexpr bool large_last64(int64_t M) { return M % 128 >= 1 && M % 128 <= 64; }
 template <int GROUP_M>
 __device__ __forceinline__ void tile_position(int tile, int tiles_m, int tiles_n, int* tm, int* tn) {
   const int panel = GROUP_M * tiles_n;
