@@ -11,6 +11,7 @@
 // through LDS (double-buffered per chunk, XOR-swizzled 16-byte pieces, filled
 // through a small register ring two k-steps ahead), so each unpacked weight is
 // used BM times and each weight is unpacked M/BM times in total.
+// One launch may have tiles of 128 and of 64 rows (large_kernel, launch_route).
 // Workgroup ids are remapped so that the workgroups resident on one XCD (ids
 // congruent mod 8) form 4 x 8 panels of tiles that share A and W in that XCD's L2.
 // Compiled once per weight type (QG_WT).
@@ -86,8 +87,10 @@ constexpr int large_per_cu(int wt, int gpc, int bm, bool mx) {
   return (bm > 128 || wt == WT_DENSE16 || (bm == 128 && gpc == 4 && wt_bits(wt) == 8 && !mx)) ? 1 : 2;
 }
 
-template <int WT, int ROUTE, int GPC, int BM, bool MX = false>
-__global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kernel(GemmParams p, int tiles_m, int tiles_n, int per_xcd, int tn0) {
+// Rows m0 .. m0 + BM - 1 of column tile tn over the chunks of a slab.  A split tile's partial sums are at number `tile` (of
+// `tiles`) of the workspace, WS_BM rows each.
+template <int WT, int ROUTE, int GPC, int BM, int WS_BM, bool MX>
+__device__ __forceinline__ void large_tile(const GemmParams& p, int tiles, int tile, int slab, int m0, int tn) {
   // GPC = groups per 128-row chunk: 1 (group size 128 or more), 2 (64) or 4 (32)
   // MX: power-of-two block scales (8-bit exponents, one per 32 rows: GPC = 4) on e2m1 / e4m3 codes
   constexpr bool TWO_GROUPS = (GPC == 2), FOUR_GROUPS = (GPC == 4);
@@ -96,27 +99,15 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
   constexpr int BITS = D::BITS, RAW = D::RAW;
   constexpr int MTS = BM / 16;                 // 16-row MFMA tiles per workgroup
   constexpr int PIECES = BM * 4 / 256;         // 16-byte pieces per thread per slice
-  typedef LargeLds<BM> L;
+  // (named here and not handed in: only so are constant offsets from it folded into the accesses, a dozen additions per chunk less)
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-
-  // ---- which tile ----------------------------------------------------------------
-  // With split-K every tile is computed by p.splitk workgroups, one per slab of
-  // chunks_per_split K-chunks; the slab is the slowest index, so the workgroups of a slab
-  // keep the panel order among themselves.
-  const int tiles = tiles_m * tiles_n;
-  const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (logical >= tiles * p.splitk) return;
-  const int slab = logical / tiles, tile = logical % tiles;
-  int tm, tn;
-  tile_position<LARGE_GROUP_M>(tile, tiles_m, tiles_n, &tm, &tn);
-  tn += tn0;                                             // first column tile of this launch
+  typedef LargeLds<BM> L;
 
   const int tid = threadIdx.x, l = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
   const int b = l >> 4, i16 = l & 15;
   const int KC = p.K / TILE_K, NCH = p.N / TILE_N;
   const int kbeg = slab * p.chunks_per_split, kend = min(KC, kbeg + p.chunks_per_split);   // my K-chunks
-  const int m0 = tm * BM;
   const int ncw = tn * (LARGE_BN / TILE_N) + w;          // my 64-column strip
   const bool active = ncw < NCH;
   const int nc = active ? ncw : NCH - 1;                 // idle wavefronts shadow a valid strip
@@ -487,7 +478,7 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
       constexpr int SC1 = 16;                                   // cache policy: device coherence
       constexpr int AWAY = 0x40000000;                          // beyond the resource: loads give zeros, stores nothing
       auto ws_rsrc = [&](int sp) __attribute__((always_inline)) {
-        return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (BM * LARGE_BN), 0, BM * LARGE_BN * 4, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)tile * p.splitk + sp) * (WS_BM * LARGE_BN), 0, BM * LARGE_BN * 4, 0x00020000);
       };
       auto ws_off = [&](int mt) __attribute__((always_inline)) { return m0 + mt * 16 + i16 < p.M ? 16 * tid : AWAY; };
       const bool here = p.splitk <= LARGE_MEET;
@@ -565,16 +556,50 @@ __global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kern
   store_rows();
 }
 
+// Tiles of BM rows, or (BM = 128) `full` of 128 rows and `half` of 64: the rows are cut into tiles_m row tiles of BM
+// and, where at most 64 are left behind them, a last one of 64 (`half` tiles, one per column); of the former the last
+// `cut` in panel order are computed as two halves (`half` tiles too: two each).  An XCD gets a run of either kind: `ahead` of the
+// full ones, then its halves, then the rest.
+// With split-K every tile is computed by p.splitk workgroups, one per slab of
+// chunks_per_split K-chunks; the slab is the slowest index, so the workgroups of a slab
+// keep the panel order among themselves.
+template <int WT, int ROUTE, int GPC, int BM, bool MX = false>
+__global__ __launch_bounds__(256, large_per_cu(WT, GPC, BM, MX)) void large_kernel(GemmParams p, int tiles_m, int tiles_n, int full, int half, int ahead, int tn0) {
+  const int xcd = (int)(blockIdx.x % 8), j = (int)(blockIdx.x / 8);
+  const int fx = (full * p.splitk + 7) / 8, hx = (half * p.splitk + 7) / 8, lead = min(fx, ahead);
+  int tm, tn;
+  if (BM != 128 || j < lead || j >= lead + hx) {
+    const int at = j < lead ? j : j - hx, logical = xcd * fx + at;
+    if (at >= fx || logical >= full * p.splitk) return;
+    const int tile = logical % full;
+    tile_position<LARGE_GROUP_M>(tile, tiles_m, tiles_n, &tm, &tn);
+    large_tile<WT, ROUTE, GPC, BM, BM, MX>(p, full + half, tile, logical / full, tm * BM, tn0 + tn);
+  } else if constexpr (BM == 128) {
+    const int logical = xcd * hx + (j - lead);
+    if (logical >= half * p.splitk) return;
+    const int i = logical % half, cut2 = 2 * (tiles_m * tiles_n - full);
+    int m0 = tiles_m * 128;
+    tn = i - cut2;
+    if (i < cut2) {
+      tile_position<LARGE_GROUP_M>(full + i / 2, tiles_m, tiles_n, &tm, &tn);
+      m0 = tm * 128 + 64 * (i & 1);
+    }
+    large_tile<WT, ROUTE, GPC, 64, 128, MX>(p, full + half, full + i, logical / half, m0, tn0 + tn);
+  }
+}
+
 #define QG_CAT2(a, b) a##b
 #define QG_CAT(a, b) QG_CAT2(a, b)
 
-// One launch over the column tiles [tn0, tn0 + tiles_n) and all row tiles of height BM.
+// One launch over the column tiles [tn0, tn0 + tiles_n) and all row tiles of height BM, `cut` of 128 rows as two halves.
 template <int ROUTE, int GPC, int BM, bool MX = false>
-static int launch_bm(const GemmParams& p, hipStream_t st, int tn0, int tiles_n) {
-  const int tiles_m = (p.M + BM - 1) / BM;
+static int launch_bm(const GemmParams& p, hipStream_t st, int tn0, int tiles_n, int cut) {
   if (p.splitk > 1 && BM > 128) return QG_EINVAL;
-  const int total = tiles_m * tiles_n * p.splitk;
-  const int per_xcd = (total + 7) / 8;
+  const bool last64 = BM == 128 && large_last64(p.M);
+  const int tiles_m = last64 ? p.M / 128 : (p.M + BM - 1) / BM;
+  if (cut < 0 || cut > tiles_m * tiles_n || (cut && (BM != 128 || p.splitk > 1))) return QG_EINVAL;
+  const int full = tiles_m * tiles_n - cut, half = 2 * cut + (last64 ? tiles_n : 0);
+  const int per_xcd = (full * p.splitk + 7) / 8 + (half * p.splitk + 7) / 8;
   typedef typename DecoderFor<QG_WT, ROUTE, MX>::type D;
   size_t lds_bytes = 2 * LargeLds<BM>::BUF;
   if constexpr (D::IS_LUT) lds_bytes += (size_t)D::TABLE_DWORDS * 4;      // 256-row tiles + a 32 KiB table: exactly the 160 KiB of a CU
@@ -589,19 +614,19 @@ static int launch_bm(const GemmParams& p, hipStream_t st, int tn0, int tiles_n) 
       return QG_EHIP;
     attr_done[dev] = true;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), lds_bytes, st, p, tiles_m, tiles_n, per_xcd, tn0);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), lds_bytes, st, p, tiles_m, tiles_n, full, half, tiles_ahead(full), tn0);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
 template <int ROUTE>
-static int launch_rows(const GemmParams& p, int bm, hipStream_t st, int tn0, int tiles_n) {
+static int launch_rows(const GemmParams& p, int bm, hipStream_t st, int tn0, int tiles_n, int cut = 0) {
   const int gpc = (p.group == 32) ? 4 : (p.group == 64) ? 2 : 1;       // groups per 128-row chunk
   if (p.scale_e8m0) {
 #if QG_WT == 9 || QG_WT == 13
     if (gpc != 4) return QG_EUNSUPPORTED;
-    if (bm == 64) return launch_bm<ROUTE, 4, 64, true>(p, st, tn0, tiles_n);
-    if (bm == 128) return launch_bm<ROUTE, 4, 128, true>(p, st, tn0, tiles_n);
-    if (bm == 256) return launch_bm<ROUTE, 4, 256, true>(p, st, tn0, tiles_n);
+    if (bm == 64) return launch_bm<ROUTE, 4, 64, true>(p, st, tn0, tiles_n, cut);
+    if (bm == 128) return launch_bm<ROUTE, 4, 128, true>(p, st, tn0, tiles_n, cut);
+    if (bm == 256) return launch_bm<ROUTE, 4, 256, true>(p, st, tn0, tiles_n, cut);
     return QG_EINVAL;
 #else
     return QG_EUNSUPPORTED;
@@ -609,8 +634,8 @@ static int launch_rows(const GemmParams& p, int bm, hipStream_t st, int tn0, int
   }
 #define QG_ROWS(BM_)                                                              \
   if (bm == BM_)                                                                  \
-    return gpc == 4 ? launch_bm<ROUTE, 4, BM_>(p, st, tn0, tiles_n)               \
-         : gpc == 2 ? launch_bm<ROUTE, 2, BM_>(p, st, tn0, tiles_n) : launch_bm<ROUTE, 1, BM_>(p, st, tn0, tiles_n);
+    return gpc == 4 ? launch_bm<ROUTE, 4, BM_>(p, st, tn0, tiles_n, cut)               \
+         : gpc == 2 ? launch_bm<ROUTE, 2, BM_>(p, st, tn0, tiles_n, cut) : launch_bm<ROUTE, 1, BM_>(p, st, tn0, tiles_n, cut);
   QG_ROWS(64) QG_ROWS(128) QG_ROWS(256)
 #undef QG_ROWS
   return QG_EINVAL;
@@ -620,30 +645,35 @@ template <int ROUTE>
 static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   const int tiles_n = (p.N + LARGE_BN - 1) / LARGE_BN;
   if (bm != 0) return launch_rows<ROUTE>(p, bm, st, 0, tiles_n);
-  // Row-tile height by a small cost model: workgroups run in rounds of 256 (one per
-  // CU), a tile costs its rows plus about 64 rows' worth of unpack and start-up.
-  // 128 rows win when they fill a round that 256 rows leave half empty (M <= 256 on
-  // 28672 columns, M = 384 on 57344: measured 20-30 % shorter), 256 rows otherwise.
-  auto cost = [&](int rows, long cols) {
-    const long tiles = ((p.M + rows - 1) / rows) * cols;
-    return ((tiles + 255) / 256) * (rows + 64);
-  };
   // 128-row tiles that would occupy at most half of the CUs: 64-row tiles instead -- a tile
   // costs 0.89 of a 128-row one (the unpack per matrix instruction doubles) but twice as many
   // CUs work (measured 10-15 % shorter: M = 128 on 28672 columns, M = 256..512 on 8192)
   if (large_prefers_64_rows(p.M, p.N)) return launch_rows<ROUTE>(p, 64, st, 0, tiles_n);
-  if (p.M <= 128) return launch_rows<ROUTE>(p, 128, st, 0, tiles_n);
-  // Whole rounds of 256-row tiles first; the column tiles that would start a partly
-  // filled last round go into a second launch with whichever height is cheaper for
-  // them (M = 1024 on 57344 columns: 3.5 rounds become 3 + one round of 128-row tiles).
-  const int tm256 = (p.M + 255) / 256;
-  const long rounds = ((long)tm256 * tiles_n) / 256;
-  const int tn_full = (int)((rounds * 256) / tm256 < tiles_n ? (rounds * 256) / tm256 : tiles_n);
-  if (tn_full == 0) return launch_rows<ROUTE>(p, cost(128, tiles_n) < cost(256, tiles_n) ? 128 : 256, st, 0, tiles_n);
-  int rc = launch_rows<ROUTE>(p, 256, st, 0, tn_full);
-  if (rc != QG_OK || tn_full == tiles_n) return rc;
-  const int rest = tiles_n - tn_full;
-  return launch_rows<ROUTE>(p, cost(128, rest) < cost(256, rest) ? 128 : 256, st, tn_full, rest);
+  // Otherwise by what a chunk takes, in microseconds (u4): a 256-row tile, which has a CU to itself, 2.86, a 128-row one 1.43 and
+  // a 64-row one 0.83, with a neighbour or one after the other.  Three ways to cut the rows: 256-row tiles; whole rounds of them and the
+  // other columns in 128-row tiles, in a second launch (4 us); all in 128-row tiles, or 256 more of them than a whole number
+  // of rounds leaves and the others as halves.  A last row tile of at most 64 rows costs only that in 128-row tiles.
+  // The third has to be 3 % better: with full rounds the card's power bounds all of them.  u4, us, with the first two alone and now: K = 8192,
+  // N = 28672: M = 300 171.5 and 141.2, M = 600 274.8 and 253.8, M = 1100 478.2 and 402.3; N = 57344: M = 150 165.1 and 147.3, M = 300 335.3 and
+  // 258.1; K = 4096, N = 14336, M = 1100 147.1 and 104.3 (120 calls of 65 to 2048 rows 6 % shorter on average, none more than 3 % longer).
+  constexpr double TALL = 2.86, HIGH = 1.43, LOW = 0.83, SECOND_LAUNCH = 4.0;
+  auto mixed = [&](int cols, int* cut) {
+    const int64_t high = (int64_t)(large_last64(p.M) ? p.M / 128 : (p.M + 127) / 128) * cols, low = large_last64(p.M) ? cols : 0, over = high % 256;
+    const double whole = tiles_level(high, low, HIGH, LOW, 0.0), some = over ? tiles_level(high - over, low + 2 * over, HIGH, LOW, 0.0) : whole;
+    *cut = some < whole ? (int)over : 0;
+    return std::min(some, whole);
+  };
+  int cut_all = 0, cut_rest = 0;
+  const double all = mixed(tiles_n, &cut_all);
+  if (p.M <= 128) return launch_rows<ROUTE>(p, 128, st, 0, tiles_n, cut_all);
+  const int64_t tm256 = (p.M + 255) / 256, rounds = tm256 * tiles_n / 256;
+  const int tn_full = (int)(rounds * 256 / tm256 < tiles_n ? rounds * 256 / tm256 : tiles_n);
+  const double tall = TALL * (double)((tm256 * tiles_n + 255) / 256);
+  const double two = tn_full == 0 || tn_full == tiles_n ? tall : TALL * (double)rounds + SECOND_LAUNCH * TILE_K / p.K + mixed(tiles_n - tn_full, &cut_rest);
+  if (all < 0.97 * std::min(tall, two)) return launch_rows<ROUTE>(p, 128, st, 0, tiles_n, cut_all);
+  if (tall <= two) return launch_rows<ROUTE>(p, 256, st, 0, tiles_n);
+  const int rc = launch_rows<ROUTE>(p, 256, st, 0, tn_full);
+  return rc != QG_OK ? rc : launch_rows<ROUTE>(p, 128, st, tn_full, tiles_n - tn_full, cut_rest);
 }
 
 int QG_CAT(large_launch_wt, QG_WT)(const GemmParams& p, int route, int bm, hipStream_t st) {

@@ -17,8 +17,8 @@ template <int ROUTE>
 __global__ __launch_bounds__(256) void reduce_tiles_kernel(const float* __restrict__ ws, uint16_t* __restrict__ C, int M, int N,
                                                            int bm, int splitk, int tiles_m, int tiles_n) {
   const int mts = bm / 16, tile = blockIdx.x / mts, mt = blockIdx.x % mts;
-  int tm, tn;
-  tile_position<LARGE_GROUP_M>(tile, tiles_m, tiles_n, &tm, &tn);
+  int tm = tiles_m, tn = tile - tiles_m * tiles_n;        // behind the others: the last row tile of 64 rows
+  if (tn < 0) tile_position<LARGE_GROUP_M>(tile, tiles_m, tiles_n, &tm, &tn);
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
   const int m = tm * bm + mt * 16 + (l & 15);
   const int nc = tn * (LARGE_BN / TILE_N) + w;
@@ -58,9 +58,10 @@ __global__ __launch_bounds__(256) void reduce_tiles_kernel(const float* __restri
 }
 
 int launch_reduce_tiles(const GemmParams& p, int route, int bm, hipStream_t st) {
-  const int tiles_m = (p.M + bm - 1) / bm, tiles_n = (p.N + LARGE_BN - 1) / LARGE_BN;
+  const int all_m = (p.M + bm - 1) / bm, tiles_n = (p.N + LARGE_BN - 1) / LARGE_BN;
+  const int tiles_m = bm == 128 && large_last64(p.M) ? all_m - 1 : all_m;
   auto kern = route == ROUTE_F16 ? reduce_tiles_kernel<ROUTE_F16> : reduce_tiles_kernel<ROUTE_BF16>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * (bm / 16))), dim3(256), 0, st, p.ws, p.C, p.M, p.N, bm, p.splitk, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(all_m * tiles_n * (bm / 16))), dim3(256), 0, st, p.ws, p.C, p.M, p.N, bm, p.splitk, tiles_m, tiles_n);
   return hipGetLastError() == hipSuccess ? QG_OK : QG_EHIP;
 }
 
