@@ -106,7 +106,9 @@ _SDT = {torch.float16: QG_F16, torch.bfloat16: QG_BF16, torch.uint8: QG_E8M0}
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle of the current device's current stream; building a Stream object around it takes 2.5 us
+    # of a call's 10.8
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t, name):
