@@ -330,6 +330,49 @@ static bool four_wavefronts(int M, int NCH, int KC, int splitk, int group, int w
   return NCH > 224 && NCH <= 256 && few && KC >= 16 && KC <= 32 && !lut && !codes_float && (mx || group != 32);      // (M = 17, u4, K = 4096, N = 16384: 11.9 against 13.0)
 }
 
+// Streaming kernel: strips that a workgroup of an arrangement computes.
+static int strips_of(int variant) {
+  const int e = variant % 10;
+  return variant / 10 == 1 ? (e == 6 ? 4 : e == 4 || e == 5 ? 2 : 1) : (e == 6 || e == 7 ? 2 : 1);
+}
+
+// Streaming kernel: what a call takes, in microseconds, up to a factor that a weight type has for itself: chunks of K after each
+// other in the workgroups of a CU, more for every further round of them, and the exchange -- a trip to memory for every level of the
+// tree, with three and four row tiles a slab after the other -- and its traffic.
+static double streaming_cost(int M, int N, int K, int bits, int variant, int splitk) {
+  const int KC = K / TILE_K, strips = strips_of(variant), mt = variant / 10, cps = (KC + splitk - 1) / splitk;
+  const int64_t rounds = ((int64_t)((N / TILE_N + strips - 1) / strips) * splitk + 255) / 256;
+  const double chunk = (0.095 + 0.049 * mt) * (1.0 + 0.09 * (bits > 4 ? bits - 4 : 0)) * strips;
+  double exchange = 0.0;
+  if (splitk > 1) {
+    exchange = 2.4e-6 * splitk * (double)M * (double)N;
+    if (mt > 2) exchange += 0.3 + 0.6 * (splitk - 1);
+    else for (int s = 1; s < splitk; s *= 2) exchange += 1.0;
+  }
+  return 5.0 + chunk * (double)(rounds * cps) + 2.5 * (double)(rounds - 1) + exchange;
+}
+
+// The slabs that doubling came to, or a number that is better by 7 % or more: doubling leaves CUs idle, or a second round with few
+// workgroups, where the strips are no power of two, 80 in four slabs for instance (us, M = 16 and 64: K = 13824, N = 5120, u4 15.0 and 29.3, in
+// three slabs 11.7 and 20.8; K = 4096, N = 10240 whole instead of in two, M = 64 21.0 and 15.2).
+// 1056 calls (22 shapes, M = 1 .. 64, u4, u8, int2, e2m2, e3m2, 4-bit codebook): 180 get other slabs and are 1.04 to 1.57 times as fast, 1.29 on average.
+static int better_split(int M, int N, int K, int wt, int variant, int splitk) {
+  const int KC = K / TILE_K, NCH = N / TILE_N, mt = variant / 10;
+  // a call that needs no workspace keeps doing without; 17 .. 24 rows mostly run on four wavefronts and one row tile of
+  // some types on eight: two workgroups to a CU (with this rule e3m2, M = 1, K = 8192, N = 7168 went from 9.8 to 13.5 us); the two
+  // slabs that two row tiles have on long K stay, and more than four come from doubling alone
+  if (splitk == 1 || (M > 16 && M <= 24) || variant == 10 || (mt == 2 && KC > 32 && splitk == 2)) return splitk;
+  const double now = streaming_cost(M, N, K, wt_bits(wt), variant, splitk);
+  int best = splitk;
+  double least = 0.93 * now;
+  for (int sk = 1; sk <= std::max(4, splitk); ++sk) {
+    if (sk > 1 && ((KC + sk - 1) / sk < 4 || NCH * sk >= 512 || (size_t)(sk - 1) * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float) > WS_SLOT_BYTES)) continue;
+    const double cost = streaming_cost(M, N, K, wt_bits(wt), variant, sk);
+    if (cost < least) { least = cost; best = sk; }
+  }
+  return best;
+}
+
 // Streaming kernel (M <= 64): wavefront arrangement and split-K by shape.  Host arithmetic only.
 // (mx: block-scaled weights -- group 32, but only four scale bytes per block and lane, so every
 // arrangement has the registers for them)
@@ -400,6 +443,7 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
     // long K and still at most half of the CUs busy: K in four, down to one chunk per wavefront
     // (K = 14336, N = 4096: 11.0 us against 16.2 with K in two; deeper splits lose to the exchange)
     while (KC > 32 && splitk < 4 && NCH * splitk <= 128 && KC / (splitk * 2) >= waves) splitk *= 2;
+    splitk = better_split(M, N, K, wt, variant, splitk);
   }
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
