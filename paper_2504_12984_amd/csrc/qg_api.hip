@@ -356,18 +356,17 @@ static double streaming_cost(int M, int N, int K, int bits, int variant, int spl
 // workgroups, where the strips are no power of two, 80 in four slabs for instance (us, M = 16 and 64: K = 13824, N = 5120, u4 15.0 and 29.3, in
 // three slabs 11.7 and 20.8; K = 4096, N = 10240 whole instead of in two, M = 64 21.0 and 15.2).
 // 1056 calls (22 shapes, M = 1 .. 64, u4, u8, int2, e2m2, e3m2, 4-bit codebook): 180 get other slabs and are 1.04 to 1.57 times as fast, 1.29 on average.
-static int better_split(int M, int N, int K, int wt, int variant, int splitk) {
+// The int8 kernel by the same estimate (285 calls, 19 shapes, u4, i8, int2, each in 1 to 8 slabs): 0.2 % longer than the best on average, by doubling 19.6 %;
+// K = 4096, N = 14336, u4, M = 16 11.0 us in two slabs, whole 8.2; K = 13824, N = 5120 15.1 in four, 10.3 in three.
+// A call that needs no workspace keeps doing without, and more than four slabs come from doubling alone.
+static int better_split(int M, int N, int K, int bits, int variant, int splitk) {
+  if (splitk == 1) return 1;
   const int KC = K / TILE_K, NCH = N / TILE_N, mt = variant / 10;
-  // a call that needs no workspace keeps doing without; 17 .. 24 rows mostly run on four wavefronts and one row tile of
-  // some types on eight: two workgroups to a CU (with this rule e3m2, M = 1, K = 8192, N = 7168 went from 9.8 to 13.5 us); the two
-  // slabs that two row tiles have on long K stay, and more than four come from doubling alone
-  if (splitk == 1 || (M > 16 && M <= 24) || variant == 10 || (mt == 2 && KC > 32 && splitk == 2)) return splitk;
-  const double now = streaming_cost(M, N, K, wt_bits(wt), variant, splitk);
+  double least = 0.93 * streaming_cost(M, N, K, bits, variant, splitk);
   int best = splitk;
-  double least = 0.93 * now;
   for (int sk = 1; sk <= std::max(4, splitk); ++sk) {
     if (sk > 1 && ((KC + sk - 1) / sk < 4 || NCH * sk >= 512 || (size_t)(sk - 1) * NCH * (size_t)(mt * 16 * TILE_N) * sizeof(float) > WS_SLOT_BYTES)) continue;
-    const double cost = streaming_cost(M, N, K, wt_bits(wt), variant, sk);
+    const double cost = streaming_cost(M, N, K, bits, variant, sk);
     if (cost < least) { least = cost; best = sk; }
   }
   return best;
@@ -443,7 +442,9 @@ static void plan_streaming(int M, int N, int K, int group, int wt, int* variant_
     // long K and still at most half of the CUs busy: K in four, down to one chunk per wavefront
     // (K = 14336, N = 4096: 11.0 us against 16.2 with K in two; deeper splits lose to the exchange)
     while (KC > 32 && splitk < 4 && NCH * splitk <= 128 && KC / (splitk * 2) >= waves) splitk *= 2;
-    splitk = better_split(M, N, K, wt, variant, splitk);
+    // (not 17 .. 24 rows, mostly on four wavefronts, and one row tile of some types on eight: two workgroups to a CU -- e3m2, M = 1, K = 8192,
+    // N = 7168 went from 9.8 to 13.5 us --; the two slabs that two row tiles have on long K stay)
+    if (!(M > 16 && M <= 24) && variant != 10 && !(mt == 2 && KC > 32 && splitk == 2)) splitk = better_split(M, N, K, wt_bits(wt), variant, splitk);
   }
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
@@ -886,7 +887,7 @@ int qgemm_codebook(const void* A, const void* packed_W, const void* codebook, co
 static int a8_row_tiles(int64_t M) { return M > 32 && M <= 48 ? 3 : row_tiles(M); }
 
 // int8 activations: wavefronts per strip and split-K of one block of at most 64 rows
-static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* cps_out) {
+static void plan_a8(int M, int N, int K, int bits, int* waves_out, int* splitk_out, int* cps_out) {
   const int KC = K / TILE_K, NCH = N / TILE_N, mt = a8_row_tiles(M);
   // eight wavefronts per strip on long K; four with three or four row tiles (their accumulators and
   // the ring do not fit the registers eight wavefronts leave each) and on short K
@@ -896,6 +897,7 @@ static void plan_a8(int M, int N, int K, int* waves_out, int* splitk_out, int* c
     splitk = 1;
     // K over workgroups while the strips alone leave CUs idle and every wavefront keeps two chunks
     while (NCH * splitk < 256 && KC / (splitk * 2) >= 2 * waves) splitk *= 2;
+    splitk = better_split(M, N, K, bits, 10 * mt + 1, splitk);
   }
   if (splitk > KC) splitk = KC;
   const int cps = (KC + splitk - 1) / splitk;
@@ -1033,7 +1035,7 @@ int qgemm_a8(const int8_t* A8, const float* a_scale, const void* packed_W, const
     q.C = p.C + r0 * N;
     q.M = (int)((M - r0 < 64) ? (M - r0) : 64);
     int waves;
-    plan_a8(q.M, q.N, q.K, &waves, &q.splitk, &q.chunks_per_split);
+    plan_a8(q.M, q.N, q.K, t.bits, &waves, &q.splitk, &q.chunks_per_split);
     const int mt = a8_row_tiles(q.M);
     if (q.splitk > 1) {
       const int NCH = q.N / TILE_N;

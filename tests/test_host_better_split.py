@@ -2,6 +2,7 @@
 import pytest
 
 from paper_2504_12984_amd import binding as B
+from test_host_workspace import _run, stub  # noqa: F401
 
 U4, U8, I2, F6 = B.WType(B.QG_UINT, 4), B.WType(B.QG_UINT, 8), B.WType(B.QG_INT, 2), B.WType(B.QG_FLOAT, 6, 3, 2)
 
@@ -30,3 +31,11 @@ def test_slabs_invariants(M, K):
             row_tiles = p["variant"] // 10
             assert sk == 1 or (strips * sk < 512 and 4096 * row_tiles * strips * sk <= 32 << 20)          # the workspace's capacity
             assert sk == 1 or row_tiles > 2 or 4096 * row_tiles * strips * (sk - 1) <= 4 << 20          # and that of the slots
+
+
+def test_slabs_int8(stub):
+    # a launch has strips x slabs workgroups: whole rather than two rounds of halves, three slabs of 80 strips rather than four
+    shapes = [(16, 4096, 14336, 1), (64, 4096, 10240, 1), (16, 13824, 5120, 3), (64, 5120, 5120, 3), (16, 8192, 8192, 2)]
+    calls = _run(stub, "out = [" + ", ".join(f"a8({M}, {K}, {N})" for M, K, N, _ in shapes) + "]")
+    for (M, K, N, slabs), c in zip(shapes, calls):
+        assert c["rc"] == 0 and c["launches"][-1][0] == "a8_kernel" and c["launches"][-1][2:] == [N // 64, slabs], (M, K, N, c)
