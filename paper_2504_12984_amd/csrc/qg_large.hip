@@ -653,10 +653,15 @@ static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   // a 64-row one 0.83, with a neighbour or one after the other.  Three ways to cut the rows: 256-row tiles; whole rounds of them and the
   // other columns in 128-row tiles, in a second launch (4 us); all in 128-row tiles, or 256 more of them than a whole number
   // of rounds leaves and the others as halves.  A last row tile of at most 64 rows costs only that in 128-row tiles.
-  // The third has to be 3 % better: with full rounds the card's power bounds all of them.  u4, us, with the first two alone and now: K = 8192,
+  // Types whose unpack no longer hides between the matrix instructions pay more for lower tiles, which unpack a weight more often: relative to 2.86, floats
+  // without a quick hardware convert 1.66 and 1.12, codebooks 1.77 and 1.05, of more than 4 bits, and 16-bit weights, 1.88 and 1.36 (at the integers' values codebooks were 2 % longer on
+  // average than with 256-row tiles: 8 bits, M = 1500, K = 4096, N = 57344 918 us against 742, 4 bits, M = 700, N = 14336 110 against 95).
+  // The second has to be 3 % better than the first, the third 4 % than both: with full rounds the card's power bounds all of them.  u4, us, with the first two alone and now: K = 8192,
   // N = 28672: M = 300 171.5 and 141.2, M = 600 274.8 and 253.8, M = 1100 478.2 and 402.3; N = 57344: M = 150 165.1 and 147.3, M = 300 335.3 and
   // 258.1; K = 4096, N = 14336, M = 1100 147.1 and 104.3 (120 calls of 65 to 2048 rows 6 % shorter on average, none more than 3 % longer).
-  constexpr double TALL = 2.86, HIGH = 1.43, LOW = 0.83, SECOND_LAUNCH = 4.0;
+  constexpr bool LUT = wt_is_lut(QG_WT), DENSE = QG_WT == WT_DENSE16, WIDE = wt_bits(QG_WT) > 4, SOFT = wt_is_float(QG_WT) && QG_WT != 9 && QG_WT != 13;
+  constexpr double TALL = 2.86, SECOND_LAUNCH = 4.0;
+  constexpr double HIGH = LUT || DENSE ? (WIDE ? 1.88 : 1.77) : SOFT ? 1.66 : 1.43, LOW = LUT || DENSE ? (WIDE ? 1.36 : 1.05) : SOFT ? 1.12 : 0.83;
   auto mixed = [&](int cols, int* cut) {
     const int64_t high = (int64_t)(large_last64(p.M) ? p.M / 128 : (p.M + 127) / 128) * cols, low = large_last64(p.M) ? cols : 0, over = high % 256;
     const double whole = tiles_level(high, low, HIGH, LOW, 0.0), some = over ? tiles_level(high - over, low + 2 * over, HIGH, LOW, 0.0) : whole;
@@ -670,8 +675,8 @@ static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   const int tn_full = (int)(rounds * 256 / tm256 < tiles_n ? rounds * 256 / tm256 : tiles_n);
   const double tall = TALL * (double)((tm256 * tiles_n + 255) / 256);
   const double two = tn_full == 0 || tn_full == tiles_n ? tall : TALL * (double)rounds + SECOND_LAUNCH * TILE_K / p.K + mixed(tiles_n - tn_full, &cut_rest);
-  if (all < 0.97 * std::min(tall, two)) return launch_rows<ROUTE>(p, 128, st, 0, tiles_n, cut_all);
-  if (tall <= two) return launch_rows<ROUTE>(p, 256, st, 0, tiles_n);
+  if (all < 0.96 * std::min(tall, two)) return launch_rows<ROUTE>(p, 128, st, 0, tiles_n, cut_all);
+  if (0.97 * tall <= two) return launch_rows<ROUTE>(p, 256, st, 0, tiles_n);
   const int rc = launch_rows<ROUTE>(p, 256, st, 0, tn_full);
   return rc != QG_OK ? rc : launch_rows<ROUTE>(p, 128, st, tn_full, tiles_n - tn_full, cut_rest);
 }
