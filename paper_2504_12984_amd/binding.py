@@ -105,10 +105,15 @@ _DT = {torch.float16: QG_F16, torch.bfloat16: QG_BF16}
 _SDT = {torch.float16: QG_F16, torch.bfloat16: QG_BF16, torch.uint8: QG_E8M0}
 
 
+# the raw handle of a device's current stream: building a Stream object around it takes 2.5 us of a call's 10.8.  It is no public
+# name, so a torch without it gets the Stream object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the raw handle of the current device's current stream; building a Stream object around it takes 2.5 us
-    # of a call's 10.8
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t, name):
