@@ -21,7 +21,6 @@ def _grid(full, half=0):
 
 
 U = "T(0, %d, 0, 0)"
-CLASSES = {"u4": ("qgemm", U % 4), "u8": ("qgemm", U % 8), "e2m1": ("qgemm", "T(2, 4, 2, 1)"), "e2m2": ("qgemm", "T(2, 5, 2, 2)"), "e3m2": ("qgemm", "T(2, 6, 3, 2)")}
 
 
 def _calls(stub, calls, path=2):
@@ -59,6 +58,13 @@ def test_cut_of_other_types(stub, N, M, full, half):
         assert _tiles(c) == [(128, _grid(full, half))], (c["launches"], _tiles(c))
     dense, = _calls(stub, [_qgemm(U % 5, M, 256, N)], path=4)
     assert _tiles(dense) == [(128, _grid(full, half))]
+
+
+def test_e3m2_is_cut_as_the_types_with_a_quick_convert(stub):
+    # M = 257, K = 8192, N = 28672: 146 us in tiles of 128 and 64 rows, 198 in 256-row ones, which e2m2 takes
+    e2m1, e3m2, e4m3, e2m2 = _calls(stub, [_qgemm(f"T(2, {b}, {e}, {m})", 257, 8192, 28672) for b, e, m in ((4, 2, 1), (6, 3, 2), (8, 4, 3), (5, 2, 2))])
+    assert _tiles(e3m2) == _tiles(e2m1) == _tiles(e4m3) == [(128, _grid(224, 112))]
+    assert _tiles(e2m2) == [(256, _grid(224))]
 
 
 @pytest.mark.parametrize("N,M,full,half", [
