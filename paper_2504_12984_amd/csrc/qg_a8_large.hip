@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256, 2) void a8_large_kernel(A8Params p, int tiles_
 
 template <int GPC, int BM, bool SBF16, bool SPLIT, bool CORR>
 static int launch_one(const A8Params& p, int cut, hipStream_t st) {
-  const bool last64 = BM == 128 && p.M % 128 >= 1 && p.M % 128 <= 64;
+  const bool last64 = BM == 128 && large_last64(p.M);
   const int tiles_m = last64 ? p.M / 128 : (p.M + BM - 1) / BM, tiles_n = (p.N + A8_BN - 1) / A8_BN;
   if (cut < 0 || cut > tiles_m * tiles_n || (cut && (BM != 128 || SPLIT))) return QG_EINVAL;
   const int full = tiles_m * tiles_n - cut, half = 2 * cut + (last64 ? tiles_n : 0);
