@@ -654,15 +654,21 @@ static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   // other columns in 128-row tiles, in a second launch (4 us); all in 128-row tiles, or 256 more of them than a whole number
   // of rounds leaves and the others as halves.  A last row tile of at most 64 rows costs only that in 128-row tiles.
   // Types whose unpack no longer hides between the matrix instructions pay more for lower tiles, which unpack a weight more often: relative to 2.86, floats
-  // without a quick hardware convert 1.66 and 1.12, codebooks 1.77 and 1.05, of more than 4 bits, and 16-bit weights, 1.88 and 1.36 (at the integers' values codebooks were 2 % longer on
-  // average than with 256-row tiles: 8 bits, M = 1500, K = 4096, N = 57344 918 us against 742, 4 bits, M = 700, N = 14336 110 against 95).  e3m2 has the integers' values
-  // (104 calls, M = 129 .. 1300, groups of 64 and 128: 22 in 128-row tiles for 256-row ones, 7 % shorter on average; M = 257, K = 8192, N = 28672 198 us and 146).
+  // without a quick hardware convert 1.66 and 1.12 (e3m2 has one: 104 calls, M = 129 .. 1300, 22 of them in 128-row tiles for 256-row ones, 7 % shorter on
+  // average; M = 257, K = 8192, N = 28672 198 us and 146), codebooks of up to 4 bits 1.77 and 1.05 (M = 700, K = 4096, N = 14336 95 us, by the integers' values 110).
+  // Those whose 128-row tiles have a CU to themselves 1.88 and 1.36: 16-bit weights for their registers (M = 1500, K = 4096, N = 57344
+  // 742 us, by the integers' values 918), 8-bit codebooks for their table (32 KiB of LDS).  Codebooks of 5 to 7 bits have the integers' values with fp16 activations, 1.66 and 1.05 with
+  // bf16, whose rounding takes more (224 calls, M = 129 .. 1000, every way of cutting timed: 2 % longer than the shortest on average, 14 % by the values of 8 bits;
+  // 6 bits, K = 8192, N = 28672, M = 300: fp16 298 us in 256-row tiles, 208 in 128- and 64-row ones, bf16 262 and 246, M = 1000 520 and 550).
   // The second has to be 3 % better than the first, the third 4 % than both: with full rounds the card's power bounds all of them.  u4, us, with the first two alone and now: K = 8192,
   // N = 28672: M = 300 171.5 and 141.2, M = 600 274.8 and 253.8, M = 1100 478.2 and 402.3; N = 57344: M = 150 165.1 and 147.3, M = 300 335.3 and
   // 258.1; K = 4096, N = 14336, M = 1100 147.1 and 104.3 (120 calls of 65 to 2048 rows 6 % shorter on average, none more than 3 % longer).
-  constexpr bool LUT = wt_is_lut(QG_WT), DENSE = QG_WT == WT_DENSE16, WIDE = wt_bits(QG_WT) > 4, SOFT = wt_is_float(QG_WT) && !wt_natural(QG_WT);
+  constexpr bool LUT = wt_is_lut(QG_WT), SOFT = wt_is_float(QG_WT) && !wt_natural(QG_WT);
+  constexpr bool ALONE = QG_WT == WT_DENSE16 || (LUT && wt_bits(QG_WT) == 8), SHORT = LUT && wt_bits(QG_WT) <= 4;
+  constexpr bool WIDE_BF16 = LUT && !ALONE && !SHORT && ROUTE == ROUTE_BF16;
   constexpr double TALL = 2.86, SECOND_LAUNCH = 4.0;
-  constexpr double HIGH = LUT || DENSE ? (WIDE ? 1.88 : 1.77) : SOFT ? 1.66 : 1.43, LOW = LUT || DENSE ? (WIDE ? 1.36 : 1.05) : SOFT ? 1.12 : 0.83;
+  constexpr double HIGH = ALONE ? 1.88 : SHORT ? 1.77 : SOFT || WIDE_BF16 ? 1.66 : 1.43;
+  constexpr double LOW = ALONE ? 1.36 : SHORT || WIDE_BF16 ? 1.05 : SOFT ? 1.12 : 0.83;
   auto mixed = [&](int cols, int* cut) {
     const int64_t high = (int64_t)(large_last64(p.M) ? p.M / 128 : (p.M + 127) / 128) * cols, low = large_last64(p.M) ? cols : 0, over = high % 256;
     const double whole = tiles_level(high, low, HIGH, LOW, 0.0), some = over ? tiles_level(high - over, low + 2 * over, HIGH, LOW, 0.0) : whole;

@@ -67,6 +67,15 @@ def test_e3m2_is_cut_as_the_types_with_a_quick_convert(stub):
     assert _tiles(e2m2) == [(256, _grid(224))]
 
 
+def test_only_the_8_bit_table_leaves_a_cu_one_workgroup(stub):
+    # M = 300, K = 8192, N = 28672, 6 bits: 208 us in tiles of 128 and 64 rows, 298 in 256-row ones; 8 bits: 311 and 286
+    calls = _calls(stub, [f"codebook(300, 8192, 28672, {bits})" for bits in (5, 6, 7, 8)])
+    assert [_tiles(c) for c in calls] == 3 * [[(128, _grid(224, 112))]] + [[(256, _grid(224))]]
+    # bf16, M = 1000: 520 us in 256-row tiles, 550 with lower ones behind 64 columns of them
+    bf16 = "call(lib.qgemm_codebook(A, A, A, A, 6, 1, 1, 128, %d, 28672, 8192, A, 1))"
+    assert [_tiles(c) for c in _calls(stub, [bf16 % 300, bf16 % 1000])] == [[(128, _grid(224, 112))], [(256, _grid(448))]]
+
+
 @pytest.mark.parametrize("N,M,full,half", [
     (16384, 257, 128, 64), (16448, 320, 130, 65), (16384, 600, 256, 128), (16448, 700, 256, 203), (16448, 1100, 512, 146), (16384, 1600, 768, 64)])
 def test_heights_int8(stub, N, M, full, half):
