@@ -358,7 +358,8 @@ static double streaming_cost(int M, int N, int K, int bits, int variant, int spl
 // 1056 calls (22 shapes, M = 1 .. 64, u4, u8, int2, e2m2, e3m2, 4-bit codebook): 180 get other slabs and are 1.04 to 1.57 times as fast, 1.29 on average.
 // The int8 kernel by the same estimate (285 calls, 19 shapes, u4, i8, int2, each in 1 to 8 slabs): 0.2 % longer than the best on average, by doubling 19.6 %;
 // K = 4096, N = 14336, u4, M = 16 11.0 us in two slabs, whole 8.2; K = 13824, N = 5120 15.1 in four, 10.3 in three.
-// A call that needs no workspace keeps doing without, and more than four slabs come from doubling alone.
+// A call that needs no workspace keeps doing without.  Looked at are up to four slabs, or as many as doubling came to
+// (eight at most: K = 16384, N = 3072, 48 strips, u8, M = 8 15.2 us, in five 13.0; e4m3, M = 16 15.0 and 12.9).
 static int better_split(int M, int N, int K, int bits, int variant, int splitk) {
   if (splitk == 1) return 1;
   const int KC = K / TILE_K, NCH = N / TILE_N, mt = variant / 10;
@@ -493,8 +494,8 @@ static int launch_streaming(GemmParams& p, int wt, int route, int ws_mode, hipSt
   return wt_is_lut(wt) ? kDecodeLut[wt - WT_LUT0](p, route, variant, st) : kDecode[wt](p, route, variant, st);
 }
 
-// Tiled kernel of the first layout: row-tile height (0 = the kernel's own choice between
-// 256 and 128 rows by rounds of workgroups) and split-K.  Host arithmetic only.
+// Tiled kernel of the first layout: row-tile height (0 = the kernel's own choice: tiles of 256 rows, or of 128 and 64 in one
+// launch, or both) and split-K.  Host arithmetic only.
 //
 // Split-K serves the lower row tiles when they would leave CUs idle.  Candidates: 64- or
 // 128-row tiles, K cut into 1 to 8 slabs of an even number of chunks (the kernel
@@ -908,8 +909,9 @@ static void plan_a8(int M, int N, int K, int bits, int* waves_out, int* splitk_o
 // Workgroups (64 or 128 x 256 tiles times K-slabs) sit two to a CU.  A chunk of K takes a 128-row tile 1.45 us alone
 // on a CU and 2.3 with a neighbour, a 64-row tile 1.0 and 1.5 (2 % more per bit above 4, group 64 30 %); a launch 6 us; the
 // exchange of partial sums 4 + 0.12 per MB + 1.2 per slab of 64 rows that the last one of a tile reads.  Fitted to M = 65 .. 1000,
-// K = 2048 .. 14336, N = 4096 .. 28672, u4, i8, groups 64 and 128 (640 points, 7 % rms); what it picks takes 3.6 % longer than the best
-// of all heights and splits on average.  64-row tiles: M = 300, K = N = 8192, u4 60.6 -> 44.4 us in three slabs, M = 128
+// K = 2048 .. 14336, N = 4096 .. 28672, u4, i8, groups 64 and 128 (640 points, 7 % rms) when a launch had tiles of one height; what it
+// picked took 3.6 % longer than the best of all heights and splits on average (252 calls with both heights, M = 100 .. 1100: 4 % shorter than
+// then on average, none longer).  64-row tiles: M = 300, K = N = 8192, u4 60.6 -> 44.4 us in three slabs, M = 128
 // 36.9 -> 29.2, K = N = 4096, M = 200 36.1 -> 23.2; 128-row tiles stay where they fill the chip.
 // A chunk of K on the fullest CU.  One launch of both heights (a8_large_kernel): a last row tile of at most 64 rows costs that and no
 // more, and 128-row tiles beyond whole rounds of 256 are computed as halves where that is shorter.  us, before and now: K = 8192, N = 28672,
@@ -953,7 +955,7 @@ static double plan_a8_tiled(int64_t rows, int64_t N, int64_t K, int64_t group, i
 
 // int8 activations on more than 64 rows: the tiled kernel, or blocks of 64 rows through the streaming kernel?
 // The latter take 8 us + 0.16 per million weights (6 % more per bit above 4) each (a last block of up to 16 rows 0.48 of that, of
-// up to 32 rows 0.65, 48 0.85), and win while the tiled kernel's chip is nearly empty: M = 65 on K = N = 8192 26.9 us against 28.5,
+// up to 32 rows 0.65, 48 0.85), and win while the tiled kernel's chip is nearly empty (an estimate from before the streaming kernel's slabs were chosen by theirs): M = 65 on K = N = 8192 26.9 us against 28.5,
 // M = 128 36.7 against 29.1; M = 96 on K = N = 4096 a tie (19.7); M = 1000 on N = 28672 750 against 287.
 static bool plan_a8_path(int64_t M, int64_t N, int64_t K, int64_t group, int bits) {
   if (knob(0) == 2 || knob(0) == 3) return knob(0) == 2;

@@ -191,7 +191,9 @@ constexpr int LARGE_GROUP_M = 4;
 constexpr int LARGE_MEET = 3;      // up to so many K-slabs meet inside the tiled kernel, more in reduce_tiles_kernel
 // Tiled kernels, workgroups of 128 and of 64 rows in one launch, two to a CU: how many of the former an XCD (32 CUs) starts ahead of the
 // latter.  Where they come out at an odd number a CU, one each, so that a CU has one of either kind and none
-// is left alone at the end; where at an even one, all, and the lower ones fill the end.
+// is left alone at the end; where at an even one, all, and the lower ones fill the end.  `full`: tiles, which are workgroups where K is whole.
+// Slabs of 128-row tiles and of lower ones come to at most 256 workgroups (their partial sums fill the workspace), fewer than 256 of
+// them the former: less than one a CU either way.
 inline int tiles_ahead(int64_t full) { return (full / 256) % 2 ? 32 : 1 << 30; }
 // What `high` workgroups of 128 rows and `low` of 64 take on 256 CUs, as the sum of `a` for each of the former that a CU has and
 // `b` for each of the latter, plus `one` where the last of the fullest CU has no neighbour: the least level that holds all of them.

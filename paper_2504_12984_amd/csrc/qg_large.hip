@@ -650,19 +650,23 @@ static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   // CUs work (measured 10-15 % shorter: M = 128 on 28672 columns, M = 256..512 on 8192)
   if (large_prefers_64_rows(p.M, p.N)) return launch_rows<ROUTE>(p, 64, st, 0, tiles_n);
   // Otherwise by what a chunk takes, in microseconds (u4): a 256-row tile, which has a CU to itself, 2.86, a 128-row one 1.43 and
-  // a 64-row one 0.83, with a neighbour or one after the other.  Three ways to cut the rows: 256-row tiles; whole rounds of them and the
-  // other columns in 128-row tiles, in a second launch (4 us); all in 128-row tiles, or 256 more of them than a whole number
-  // of rounds leaves and the others as halves.  A last row tile of at most 64 rows costs only that in 128-row tiles.
-  // Types whose unpack no longer hides between the matrix instructions pay more for lower tiles, which unpack a weight more often: relative to 2.86, floats
-  // without a quick hardware convert 1.66 and 1.12 (e3m2 has one: 104 calls, M = 129 .. 1300, 22 of them in 128-row tiles for 256-row ones, 7 % shorter on
-  // average; M = 257, K = 8192, N = 28672 198 us and 146), codebooks of up to 4 bits 1.77 and 1.05 (M = 700, K = 4096, N = 14336 95 us, by the integers' values 110).
-  // Those whose 128-row tiles have a CU to themselves 1.88 and 1.36: 16-bit weights for their registers (M = 1500, K = 4096, N = 57344
-  // 742 us, by the integers' values 918), 8-bit codebooks for their table (32 KiB of LDS).  Codebooks of 5 to 7 bits have the integers' values with fp16 activations, 1.66 and 1.05 with
-  // bf16, whose rounding takes more (224 calls, M = 129 .. 1000, every way of cutting timed: 2 % longer than the shortest on average, 14 % by the values of 8 bits;
-  // 6 bits, K = 8192, N = 28672, M = 300: fp16 298 us in 256-row tiles, 208 in 128- and 64-row ones, bf16 262 and 246, M = 1000 520 and 550).
-  // The second has to be 3 % better than the first, the third 4 % than both: with full rounds the card's power bounds all of them.  u4, us, with the first two alone and now: K = 8192,
-  // N = 28672: M = 300 171.5 and 141.2, M = 600 274.8 and 253.8, M = 1100 478.2 and 402.3; N = 57344: M = 150 165.1 and 147.3, M = 300 335.3 and
-  // 258.1; K = 4096, N = 14336, M = 1100 147.1 and 104.3 (120 calls of 65 to 2048 rows 6 % shorter on average, none more than 3 % longer).
+  // a 64-row one 0.83, with a neighbour or one after the other.  Three ways to cut the rows: 256-row tiles; whole rounds of them
+  // and the other columns in 128-row tiles, in a second launch (4 us), which has to be 3 % better; all in 128-row tiles, or 256
+  // more of them than a whole number of rounds leaves and the others as halves, which has to be 4 % better than both: with full
+  // rounds the card's power bounds all of them.  A last row tile of at most 64 rows costs only that in 128-row tiles; where that
+  // saves no round (M = 150, K = 8192, N = 28672) it is up to 6 % shorter still, for none of 19 types longer.
+  // Types whose unpack no longer hides between the matrix instructions pay more for lower tiles, which unpack a weight more often;
+  // HIGH and LOW relative to 2.86:
+  //   16-bit weights and 8-bit codebooks, whose 128-row tiles have a CU to themselves (registers; a table of 32 KiB in LDS): 1.88,
+  //     1.36.  16 bits behind their de-quantiser, M = 1500, K = 4096, N = 57344 742 us, by the integers' values 918
+  //   codebooks of 5 to 7 bits: the integers' with fp16 activations, 1.66 and 1.05 with bf16, whose rounding takes more.  6 bits,
+  //     K = 8192, N = 28672, M = 300: fp16 298 us in 256-row tiles, 208 in lower ones, bf16 262 and 246, M = 1000 520 and 550
+  //   of up to 4 bits: 1.77, 1.05.  M = 700, K = 4096, N = 14336 94 us, by the integers' values 108
+  //   floats without a quick hardware convert: 1.66, 1.12.  e3m2 has one: M = 257, K = 8192, N = 28672 198 us in 256-row tiles, 146
+  // 983 calls (15 types, groups of 32 to 128, M = 129 .. 1300, every way of cutting timed five times in turn): what is taken is 0.5 to
+  // 1.5 % longer than the shortest on average, 2 to 3 % for e1m1, e2m2, e3m2 and, with fp16, codebooks of 5 to 7 bits.  452 calls
+  // (19 types, M = 100 .. 1100) against 256-row tiles with 128-row ones behind them: 7 % shorter on average, none longer by more
+  // than the 3 % that launches of the same tiles differ by.
   constexpr bool LUT = wt_is_lut(QG_WT), SOFT = wt_is_float(QG_WT) && !wt_natural(QG_WT);
   constexpr bool ALONE = QG_WT == WT_DENSE16 || (LUT && wt_bits(QG_WT) == 8), SHORT = LUT && wt_bits(QG_WT) <= 4;
   constexpr bool WIDE_BF16 = LUT && !ALONE && !SHORT && ROUTE == ROUTE_BF16;
