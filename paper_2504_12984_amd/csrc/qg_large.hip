@@ -665,7 +665,7 @@ static int launch_route(const GemmParams& p, int bm, hipStream_t st) {
   //   floats without a quick hardware convert: 1.66, 1.12.  e3m2 has one: M = 257, K = 8192, N = 28672 198 us in 256-row tiles, 146
   // 983 calls (15 types, groups of 32 to 128, M = 129 .. 1300, every way of cutting timed five times in turn): what is taken is 0.5 to
   // 1.5 % longer than the shortest on average, 2 to 3 % for e1m1, e2m2, e3m2 and, with fp16, codebooks of 5 to 7 bits.  452 calls
-  // (19 types, M = 100 .. 1100) against 256-row tiles with 128-row ones behind them: 7 % shorter on average, none longer by more
+  // (19 types, M = 100 .. 1100) against 256-row tiles with 128-row ones behind them: 8 % shorter on average, none longer by more
   // than the 3 % that launches of the same tiles differ by.
   constexpr bool LUT = wt_is_lut(QG_WT), SOFT = wt_is_float(QG_WT) && !wt_natural(QG_WT);
   constexpr bool ALONE = QG_WT == WT_DENSE16 || (LUT && wt_bits(QG_WT) == 8), SHORT = LUT && wt_bits(QG_WT) <= 4;
